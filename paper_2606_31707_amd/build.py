@@ -8,51 +8,56 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libhlbm.so")
 CANARY_PATH = os.path.join(HERE, "libhlbm_canary.so")
-SOURCES = ["hlbm_launch.hip", "hlbm_api.hip"]
+SOURCES = ["hlbm_launch.hip", "hlbm_march2d.hip", "hlbm_api.hip"]
 ARCH = os.environ.get("HLBM_OFFLOAD_ARCH", "gfx950")
 CANARY_DEFINES = ["-DHLBM_TILE_BX=64", "-DHLBM_XCD_REMAP=0"]
 
 
-def _command(out: str, defines) -> list:
-    return [
-        "hipcc", "-O3", f"--offload-arch={ARCH}", "-std=c++17", "-fPIC", "-shared",
-        "-Wall", "-Wno-unused-function",
-        # multiply-adds fused per source expression only, so the same inlined
-        # per-cell code rounds identically in every kernel that contains it
-        "-ffp-contract=on",
-        # no packed FP32 instructions in device code
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        *defines, "-o", out + ".tmp",
-    ] + [os.path.join(CSRC, s) for s in SOURCES]
+FLAGS = [
+    "-O3", f"--offload-arch={ARCH}", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
+    # multiply-adds fused per source expression only, so the same inlined
+    # per-cell code rounds identically in every kernel that contains it
+    "-ffp-contract=on",
+    # no packed FP32 instructions in device code
+    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+]
 
 
 def build(verbose: bool = False, canary: bool = True) -> str:
-    jobs = [(LIB_PATH, [])] + ([(CANARY_PATH, CANARY_DEFINES)] if canary else [])
-    procs = []
-    for out, defines in jobs:
-        cmd = _command(out, defines)
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        procs.append((out, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)))
-    failed = False
-    for out, p in procs:
-        _, stderr = p.communicate()
-        # the host pass warns about the device-only target feature; keep other diagnostics
-        err = "\n".join(l for l in stderr.splitlines() if "packed-fp32-ops" not in l and l.strip())
-        if p.returncode != 0:
-            sys.stderr.write(err + "\n")
-            failed = True
-            continue
-        if err and verbose:
-            sys.stderr.write(err + "\n")
-        os.replace(out + ".tmp", out)
-    if failed:
-        raise RuntimeError("hipcc failed building the HLBM library")
+    """Compiles every source of both libraries (one object each, in parallel),
+    then links them."""
+    libs = [(LIB_PATH, [])] + ([(CANARY_PATH, CANARY_DEFINES)] if canary else [])
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+        def run(cmd):
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+            # the host pass warns about the device-only target feature; keep other diagnostics
+            err = "\n".join(l for l in p.stderr.splitlines() if "packed-fp32-ops" not in l and l.strip())
+            if err and (verbose or p.returncode != 0):
+                sys.stderr.write(err + "\n")
+            return p.returncode == 0
+
+        jobs = []
+        for i, (out, defines) in enumerate(libs):
+            for s in SOURCES:
+                obj = os.path.join(tmp, f"{i}_{s}.o")
+                jobs.append((out, obj, pool.submit(run, ["hipcc", *FLAGS, *defines, "-c", "-o", obj,
+                                                         os.path.join(CSRC, s)])))
+        if not all([j.result() for _, _, j in jobs]):
+            raise RuntimeError("hipcc failed building the HLBM library")
+        for out, _ in libs:
+            objs = [o for lib, o, _ in jobs if lib == out]
+            if not run(["hipcc", f"--offload-arch={ARCH}", "-shared", "-o", out + ".tmp", *objs]):
+                raise RuntimeError("hipcc failed linking the HLBM library")
+            os.replace(out + ".tmp", out)
     return LIB_PATH
 
 

@@ -57,16 +57,36 @@ void dev_free(void* p) {
 
 // Buffers owned by a lattice are allocated and freed through these, which
 // keep the handle's record of its device memory.
-hlbm_status lat_alloc(hlbm_lattice_s* L, void** p, size_t bytes) {
-  if (*p) return HLBM_OK;
-  hlbm_status s = dev_alloc(p, bytes);
-  if (s == HLBM_OK) L->allocs[*p] = bytes ? bytes : 256;
-  return s;
-}
 void lat_free(hlbm_lattice_s* L, void* p) {
   if (!p) return;
   L->allocs.erase(p);
   dev_free(p);
+}
+// The second arrays of the multi-step passes hold nothing between calls: they
+// are given back when a buffer that is needed does not fit beside them.
+bool give_back_second_arrays(hlbm_lattice_s* L) {
+  if (!L->f2) return false;
+  (void)hipStreamSynchronize(L->stream);
+  lat_free(L, L->f2);
+  L->f2 = nullptr;
+  return true;
+}
+hlbm_status lat_alloc(hlbm_lattice_s* L, void** p, size_t bytes) {
+  if (*p) return HLBM_OK;
+  hlbm_status s = dev_alloc(p, bytes);
+  if (s == HLBM_E_OOM && give_back_second_arrays(L)) s = dev_alloc(p, bytes);
+  if (s == HLBM_OK) L->allocs[*p] = bytes ? bytes : 256;
+  return s;
+}
+// A second array is taken only where a quarter of the device's memory stays
+// free beside it: without it the lattice runs single steps in place.
+void lat_alloc_second(hlbm_lattice_s* L, void** p, size_t bytes) {
+  size_t avail = 0, total = 0;
+  if (*p || hipMemGetInfo(&avail, &total) != hipSuccess || avail < bytes || avail - bytes < total / 4) return;
+  void* q = nullptr;
+  if (dev_alloc(&q, bytes) != HLBM_OK) return;
+  *p = q;
+  L->allocs[q] = bytes;
 }
 
 // Scratch of the allocation-free entry point (hlbm_set_porosity_noalloc): a
@@ -251,13 +271,23 @@ hlbm_status prof_collect_all(hlbm_lattice_s* L) {
   return HLBM_OK;
 }
 
-// Launches one sweep of the given kind.  With profiling on, the launches are
+bool stream_capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;  // unknown (a legacy stream while another one captures)
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
+// Launches `sweeps` sweeps of the given kind (one, or those of a multi-step
+// pass, which counts as that many).  With profiling on, the launches are
 // timed in blocks of up to prof_every back-to-back launches of one kind; a
 // block never extends past the caller's run of `remaining` consecutive sweeps
 // (other kernels follow it), so the block time per launch is the sweep's
 // duration in a steady stream of launches, dispatch gaps included.
 template <typename F>
-hlbm_status timed_launch(hlbm_lattice_s* L, int kind, int64_t remaining, F&& launch) {
+hlbm_status timed_launch(hlbm_lattice_s* L, int kind, int64_t remaining, int64_t sweeps, F&& launch) {
   if (L->prof_every <= 0) {
     hipError_t e = launch();
     if (e != hipSuccess) return fail(HLBM_E_DEVICE, "sweep launch: %s", hipGetErrorString(e));
@@ -281,8 +311,8 @@ hlbm_status timed_launch(hlbm_lattice_s* L, int kind, int64_t remaining, F&& lau
   hipError_t e = launch();
   if (e != hipSuccess) return fail(HLBM_E_DEVICE, "sweep launch: %s", hipGetErrorString(e));
   const int slot = L->prof_open;
-  L->prof_slot_n[slot] += 1;
-  if (L->prof_slot_n[slot] >= L->prof_every || remaining <= 1) {  // close the block
+  L->prof_slot_n[slot] += sweeps;
+  if (L->prof_slot_n[slot] >= L->prof_every || remaining <= sweeps) {  // close the block
     HIP_TRY(hipEventRecord(L->prof_ev[slot][1], L->stream));
     L->prof_slot_kind[slot] = L->prof_open_kind;
     L->prof_open = -1;
@@ -368,14 +398,15 @@ hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out) {
   // 256 MiB Infinity Cache (D2Q9 measured 160 MB slower with them, 320 MB
   // faster); which steps take them is decided per stencil at launch
   const int64_t sweep_bytes = (int64_t)(L->ssize * L->q + L->dsize) * L->plane;
-  L->stream_nt = desc->cache_policy == HLBM_CACHE_STREAMING ||
-                 (desc->cache_policy == HLBM_CACHE_AUTO && sweep_bytes > ((int64_t)256 << 20));
+  L->large = sweep_bytes > ((int64_t)256 << 20);
+  L->stream_nt = desc->cache_policy == HLBM_CACHE_STREAMING || (desc->cache_policy == HLBM_CACHE_AUTO && L->large);
   auto bail = [&](hlbm_status st) {
     hlbm_destroy(L);
     return st;
   };
   if ((s = lat_alloc(L, &L->f, L->ssize * L->q * L->plane)) != HLBM_OK) return bail(s);
   if ((s = lat_alloc(L, &L->dpor, L->dsize * L->plane)) != HLBM_OK) return bail(s);
+  if (primal_passes(L)) lat_alloc_second(L, &L->f2, L->ssize * L->q * L->plane);
   if ((s = lat_alloc(L, &L->ghost, L->ssize * L->q * L->gplane)) != HLBM_OK) return bail(s);
   if ((s = ensure_partials(L, 2 * n_blocks(L) + 8)) != HLBM_OK) return bail(s);
   if (hipHostMalloc((void**)&L->red_host, 4 * sizeof(double)) != hipSuccess)
@@ -399,7 +430,7 @@ hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out) {
 void hlbm_destroy(hlbm_lattice L) {
   if (!L) return;
   (void)hipStreamSynchronize(L->stream);
-  void* bufs[] = {L->f,   L->dpor,  L->ghost, L->acc_rho, L->acc_j, L->acc_f, L->acc_tau, L->acc_obj, L->acc_pend,
+  void* bufs[] = {L->f,   L->f2,    L->dpor,  L->ghost, L->acc_rho, L->acc_j, L->acc_f, L->acc_tau, L->acc_obj, L->acc_pend,
                   L->phi, L->prep,  L->src,   L->gdat,    L->oprep, L->pv[0], L->pv[1],   L->snap,
                   L->red, L->usnap, L->probe_buf, L->mea_flag, L->mea_src, L->rcopy, L->tan_f, L->tan_ghost,
                   L->tan_v, L->tan_rec};
@@ -703,6 +734,9 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
     if ((s = lat_alloc(L, (void**)&L->usnap, sizeof(double) * L->plane * L->dim)) != HLBM_OK) return s;
   }
   const int64_t nb = n_blocks(L);
+  // Multi-step passes swap the two population arrays: a captured run, whose
+  // replays start from the same array every time, takes single steps.
+  const bool multi = L->f2 != nullptr && !stream_capturing(L->stream);
   // snapshot of u at the start of a steady run
   if (steady_tol > 0.0) {
     int nbl = 0;
@@ -717,14 +751,17 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
   while (done < n_steps) {
     int64_t chunk = n_steps - done;
     if (steady_tol > 0.0 && chunk > check_every) chunk = check_every;
-    for (int64_t k = 0; k < chunk; ++k) {
-      s = timed_launch(L, accumulate ? 1 : 0, chunk - k,
-                       [&]() { return launch_primal_step(L, accumulate); });
+    for (int64_t k = 0; k < chunk;) {
+      const int K = multi && L->parity == 0 ? primal_pass_steps(L, accumulate, chunk - k) : 1;
+      s = timed_launch(L, accumulate ? 1 : 0, chunk - k, K, [&]() {
+        return K > 1 ? launch_primal_pass(L, accumulate, K) : launch_primal_step(L, accumulate);
+      });
       if (s != HLBM_OK) return s;
-      L->parity ^= 1;
-      L->steps += 1;
-      if (accumulate) L->nsamp += 1;
-      if (L->probe_buf) L->probe_n += 1;
+      L->parity ^= K & 1;
+      L->steps += K;
+      if (accumulate) L->nsamp += K;
+      if (L->probe_buf) L->probe_n += K;
+      k += K;
     }
     done += chunk;
     if (steady_tol > 0.0) {
@@ -884,7 +921,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
     int64_t chunk = iters - done;
     if (o->tol > 0.0 && chunk > M) chunk = M;
     for (int64_t k = 0; k < chunk; ++k) {
-      s = timed_launch(L, 2, chunk - k, [&]() { return launch_adjoint_step(L); });
+      s = timed_launch(L, 2, chunk - k, 1, [&]() { return launch_adjoint_step(L); });
       if (s != HLBM_OK) return s;
       L->pvcur ^= 1;
       L->adj_iters += 1;

@@ -22,10 +22,12 @@ struct hlbm_lattice_s {
   hipStream_t stream = nullptr;
 
   // primal state
+  void* f2 = nullptr;     // a second population array: the multi-step passes read f, write f2 and swap
   void* f = nullptr;      // q * plane stored populations (AA pattern, in place)
   void* dpor = nullptr;   // plane porosity values
   void* ghost = nullptr;  // q * gplane outlet virtual values (even -> odd step)
   bool stream_nt = false;  // streaming load/store hints in the sweeps
+  bool large = false;      // populations and porosity exceed the Infinity Cache
   int parity = 0;         // 0: canonical layout; 1: after an even (local) step
   int64_t steps = 0;
 
@@ -176,6 +178,12 @@ hipError_t launch_mea_flags(hlbm_lattice_s* L);
 hipError_t launch_tangent_step(hlbm_lattice_s* L);
 hipError_t launch_tangent_objective(hlbm_lattice_s* L, double* partials, int* nblocks);
 hipError_t launch_primal_step(hlbm_lattice_s* L, int accumulate);
+// Multi-step passes (L->f2 present, parity 0): whether the lattice has them,
+// how many of `left` steps the next launch takes (1: a single step), and a
+// pass of K steps, which reads L->f, writes L->f2 and swaps the two.
+bool primal_passes(const hlbm_lattice_s* L);
+int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left);
+hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K);
 hipError_t launch_gather(hlbm_lattice_s* L, double* out_dev);
 hipError_t launch_scatter(hlbm_lattice_s* L, const double* in_dev);
 hipError_t launch_moments(hlbm_lattice_s* L, double* rho_dev, double* u_dev);

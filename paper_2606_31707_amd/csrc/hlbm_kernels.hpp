@@ -530,15 +530,26 @@ __device__ __forceinline__ void load_state(const Geo& g, const S* __restrict__ A
   }
 }
 
+// Shifted equilibrium of direction k at density 1 and inflow speed ui along x.
+template <int Q, typename T>
+__device__ __forceinline__ T inlet_value(int k, T ui) {
+  using L = Lat<Q>;
+  const T cu = (T)L::cx[k] * ui;
+  return (T)L::w[k] * ((T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * ui * ui);
+}
 template <int Q, typename T>
 __device__ __forceinline__ void inlet_state(const Geo& g, int y, T (&s)[Q]) {
-  using L = Lat<Q>;
   const T ui = inlet_velocity<T>(g, y);
 #pragma unroll
-  for (int k = 0; k < Q; ++k) {
-    const T cu = (T)L::cx[k] * ui;
-    s[k] = (T)L::w[k] * ((T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * ui * ui);
-  }
+  for (int k = 0; k < Q; ++k) s[k] = inlet_value<Q, T>(k, ui);
+}
+// The outlet's virtual column: shifted equilibrium of direction k at density
+// 1 and velocity (ux, uy, uz), uu its square.
+template <int Q, typename T>
+__device__ __forceinline__ T outlet_value(int k, T ux, T uy, T uz, T uu) {
+  using L = Lat<Q>;
+  const T cu = (T)L::cx[k] * ux + (T)L::cy[k] * uy + (T)L::cz[k] * uz;
+  return (T)L::w[k] * ((T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * uu);
 }
 
 // HRRLBM collision (Sec. 2.2, Eq. HRRLBM) on shifted populations s = f - w:
@@ -741,6 +752,68 @@ __host__ __device__ constexpr bool adjoint_runs() {
 // AA propagation with boundaries, fused FP64 window accumulation.
 // =========================================================================
 
+// Relaxation of one cell from its pre-collision state: tau_eff and omega =
+// 1 / tau_eff (the molecular ones without the closure), and the second moments
+// p2, which the closure and the HRR collision share (formed where needed).
+template <int Q, typename T, bool HRR>
+__device__ __forceinline__ void relaxation(const Coll& c, const bool smag, const T (&s)[Q], T drho, T jx, T jy, T jz,
+                                           T ir, T& omega, T& taue, T (&p2)[6]) {
+  omega = (T)c.omega0;
+  taue = (T)c.tau0;
+  if constexpr (HRR) second_moments<Q, T>(s, p2);
+  if (smag) {
+    T P[6];
+    if constexpr (HRR)
+      neq_from_moments<Q, T>(p2, drho, jx, jy, jz, ir, P);
+    else
+      neq_flux<Q, T>(s, drho, jx, jy, jz, ir, P);
+    const T tau0 = (T)c.tau0;
+    taue = (T)0.5 * (tau0 + sqrt(tau0 * tau0 + (T)c.kS * sqrt(frob2(P))));
+    omega = recip(taue);  // refined hardware reciprocal, as for 1/rho
+  }
+}
+
+// Post-collision state of one cell (s in place), HLBM-BGK or HRRLBM, body
+// force included; every sweep form of the primal step runs this code.
+template <int Q, typename T, bool HRR>
+__device__ __forceinline__ void collide_cell(const Coll& c, T (&s)[Q], T drho, T jx, T jy, T jz, T rho, T ir, T d,
+                                             T omega, const T (&p2)[6]) {
+  using L = Lat<Q>;
+  if constexpr (HRR) {
+    hrr_collide<Q, T>(s, drho, jx, jy, jz, ir, d, omega, c.force, p2);
+  } else {
+    // s <- (1 - omega) s + omega (f^eq(rho, u~) - w), u~ = d j / rho, written
+    // per opposite pair (k, opp k): with cu = xi_k . u~ the equilibrium is
+    // w (A0 + C cu^2) +- w B cu, A0 = drho - 1.5 rho u~^2, B = 3 rho,
+    // C = 4.5 rho; omega is folded into A0, B and C.
+    const T dir = d * ir;
+    const T tx = jx * dir, ty = jy * dir, tz = (L::D == 3) ? jz * dir : (T)0;
+    const T tt = (L::D == 3) ? tx * tx + ty * ty + tz * tz : tx * tx + ty * ty;
+    const T orho = omega * rho;
+    const T a0 = omega * drho - (T)1.5 * orho * tt;
+    const T b1 = (T)3 * orho, c2 = (T)4.5 * orho;
+    const T omc = (T)1 - omega;
+    s[0] = omc * s[0] + (T)L::w[0] * a0;
+#pragma unroll
+    for (int k = 1; k < Q; ++k) {
+      if (L::opp[k] < k) continue;
+      const int o = L::opp[k];
+      const T w = (T)L::w[k];
+      const T cu = csum<T>(L::cx[k], L::cy[k], L::cz[k], tx, ty, tz);
+      const T sym = (w * a0) + ((w * c2) * cu) * cu;
+      const T asy = (w * b1) * cu;
+      s[k] = omc * s[k] + (sym + asy);
+      s[o] = omc * s[o] + (sym - asy);
+    }
+    if (c.force[0] != 0.0 || c.force[1] != 0.0 || c.force[2] != 0.0) {  // body force 3 w xi.F
+#pragma unroll
+      for (int k = 1; k < Q; ++k)
+        s[k] += (T)(3.0 * L::w[k]) *
+                csum<T>(L::cx[k], L::cy[k], L::cz[k], (T)c.force[0], (T)c.force[1], (T)c.force[2]);
+    }
+  }
+}
+
 // One lattice update of cell (x, y, z) (inside the lattice), at lane offset
 // lo from its tile's first cell c0 (see plane_base).
 // ACC: 0 no window; 1 window with the moment-form objective terms; 2 window
@@ -889,20 +962,8 @@ __device__ __forceinline__ void primal_cell(const Geo& g, const Coll& c, const O
   const T ir = recip(rho);
 
   if (cell == c.probe_cell && !inlet) *c.probe_out = (double)(jy * ir);
-  T omega = (T)c.omega0;
-  T taue = (T)c.tau0;
-  T p2[6];  // second moments, shared by the closure and the HRR collision
-  if constexpr (HRR) second_moments<Q, T>(s, p2);
-  if (c.smag) {
-    T P[6];
-    if constexpr (HRR)
-      neq_from_moments<Q, T>(p2, drho, jx, jy, jz, ir, P);
-    else
-      neq_flux<Q, T>(s, drho, jx, jy, jz, ir, P);
-    const T tau0 = (T)c.tau0;
-    taue = (T)0.5 * (tau0 + sqrt(tau0 * tau0 + (T)c.kS * sqrt(frob2(P))));
-    omega = recip(taue);  // refined hardware reciprocal, as for 1/rho
-  }
+  T omega, taue, p2[6];
+  relaxation<Q, T, HRR>(c, c.smag != 0, s, drho, jx, jy, jz, ir, omega, taue, p2);
 
   // Objective terms of a region cell (moment form): from the pre-collision
   // moments, evaluated after the stores so that their temporaries do not
@@ -997,39 +1058,7 @@ __device__ __forceinline__ void primal_cell(const Geo& g, const Coll& c, const O
     }
   }
 
-  if constexpr (HRR) {
-    hrr_collide<Q, T>(s, drho, jx, jy, jz, ir, d, omega, c.force, p2);
-  } else {
-    // s <- (1 - omega) s + omega (f^eq(rho, u~) - w), u~ = d j / rho, written
-    // per opposite pair (k, opp k): with cu = xi_k . u~ the equilibrium is
-    // w (A0 + C cu^2) +- w B cu, A0 = drho - 1.5 rho u~^2, B = 3 rho,
-    // C = 4.5 rho; omega is folded into A0, B and C.
-    const T dir = d * ir;
-    const T tx = jx * dir, ty = jy * dir, tz = (L::D == 3) ? jz * dir : (T)0;
-    const T tt = (L::D == 3) ? tx * tx + ty * ty + tz * tz : tx * tx + ty * ty;
-    const T orho = omega * rho;
-    const T a0 = omega * drho - (T)1.5 * orho * tt;
-    const T b1 = (T)3 * orho, c2 = (T)4.5 * orho;
-    const T omc = (T)1 - omega;
-    s[0] = omc * s[0] + (T)L::w[0] * a0;
-#pragma unroll
-    for (int k = 1; k < Q; ++k) {
-      if (L::opp[k] < k) continue;
-      const int o = L::opp[k];
-      const T w = (T)L::w[k];
-      const T cu = csum<T>(L::cx[k], L::cy[k], L::cz[k], tx, ty, tz);
-      const T sym = (w * a0) + ((w * c2) * cu) * cu;
-      const T asy = (w * b1) * cu;
-      s[k] = omc * s[k] + (sym + asy);
-      s[o] = omc * s[o] + (sym - asy);
-    }
-    if (c.force[0] != 0.0 || c.force[1] != 0.0 || c.force[2] != 0.0) {  // body force 3 w xi.F
-#pragma unroll
-      for (int k = 1; k < Q; ++k)
-        s[k] += (T)(3.0 * L::w[k]) *
-                csum<T>(L::cx[k], L::cy[k], L::cz[k], (T)c.force[0], (T)c.force[1], (T)c.force[2]);
-    }
-  }
+  collide_cell<Q, T, HRR>(c, s, drho, jx, jy, jz, rho, ir, d, omega, p2);
 
   if (inlet) inlet_state<Q, T>(g, y, s);  // pinned: not collided
 
@@ -1042,8 +1071,7 @@ __device__ __forceinline__ void primal_cell(const Geo& g, const Coll& c, const O
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
         if (L::cx[k] != -1) continue;
-        const T cu = (T)L::cx[k] * ux + (T)L::cy[k] * uy + (T)L::cz[k] * uz;
-        const T vs = (T)L::w[k] * ((T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * uu);
+        const T vs = outlet_value<Q, T>(k, ux, uy, uz, uu);
         ghost[k * g.gplane + y + (int64_t)g.ny * z] = to_store<S>(vs);
       }
     }
@@ -1074,8 +1102,7 @@ __device__ __forceinline__ void primal_cell(const Geo& g, const Coll& c, const O
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
         if (L::cx[k] != -1) continue;
-        const T cu = (T)L::cx[k] * ux + (T)L::cy[k] * uy + (T)L::cz[k] * uz;
-        const T vs = (T)L::w[k] * ((T)3 * cu + (T)4.5 * cu * cu - (T)1.5 * uu);
+        const T vs = outlet_value<Q, T>(k, ux, uy, uz, uu);
         if (fast) {  // away from walls and seams (nx-1, y+cy, z+cz) is a lattice cell
           at(A, k * g.plane + c0 + (int64_t)L::cy[k] * g.nx + (int64_t)L::cz[k] * g.nx * g.ny, lo) = to_store<S>(vs);
         } else {
@@ -1812,7 +1839,7 @@ __global__ __launch_bounds__(256) void k_objective(const Geo g, const ObjBox ob,
   if (threadIdx.x + blockDim.x * threadIdx.y == 0) partials[linear_block()] = sum;
 }
 
-__global__ __launch_bounds__(256) void k_finalize_sum(const double* __restrict__ partials, int n,
+static __global__ __launch_bounds__(256) void k_finalize_sum(const double* __restrict__ partials, int n,
                                                       double* __restrict__ out) {
   __shared__ double lds[4];
   double v = 0.0;
@@ -1821,7 +1848,7 @@ __global__ __launch_bounds__(256) void k_finalize_sum(const double* __restrict__
   if (threadIdx.x == 0) out[0] = s;
 }
 
-__global__ __launch_bounds__(256) void k_finalize_max2(const double* __restrict__ partials, int n,
+static __global__ __launch_bounds__(256) void k_finalize_max2(const double* __restrict__ partials, int n,
                                                        double* __restrict__ out) {
   __shared__ double lds[4];
   double a = 0.0, b = 0.0;

@@ -1,0 +1,432 @@
+// hlbm_march2d.hpp -- D2Q9 sweeps that take K steps in one pass over memory.
+//
+// A wavefront owns a strip of 64 columns and marches down its rows; the K
+// time levels follow one another one row apart (level t works on row r - t
+// when level 0 works on row r), so a row is loaded once, goes through all K
+// levels in registers and is stored once.  Between the levels a population
+// moves along x by a lane shift (DPP) and along y by staying in registers for
+// up to two rows: per level boundary the nine values that a row still waits
+// for.  No LDS and no barrier: wavefronts are independent.
+//
+// Input and output are the canonical layout (parity 0) in two arrays, read
+// from one and written to the other: the last level pushes its post-collision
+// values to the neighbours' slots, each slot having one writer.  Level t is
+// valid on lanes [t, 63 - t], so 64 - 2 (K - 1) columns of a strip and the
+// rows of its chunk are its own and the rest is recomputed by the neighbours.
+// Every cell runs the per-cell code of the single-step sweeps, stored values
+// are rounded to the storage type between the levels: the results are
+// bitwise those of K single steps.
+//
+// What bounds it: a single step moves every population through memory once
+// (the sweeps of hlbm_kernels.hpp run at what an in-place copy reaches); a
+// pass of four moves them once for four steps, 2.9 times fewer bytes with the
+// halo, and then the vector units and the latency of a row's chain of levels
+// share the time (77 vector instructions a level in FP32, 84 in FP64).
+// Microseconds a step, single step -> pass: 8192 x 4096 FP32 448 -> 167,
+// FP64 912 -> 285, FP16S 228 -> 110; 1100 x 410 FP64 10.0 -> 6.1, FP32
+// 6.5 -> 4.3; 220 x 41 FP64 4.0 -> 2.9, where launches and one wavefront's
+// chain are all there is.
+#pragma once
+
+#include <type_traits>
+
+#include "hlbm_kernels.hpp"
+
+namespace hlbm {
+
+// Strips and row chunks of a pass (host: march2d_plan).
+struct March2 {
+  int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
+};
+
+// Values of the lane one to the left (cx = +1 moves them right) / right.
+// DPP wave_shr:1 / wave_shl:1; the end lanes get 0, which nobody uses.
+__device__ __forceinline__ uint32_t lane_shift32(uint32_t v, int cx) {
+  return cx > 0 ? (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xf, 0xf, true)
+                : (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xf, 0xf, true);
+}
+template <typename T>
+__device__ __forceinline__ T lane_shift(T v, int cx) {
+  if (cx == 0) return v;
+  if constexpr (sizeof(T) == 8) {
+    union {
+      T t;
+      uint32_t w[2];
+    } u;
+    u.t = v;
+    u.w[0] = lane_shift32(u.w[0], cx);
+    u.w[1] = lane_shift32(u.w[1], cx);
+    return u.t;
+  } else {
+    union {
+      T t;
+      uint32_t w;
+    } u;
+    u.t = v;
+    u.w = lane_shift32(u.w, cx);
+    return u.t;
+  }
+}
+
+// Where a wavefront's lanes lie: x of the lane, the columns its neighbours
+// have (periodic wrap), and what ends of the lattice the strip touches.
+struct Strip {
+  int gx;                  // column (may lie outside the lattice)
+  int xm, x, xp;           // columns of the lane and of its neighbours, wrapped or clamped into [0, nx)
+  bool own;                // the lane's column is the strip's own
+  bool inlet, outlet;      // lane on the inlet / outlet column
+  bool ends;               // the strip holds an inlet or outlet lane (uniform)
+};
+
+template <int K>
+__device__ __forceinline__ Strip make_strip(const Geo& g, int strip) {
+  constexpr int W = 64 - 2 * (K - 1);
+  Strip s;
+  const int lane = threadIdx.x & 63;
+  s.gx = strip * W - (K - 1) + lane;
+  const bool per = g.bcx == BC_PERIODIC;
+  auto col = [&](int x) {
+    if (per) {
+      x %= g.nx;
+      return x < 0 ? x + g.nx : x;
+    }
+    return x < 0 ? 0 : (x >= g.nx ? g.nx - 1 : x);
+  };
+  s.x = col(s.gx);
+  s.xm = col(s.gx - 1);
+  s.xp = col(s.gx + 1);
+  s.own = lane >= K - 1 && lane <= 64 - K && s.gx < g.nx;
+  s.inlet = g.bcx == BC_INOUT && s.gx == 0;
+  s.outlet = g.bcx == BC_INOUT && s.gx == g.nx - 1;
+  s.ends = __ballot(s.inlet || s.outlet) != 0;
+  return s;
+}
+
+// The i-th direction with cy = CY in D2Q9 order.
+template <int CY>
+__device__ constexpr int dir9(int i) {
+  int n = 0;
+  for (int k = 0; k < 9; ++k)
+    if (Lat<9>::cy[k] == CY && n++ == i) return k;
+  return -1;
+}
+
+// What a level boundary holds between rows: the values moving up (cy = +1)
+// from the last two rows (up[r & 1] of row r) and those staying on the last row.
+template <typename T>
+struct Wait {
+  T up[2][3], mid[3];
+};
+
+// Hands the post-collision values c of a row to the next level: fills in what
+// the row before it was still waiting for (s: all nine of that row) and keeps
+// the rest.  ph: parity of the row within the loop.  EDGE 1, 2: o holds what the
+// outlet lane gets from the virtual column (cx = -1 directions, in order);
+// EDGE 2, beside a wall (at_wall: -1 the row is the first, +1 the last, +2 the one beyond
+// the last) the values that would cross it bounce back on their row: those
+// going down from the first row are its upward arrivals, those going up from
+// the last row wait in the place of its upward values for the row beyond.
+template <int EDGE, typename T>
+__device__ __forceinline__ void hand_on(const int ph, const Strip& st, const int at_wall, const T (&c)[9],
+                                        const T (&o)[3], Wait<T>& w, T (&s)[9]) {
+  using L = Lat<9>;
+  T sh[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) sh[k] = lane_shift(c[k], L::cx[k]);
+  if (EDGE) {
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+      if (L::cx[k] == -1) sh[k] = st.outlet ? o[n++] : sh[k];
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    s[dir9<1>(i)] = w.up[ph][i];  // from two rows before
+    s[dir9<0>(i)] = w.mid[i];
+    s[dir9<-1>(i)] = sh[dir9<-1>(i)];
+    w.up[ph][i] = sh[dir9<1>(i)];
+    w.mid[i] = sh[dir9<0>(i)];
+  }
+  if (EDGE == 2 && __builtin_expect(at_wall != 0, 0)) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      if (at_wall == -1) w.up[ph ^ 1][i] = c[L::opp[dir9<1>(i)]];
+      if (at_wall == 1) w.up[ph][i] = c[dir9<1>(i)];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (dir9<1>(j) == L::opp[dir9<-1>(i)] && at_wall == 2) s[dir9<-1>(i)] = w.up[ph ^ 1][j];
+    }
+  }
+}
+
+__device__ __forceinline__ int wrap_row(int y, int ny) {
+  y %= ny;
+  return y < 0 ? y + ny : y;
+}
+
+__device__ __forceinline__ uint64_t uni64(uint64_t v) { return (uint64_t)wave_uniform64((int64_t)v); }
+
+// The row a wavefront loads: scalar base address of plane 0 (stepped plane to
+// plane at the accesses), wrapped on a periodic y axis.
+struct RowPtr {
+  uint64_t base, row_bytes, lat_bytes;
+  int y, ny;
+  __device__ __forceinline__ RowPtr(const void* A, int row, int nx, int ny_, int size) {
+    ny = ny_;
+    y = row;
+    while (y < 0) y += ny;
+    while (y >= ny) y -= ny;
+    row_bytes = (uint64_t)nx * (uint64_t)size;
+    lat_bytes = row_bytes * (uint64_t)ny;
+    base = uni64((uint64_t)A + row_bytes * (uint64_t)y);
+  }
+  __device__ __forceinline__ void next() {
+    base += row_bytes;
+    if (++y == ny) {
+      y = 0;
+      base -= lat_bytes;
+    }
+  }
+};
+template <typename S>
+__device__ __forceinline__ typename Glob<S>::type* lane_ptr(uint64_t base, uint32_t off) {
+  typedef typename Glob<char>::type gchar;
+  return (typename Glob<S>::type*)((gchar*)base + off);
+}
+
+// Stores the last level's post-collision values c of row y to the slots they
+// move to (B).  o: the virtual column's values on the outlet lane.  Rows away
+// from walls and periodic seams share one scalar base per plane (below: row
+// y - 1 of plane 0); v: byte offsets of the three neighbour columns.
+template <int EDGE, typename S, typename T>
+__device__ __forceinline__ void push_row(const Geo& g, const Strip& st, bool walls, const int y,
+                                         uint64_t below, const uint32_t (&v)[3], uint64_t pstep, uint32_t rowb,
+                                         const T (&c)[9], const T (&o)[3]) {
+  using L = Lat<9>;
+  if (!st.own) return;
+  if (y > 0 && y < g.ny - 1) {
+    uint64_t pb = below;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      // what leaves through the inlet or outlet end is dropped
+      if (!EDGE || L::cx[k] == 0 || (L::cx[k] > 0 ? !st.outlet : !st.inlet))
+        *lane_ptr<S>(pb, v[L::cx[k] + 1] + (uint32_t)(L::cy[k] + 1) * rowb) = to_store<S>(c[k]);
+      pb += pstep;
+      asm("" : "+s"(pb));
+    }
+    if (EDGE && st.outlet) {
+      uint64_t po = below;
+      int n = 0;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        if (L::cx[k] == -1) *lane_ptr<S>(po, v[1] + (uint32_t)(L::cy[k] + 1) * rowb) = to_store<S>(o[n++]);
+        po += pstep;
+        asm("" : "+s"(po));
+      }
+    }
+    return;
+  }
+  // a row beside a wall or a periodic seam: the row offsets from `below`
+  const int64_t up = (int64_t)rowb * (y < g.ny - 1 ? 2 : 2 - (int64_t)g.ny), down = (int64_t)rowb * (y > 0 ? 0 : g.ny);
+  uint64_t pb = below;
+  int n = 0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const bool bounce = walls && ((L::cy[k] < 0 && y == 0) || (L::cy[k] > 0 && y == g.ny - 1));  // uniform
+    if (bounce) {  // to the opposite slot of the own cell
+      *lane_ptr<S>(pb + rowb + (L::opp[k] > k ? pstep * 4 : -(pstep * 4)), v[1]) = to_store<S>(c[k]);
+    } else {
+      const uint64_t pr = pb + (uint64_t)(L::cy[k] < 0 ? down : (L::cy[k] > 0 ? up : (int64_t)rowb));
+      if (!EDGE || L::cx[k] == 0 || (L::cx[k] > 0 ? !st.outlet : !st.inlet))
+        *lane_ptr<S>(pr, v[L::cx[k] + 1]) = to_store<S>(c[k]);
+      if (EDGE && L::cx[k] == -1 && st.outlet) *lane_ptr<S>(pr, v[1]) = to_store<S>(o[n]);
+    }
+    if (L::cx[k] == -1) ++n;
+    pb += pstep;
+    asm("" : "+s"(pb));
+  }
+}
+
+// Value of lane i (uniform) of v.
+template <typename T>
+__device__ __forceinline__ T lane_value(T v, int i) {
+  if constexpr (sizeof(T) == 8) {
+    union {
+      T t;
+      int w[2];
+    } u;
+    u.t = v;
+    u.w[0] = __builtin_amdgcn_readlane(u.w[0], i);
+    u.w[1] = __builtin_amdgcn_readlane(u.w[1], i);
+    return u.t;
+  } else {
+    union {
+      T t;
+      int w;
+    } u;
+    u.t = v;
+    u.w = __builtin_amdgcn_readlane(u.w, i);
+    return u.t;
+  }
+}
+
+// Velocity probe of a pass: step t of it records into out[t].
+struct Probe {
+  double* out[4];  // null: none
+  int x, y;
+};
+
+// Scalars of the collision (no body force: such lattices take single steps).
+struct MarchColl {
+  double tau0, omega0, kS;
+  __device__ __forceinline__ Coll coll() const {
+    Coll c;
+    c.tau0 = tau0;
+    c.omega0 = omega0;
+    c.kS = kS;
+    c.force[0] = c.force[1] = c.force[2] = 0.0;
+    return c;
+  }
+};
+
+// One wavefront's march over rows [y0, y1) of its strip.  Every level runs in
+// every iteration (no branches): rows outside what a level needs are
+// computed from whatever is there and reach no row that is stored.
+// EDGE: 0 none, 1 the strip holds an inlet or outlet column, 2 the rows come
+// near a wall or the probe (with or without an end).
+template <typename S, int K, bool HRR, bool SMAG, int EDGE>
+__device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip& st, const int y0, const int y1,
+                                        const S* __restrict__ A, S* __restrict__ B,
+                                        const typename Prec<S>::Dd* __restrict__ dpor, const Probe& pr) {
+  using L = Lat<9>;
+  using T = typename Prec<S>::T;
+  using Dd = typename Prec<S>::Dd;
+  constexpr int NB = K > 1 ? K - 1 : 1;
+  const bool walls = g.bcy != BC_PERIODIC;
+  const int none = -0x40000000;
+  const int row_first = walls ? 0 : none, row_last = walls ? g.ny - 1 : none;
+  // recorded by the chunk that owns the cell
+  const bool probe_lane =
+      EDGE == 2 && pr.out[0] != nullptr && pr.y >= y0 && pr.y < y1 && st.own && !st.inlet && st.gx == pr.x;
+
+  const int r0 = y0 - (K - 1), r_end = y1 + K - 2;
+  const uint64_t pstep = uni64((uint64_t)g.plane * sizeof(S));
+  RowPtr pa(A, r0, g.nx, g.ny, (int)sizeof(S)), pd(dpor, r0, g.nx, g.ny, (int)sizeof(Dd));
+  const uint32_t off = lane_offset((uint32_t)st.x * (uint32_t)sizeof(S));
+  const uint32_t offd = lane_offset((uint32_t)st.x * (uint32_t)sizeof(Dd));
+  const uint32_t offb[3] = {lane_offset((uint32_t)st.xm * (uint32_t)sizeof(S)), off,
+                            lane_offset((uint32_t)st.xp * (uint32_t)sizeof(S))};
+  const uint32_t rowb = (uint32_t)g.nx * (uint32_t)sizeof(S);
+  uint64_t below = uni64((uint64_t)B + (uint64_t)rowb * (uint64_t)(int64_t)(y0 - 1));
+  auto load = [&](T (&s)[9], T& dd) {
+    uint64_t pb = pa.base;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      s[k] = (T)*lane_ptr<const S>(pb, off);
+      pb += pstep;
+      asm("" : "+s"(pb));
+    }
+    dd = (T)*lane_ptr<const Dd>(pd.base, offd);
+    pa.next();
+    pd.next();
+  };
+  // What the pinned inlet column sends into the lattice (directions 1, 3 and
+  // 8, the latter two alike) on row r0 + lane; the rest of that column is
+  // used by no other.  A chunk's rows and halo fit the 64 lanes.
+  T in1 = (T)0, in3 = (T)0;
+  if (EDGE && st.ends) {
+    const int row = wrap_row(r0 + (int)(threadIdx.x & 63), g.ny);
+    const T ui = inlet_velocity<T>(g, row);
+    in1 = (T)to_store<S>(inlet_value<9, T>(1, ui));
+    in3 = (T)to_store<S>(inlet_value<9, T>(3, ui));
+  }
+  Wait<T> w[NB];
+  T cur[9], dcur, d[K];
+  auto step = [&](const int r, auto phase) {
+    constexpr int PH = decltype(phase)::value;
+    T s[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s[k] = cur[k];
+#pragma unroll
+    for (int t = K - 1; t > 0; --t) d[t] = d[t - 1];
+    d[0] = dcur;
+#pragma unroll
+    for (int t = 0; t < K; ++t) {
+      const int row = r - t;
+      if (t == 1) {  // level 0 has used the row: load the next one (past the last: in bounds, unused)
+        __builtin_amdgcn_sched_barrier(0);
+        load(cur, dcur);
+      }
+      if (EDGE == 2 || t == 1) __builtin_amdgcn_sched_barrier(0);  // EDGE 2: levels kept apart (registers)
+      if (t == K - 1 && row < y0) return;
+      T drho, jx, jy, jz, omega, taue, p2[6], o[3], ns[9];
+      cell_moments<9, T>(s, drho, jx, jy, jz);
+      const T rho = (T)1 + drho;
+      const T ir = recip(rho);
+      if (EDGE == 2 && probe_lane && row == pr.y) *pr.out[t] = (double)(jy * ir);
+      relaxation<9, T, HRR>(c, SMAG, s, drho, jx, jy, jz, ir, omega, taue, p2);
+      collide_cell<9, T, HRR>(c, s, drho, jx, jy, jz, rho, ir, d[t], omega, p2);
+      if (EDGE) {
+        const T ux = jx * ir, uy = jy * ir, uz = jz * ir;
+        const T uu = ux * ux + uy * uy + uz * uz;
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+          if (L::cx[k] == -1) o[n++] = (T)to_store<S>(outlet_value<9, T>(k, ux, uy, uz, uu));
+        const T a = lane_value(in1, row - r0), b = lane_value(in3, row - r0);
+        s[1] = st.inlet ? a : s[1];
+        s[3] = st.inlet ? b : s[3];
+        s[8] = st.inlet ? b : s[8];
+      }
+      if (t == K - 1) {
+        push_row<EDGE, S, T>(g, st, walls, row, below, offb, pstep, rowb, s, o);
+        below += rowb;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) s[k] = (T)to_store<S>(s[k]);
+        const int at_wall = row == row_first ? -1 : (row == row_last ? 1 : (row == row_last + 1 ? 2 : 0));
+        hand_on<EDGE, T>((PH + t) & 1, st, at_wall, s, o, w[t % NB], ns);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) s[k] = ns[k];
+      }
+    }
+  };
+
+  load(cur, dcur);
+  for (int r = r0;; r += 2) {
+    step(r, std::integral_constant<int, 0>{});
+    if (r + 1 > r_end) break;
+    step(r + 1, std::integral_constant<int, 1>{});
+    if (r + 2 > r_end) break;
+  }
+}
+
+// Wavefronts per SIMD the register allocation aims at: at 3 the FP64 passes of
+// four steps spill (1100 x 410: 11.2 us a step instead of 6.1), the others fit.
+template <typename S, int K>
+constexpr int march2d_waves() {
+  return sizeof(S) == 8 ? (K > 2 ? 2 : 3) : (K > 2 ? 4 : 6);
+}
+
+// K primal steps (rows a3, a4).  HRR, SMAG: collision model, closure.
+template <typename S, int K, bool HRR, bool SMAG>
+__global__ __launch_bounds__(256, (march2d_waves<S, K>())) void k_march2d(const Geo g, const MarchColl mc, const March2 m,
+                                                 const S* __restrict__ A, S* __restrict__ B,
+                                                 const typename Prec<S>::Dd* __restrict__ dpor, const Probe pr) {
+  const Coll c = mc.coll();
+  const int id = sweep_tile((int)blockIdx.x, (int)gridDim.x) * 4 + wave_uniform((int)(threadIdx.x >> 6));
+  if (id >= m.strips * m.chunks) return;
+  const int chunk = wave_uniform(id / m.strips);
+  const Strip st = make_strip<K>(g, id - chunk * m.strips);
+  const int y0 = chunk * m.rows, y1 = y0 + m.rows < g.ny ? y0 + m.rows : g.ny;
+  const bool at_walls = g.bcy != BC_PERIODIC && (y0 < K || y1 > g.ny - K);
+  const bool probed = pr.out[0] != nullptr && pr.y >= y0 && pr.y < y1 && __ballot(st.own && st.gx == pr.x) != 0;
+  if (at_walls || probed)
+    march2d<S, K, HRR, SMAG, 2>(g, c, st, y0, y1, A, B, dpor, pr);
+  else if (st.ends)
+    march2d<S, K, HRR, SMAG, 1>(g, c, st, y0, y1, A, B, dpor, pr);
+  else
+    march2d<S, K, HRR, SMAG, 0>(g, c, st, y0, y1, A, B, dpor, pr);
+}
+
+}  // namespace hlbm

@@ -1,0 +1,47 @@
+"""Multi-step passes (several steps in one pass over memory) against the same
+number of single steps: bitwise the same populations and probe record.  Sizes
+at the edges of the strips (64 - 2 (K - 1) columns: 62 and 58) and row chunks,
+channels narrower than one strip, every kind of end and wall the passes take,
+step counts with every remainder, runs that start on an odd step."""
+import numpy as np
+import pytest
+
+from tests.pairs import say
+
+pytestmark = pytest.mark.gpu
+
+
+def lattice(H, stencil, size, prec, bc, coll, cs, seed=1, **kw):
+    nx, ny, nz = size
+    G = H.Lattice(stencil=stencil, precision=prec, nx=nx, ny=ny, nz=nz, tau=0.56, cs=cs, bc_x=bc[0], bc_y=bc[1],
+                  bc_z=bc[2], inlet_profile=H.INLET_PARABOLIC, u_in=0.04, collision=coll, **kw)
+    rng = np.random.default_rng(seed)
+    G.set_porosity(rng.uniform(0.0, 1.0, G.n))
+    u = 0.02 * rng.uniform(-1.0, 1.0, (3, G.n))
+    if stencil == H.D2Q9:
+        u[2] = 0.0
+    G.init_equilibrium(1.0, u)
+    return G
+
+
+SIZES_2D = [(3, 2), (58, 8), (59, 9), (62, 13), (63, 5), (117, 16), (130, 3), (233, 41)]
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("bc", [(2, 1, 0), (2, 0, 0), (0, 0, 0), (0, 1, 0), (1, 1, 0)])
+def test_primal_passes_equal_single_steps_2d(prec, bc):
+    from paper_2606_31707_amd import hlbm as H
+    for i, (nx, ny) in enumerate(SIZES_2D):
+        coll, cs = ((0, 0.0), (0, 0.1), (1, 0.0), (1, 0.1))[i % 4]
+        say("primal passes", prec, bc, nx, ny, coll, cs)
+        a, b = (lattice(H, H.D2Q9, (nx, ny, 1), prec, bc, coll, cs) for _ in range(2))
+        for L in (a, b):
+            L.set_probe(min(nx - 1, nx // 2 + 1), ny // 2)
+        for steps in (4, 7, 9, 2, 14):
+            a.run_primal(steps)
+            for _ in range(steps):
+                b.run_primal(1)
+            assert np.array_equal(a.populations(), b.populations()), (nx, ny, steps)
+            assert np.array_equal(a.probe(), b.probe()), (nx, ny, steps)
+        a.close()
+        b.close()
