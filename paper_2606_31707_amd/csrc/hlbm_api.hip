@@ -65,10 +65,11 @@ void lat_free(hlbm_lattice_s* L, void* p) {
 // The second arrays of the multi-step passes hold nothing between calls: they
 // are given back when a buffer that is needed does not fit beside them.
 bool give_back_second_arrays(hlbm_lattice_s* L) {
-  if (!L->f2) return false;
+  if (!L->f2 && !L->phi2) return false;
   (void)hipStreamSynchronize(L->stream);
   lat_free(L, L->f2);
-  L->f2 = nullptr;
+  lat_free(L, L->phi2);
+  L->f2 = L->phi2 = nullptr;
   return true;
 }
 hlbm_status lat_alloc(hlbm_lattice_s* L, void** p, size_t bytes) {
@@ -406,7 +407,7 @@ hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out) {
   };
   if ((s = lat_alloc(L, &L->f, L->ssize * L->q * L->plane)) != HLBM_OK) return bail(s);
   if ((s = lat_alloc(L, &L->dpor, L->dsize * L->plane)) != HLBM_OK) return bail(s);
-  if (primal_passes(L)) lat_alloc_second(L, &L->f2, L->ssize * L->q * L->plane);
+  if (primal_passes_of(&L->desc)) lat_alloc_second(L, &L->f2, L->ssize * L->q * L->plane);
   if ((s = lat_alloc(L, &L->ghost, L->ssize * L->q * L->gplane)) != HLBM_OK) return bail(s);
   if ((s = ensure_partials(L, 2 * n_blocks(L) + 8)) != HLBM_OK) return bail(s);
   if (hipHostMalloc((void**)&L->red_host, 4 * sizeof(double)) != hipSuccess)
@@ -431,7 +432,7 @@ void hlbm_destroy(hlbm_lattice L) {
   if (!L) return;
   (void)hipStreamSynchronize(L->stream);
   void* bufs[] = {L->f,   L->f2,    L->dpor,  L->ghost, L->acc_rho, L->acc_j, L->acc_f, L->acc_tau, L->acc_obj, L->acc_pend,
-                  L->phi, L->prep,  L->src,   L->gdat,    L->oprep, L->pv[0], L->pv[1],   L->snap,
+                  L->phi, L->phi2, L->prep,  L->src,   L->gdat,    L->oprep, L->pv[0], L->pv[1],   L->snap,
                   L->red, L->usnap, L->probe_buf, L->mea_flag, L->mea_src, L->rcopy, L->tan_f, L->tan_ghost,
                   L->tan_v, L->tan_rec};
   for (void* p : bufs) dev_free(p);
@@ -905,6 +906,9 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
     L->adj_diff = turb_diff ? 1 : 0;
     L->adj_omega = 1.0 / tau_adj;
   }
+  const bool passes = adjoint_passes_of(&L->desc, L->obj_kind);
+  if (passes) lat_alloc_second(L, &L->phi2, as * L->q * plane);
+  const bool multi = L->phi2 != nullptr && passes && !turb_diff && !stream_capturing(L->stream);
   int64_t iters = o->max_iters + (o->max_iters & 1);
   int64_t M = o->check_every > 0 ? o->check_every : 100;
   M += (M & 1);
@@ -920,11 +924,13 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
   while (done < iters) {
     int64_t chunk = iters - done;
     if (o->tol > 0.0 && chunk > M) chunk = M;
-    for (int64_t k = 0; k < chunk; ++k) {
-      s = timed_launch(L, 2, chunk - k, 1, [&]() { return launch_adjoint_step(L); });
+    for (int64_t k = 0; k < chunk;) {
+      const int K = multi && (L->adj_iters & 1) == 0 ? adjoint_pass_steps(L, chunk - k) : 1;
+      s = timed_launch(L, 2, chunk - k, K, [&]() { return K > 1 ? launch_adjoint_pass(L, K) : launch_adjoint_step(L); });
       if (s != HLBM_OK) return s;
-      L->pvcur ^= 1;
-      L->adj_iters += 1;
+      L->pvcur ^= 1;  // a pass reads and writes the outlet buffers once
+      L->adj_iters += K;
+      k += K;
     }
     done += chunk;
     if (o->tol > 0.0) {

@@ -52,6 +52,24 @@ inline int nsym_of(int stencil) { return stencil == HLBM_D2Q9 ? 3 : 6; }
 inline int ncoef_of(int stencil) { return 3 + dim_of(stencil) + nsym_of(stencil); }
 inline int nb_of(int stencil) { return 1 + dim_of(stencil) + nsym_of(stencil); }
 
+// Whether lattices of a descriptor take multi-step passes, and so hold a second
+// population array (primal) and a second phi array (adjoint).  Single steps
+// remain for a body force (tests), walls on the x axis (a value that bounces
+// there stays on its row, which a strip does not provide for), one-row
+// channels (their row is beside both walls), and rows whose byte offsets
+// exceed 32 bits; for the adjoint also the HRR collision (its frozen data would
+// have to wait for the later levels as well) and J_MEA.
+inline bool primal_passes_of(const hlbm_desc* d) {
+  return d->stencil == HLBM_D2Q9 && d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
+         (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->force[0] == 0.0 && d->force[1] == 0.0 &&
+         d->force[2] == 0.0;
+}
+inline bool adjoint_passes_of(const hlbm_desc* d, int objective) {
+  return d->stencil == HLBM_D2Q9 && d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
+         (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->collision == HLBM_COLL_BGK &&
+         objective != HLBM_OBJ_MEA;
+}
+
 // What is wrong with a descriptor, or nullptr if it is valid.
 inline const char* desc_problem(const hlbm_desc* d) {
   if (!d) return "null descriptor";
@@ -95,7 +113,7 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
                           (uint64_t)desc->nz;
   // populations, porosity, outlet values, reduction partials, steady-check snapshot
   uint64_t b = P * (q * ss + ds) + G * q * ss + 8 * (2 * blocks + 8) + 8 * P * dim;
-  if (desc->stencil == HLBM_D2Q9) b += P * q * ss;  // second population array (multi-step passes)
+  if (primal_passes_of(desc)) b += P * q * ss;  // second population array (multi-step passes)
   if (region_cells > 0) {  // objective terms and adjoint source over the region
     const uint64_t rp = (uint64_t)round_up(region_cells, 128);
     b += 2 * 8 * rp * ncoef;
@@ -117,6 +135,7 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
     b += P * 8 * (dim + 2);                             // gradient data
     b += G * (8 * (1 + dim) + 2 * as * q);              // outlet data, outlet adjoint values
     b += P * as * q;                                    // residual snapshot
+    if (adjoint_passes_of(desc, objective)) b += P * as * q;  // second phi array (multi-iteration passes)
   }
   *bytes = b;
   return nullptr;

@@ -56,6 +56,7 @@ struct hlbm_lattice_s {
   int mea_dirty = 1;                  // flags to rebuild (porosity or region changed)
 
   // adjoint
+  void* phi2 = nullptr;   // second phi array (multi-iteration passes)
   void* phi = nullptr;    // q * plane (double for FP64, float otherwise)
   void* prep = nullptr;   // per-cell frozen coefficients (adjoint type)
   int nprep = 0;          // planes in prep
@@ -178,10 +179,9 @@ hipError_t launch_mea_flags(hlbm_lattice_s* L);
 hipError_t launch_tangent_step(hlbm_lattice_s* L);
 hipError_t launch_tangent_objective(hlbm_lattice_s* L, double* partials, int* nblocks);
 hipError_t launch_primal_step(hlbm_lattice_s* L, int accumulate);
-// Multi-step passes (L->f2 present, parity 0): whether the lattice has them,
-// how many of `left` steps the next launch takes (1: a single step), and a
-// pass of K steps, which reads L->f, writes L->f2 and swaps the two.
-bool primal_passes(const hlbm_lattice_s* L);
+// Multi-step passes (L->f2 present, parity 0): how many of `left` steps the
+// next launch takes (1: a single step), and a pass of K steps, which reads
+// L->f, writes L->f2 and swaps the two.
 int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left);
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K);
 hipError_t launch_gather(hlbm_lattice_s* L, double* out_dev);
@@ -194,6 +194,10 @@ hipError_t launch_finalize_sum(hlbm_lattice_s* L, const double* partials, int n,
 hipError_t launch_finalize_max2(hlbm_lattice_s* L, const double* partials, int n, double* out);
 hipError_t launch_adjoint_prep(hlbm_lattice_s* L, int source, double tau_adj, int turb);
 hipError_t launch_adjoint_step(hlbm_lattice_s* L);
+// The same for the adjoint (L->phi2 present, an even count so far, closure
+// frozen).
+int adjoint_pass_steps(const hlbm_lattice_s* L, int64_t left);
+hipError_t launch_adjoint_pass(hlbm_lattice_s* L, int K);
 hipError_t launch_adjoint_residual(hlbm_lattice_s* L, int first, double* partials, int* nblocks);
 hipError_t launch_gradient(hlbm_lattice_s* L, double* g_dev);
 hipError_t launch_adjoint_gather(hlbm_lattice_s* L, double* out_dev);

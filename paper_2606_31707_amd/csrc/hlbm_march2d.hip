@@ -7,7 +7,6 @@
 
 namespace hlbm {
 
-namespace {
 // Rows per chunk: the number of iterations (rows plus the halo of the levels)
 // times what an iteration costs with m workgroups on a compute unit.  Measured
 // on 1100 x 410: a second wavefront on a SIMD adds 45 % to an iteration in
@@ -16,11 +15,10 @@ namespace {
 // caches, where neighbouring chunks share their halo rows in L2
 // (8192 x 4096 FP32: 8 rows 167 us, 16 rows 169, 58 rows 184; FP16S, whose
 // rows are half as long, 150, 117 and 110).
-March2 march2d_plan(const hlbm_lattice_s* L, int K) {
+March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64) {
   const int W = 64 - 2 * (K - 1), ny = L->desc.ny;
   March2 m;
   m.strips = (L->desc.nx + W - 1) / W;
-  const bool f64 = L->desc.precision == HLBM_FP64;
   const int most = L->desc.precision == HLBM_FP16S ? 24 : 12;
   double best = 0.0;
   for (int rows = 1; rows <= most && rows <= ny; ++rows) {
@@ -40,12 +38,13 @@ March2 march2d_plan(const hlbm_lattice_s* L, int K) {
   return m;
 }
 
+namespace {
 template <typename S, int K>
 void march2d(hlbm_lattice_s* L) {
   const Geo g = make_geo(L);
   const double cs = L->desc.smagorinsky_cs;
   const MarchColl c{L->desc.tau, 1.0 / L->desc.tau, 18.0 * sqrt(2.0) * cs * cs};
-  const March2 m = march2d_plan(L, K);
+  const March2 m = march2d_plan(L, K, sizeof(S) == 8);
   Probe pr{{nullptr, nullptr, nullptr, nullptr}, 0, 0};
   if (L->probe_buf != nullptr && L->probe_cap > 0) {
     for (int i = 0; i < K; ++i) pr.out[i] = L->probe_buf + (L->probe_n + i) % L->probe_cap;
@@ -70,14 +69,6 @@ void march2d(hlbm_lattice_s* L) {
   }
 }
 }  // namespace
-
-// Single steps remain for a body force (tests), walls on the x axis (a value
-// that bounces there stays on its row, which a strip does not provide for) and
-// one-row channels, whose row is beside both walls.
-bool primal_passes(const hlbm_lattice_s* L) {
-  const double* f = L->desc.force;
-  return L->desc.stencil == HLBM_D2Q9 && L->desc.bc_x != HLBM_BC_WALLS && L->desc.ny >= 2 && f[0] == 0.0 && f[1] == 0.0 && f[2] == 0.0 && make_geo(L).slot32;
-}
 
 // Four steps a pass; two for FP16 lattices that stay in the caches, whose
 // loads and conversions rather than bytes bound a pass (1100 x 410: 4.6 us a

@@ -38,6 +38,7 @@ namespace hlbm {
 struct March2 {
   int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
 };
+March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64);
 
 // Values of the lane one to the left (cx = +1 moves them right) / right.
 // DPP wave_shr:1 / wave_shl:1; the end lanes get 0, which nobody uses.
@@ -75,7 +76,7 @@ struct Strip {
   int xm, x, xp;           // columns of the lane and of its neighbours, wrapped or clamped into [0, nx)
   bool own;                // the lane's column is the strip's own
   bool inlet, outlet;      // lane on the inlet / outlet column
-  bool ends;               // the strip holds an inlet or outlet lane (uniform)
+  bool ends, any_outlet;   // the strip holds an inlet or outlet lane, an outlet lane (uniform)
 };
 
 template <int K>
@@ -99,6 +100,7 @@ __device__ __forceinline__ Strip make_strip(const Geo& g, int strip) {
   s.inlet = g.bcx == BC_INOUT && s.gx == 0;
   s.outlet = g.bcx == BC_INOUT && s.gx == g.nx - 1;
   s.ends = __ballot(s.inlet || s.outlet) != 0;
+  s.any_outlet = __ballot(s.outlet) != 0;
   return s;
 }
 
@@ -195,55 +197,56 @@ __device__ __forceinline__ typename Glob<S>::type* lane_ptr(uint64_t base, uint3
 }
 
 // Stores the last level's post-collision values c of row y to the slots they
-// move to (B).  o: the virtual column's values on the outlet lane.  Rows away
+// move to (B).  VIRT, o: the virtual column's values on the outlet lane.  Rows away
 // from walls and periodic seams share one scalar base per plane (below: row
 // y - 1 of plane 0); v: byte offsets of the three neighbour columns.
-template <int EDGE, typename S, typename T>
+template <int EDGE, bool VIRT, typename S, typename T>
 __device__ __forceinline__ void push_row(const Geo& g, const Strip& st, bool walls, const int y,
                                          uint64_t below, const uint32_t (&v)[3], uint64_t pstep, uint32_t rowb,
                                          const T (&c)[9], const T (&o)[3]) {
   using L = Lat<9>;
+  uint64_t base[9];  // row y - 1 of each plane (formed ahead of the masked stores)
+  base[0] = below;
+#pragma unroll
+  for (int k = 1; k < 9; ++k) {
+    base[k] = base[k - 1] + pstep;
+    asm("" : "+s"(base[k]));
+  }
   if (!st.own) return;
   if (y > 0 && y < g.ny - 1) {
-    uint64_t pb = below;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
+    for (int m = 0; m < 3; ++m) {  // directions along x: 0, then 1, then -1
+      const int cx = m == 2 ? -1 : m;
       // what leaves through the inlet or outlet end is dropped
-      if (!EDGE || L::cx[k] == 0 || (L::cx[k] > 0 ? !st.outlet : !st.inlet))
-        *lane_ptr<S>(pb, v[L::cx[k] + 1] + (uint32_t)(L::cy[k] + 1) * rowb) = to_store<S>(c[k]);
-      pb += pstep;
-      asm("" : "+s"(pb));
+      if (!EDGE || cx == 0 || (cx > 0 ? !st.outlet : !st.inlet)) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+          if (L::cx[k] == cx) *lane_ptr<S>(base[k], v[cx + 1] + (uint32_t)(L::cy[k] + 1) * rowb) = to_store<S>(c[k]);
+      }
     }
-    if (EDGE && st.outlet) {
-      uint64_t po = below;
+    if (EDGE && VIRT && st.outlet) {
       int n = 0;
 #pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        if (L::cx[k] == -1) *lane_ptr<S>(po, v[1] + (uint32_t)(L::cy[k] + 1) * rowb) = to_store<S>(o[n++]);
-        po += pstep;
-        asm("" : "+s"(po));
-      }
+      for (int k = 0; k < 9; ++k)
+        if (L::cx[k] == -1) *lane_ptr<S>(base[k], v[1] + (uint32_t)(L::cy[k] + 1) * rowb) = to_store<S>(o[n++]);
     }
     return;
   }
-  // a row beside a wall or a periodic seam: the row offsets from `below`
+  // a row beside a wall or a periodic seam: the row offsets from row y - 1
   const int64_t up = (int64_t)rowb * (y < g.ny - 1 ? 2 : 2 - (int64_t)g.ny), down = (int64_t)rowb * (y > 0 ? 0 : g.ny);
-  uint64_t pb = below;
   int n = 0;
 #pragma unroll
   for (int k = 0; k < 9; ++k) {
     const bool bounce = walls && ((L::cy[k] < 0 && y == 0) || (L::cy[k] > 0 && y == g.ny - 1));  // uniform
     if (bounce) {  // to the opposite slot of the own cell
-      *lane_ptr<S>(pb + rowb + (L::opp[k] > k ? pstep * 4 : -(pstep * 4)), v[1]) = to_store<S>(c[k]);
+      *lane_ptr<S>(base[L::opp[k]] + rowb, v[1]) = to_store<S>(c[k]);
     } else {
-      const uint64_t pr = pb + (uint64_t)(L::cy[k] < 0 ? down : (L::cy[k] > 0 ? up : (int64_t)rowb));
+      const uint64_t pr = base[k] + (uint64_t)(L::cy[k] < 0 ? down : (L::cy[k] > 0 ? up : (int64_t)rowb));
       if (!EDGE || L::cx[k] == 0 || (L::cx[k] > 0 ? !st.outlet : !st.inlet))
         *lane_ptr<S>(pr, v[L::cx[k] + 1]) = to_store<S>(c[k]);
-      if (EDGE && L::cx[k] == -1 && st.outlet) *lane_ptr<S>(pr, v[1]) = to_store<S>(o[n]);
+      if (EDGE && VIRT && L::cx[k] == -1 && st.outlet) *lane_ptr<S>(pr, v[1]) = to_store<S>(o[n]);
     }
     if (L::cx[k] == -1) ++n;
-    pb += pstep;
-    asm("" : "+s"(pb));
   }
 }
 
@@ -366,7 +369,7 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
       if (EDGE == 2 && probe_lane && row == pr.y) *pr.out[t] = (double)(jy * ir);
       relaxation<9, T, HRR>(c, SMAG, s, drho, jx, jy, jz, ir, omega, taue, p2);
       collide_cell<9, T, HRR>(c, s, drho, jx, jy, jz, rho, ir, d[t], omega, p2);
-      if (EDGE) {
+      if (EDGE == 1 || (EDGE == 2 && st.ends)) {
         const T ux = jx * ir, uy = jy * ir, uz = jz * ir;
         const T uu = ux * ux + uy * uy + uz * uz;
         int n = 0;
@@ -379,7 +382,7 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
         s[8] = st.inlet ? b : s[8];
       }
       if (t == K - 1) {
-        push_row<EDGE, S, T>(g, st, walls, row, below, offb, pstep, rowb, s, o);
+        push_row<EDGE, true, S, T>(g, st, walls, row, below, offb, pstep, rowb, s, o);
         below += rowb;
       } else {
 #pragma unroll
@@ -427,6 +430,230 @@ __global__ __launch_bounds__(256, (march2d_waves<S, K>())) void k_march2d(const 
     march2d<S, K, HRR, SMAG, 1>(g, c, st, y0, y1, A, B, dpor, pr);
   else
     march2d<S, K, HRR, SMAG, 0>(g, c, st, y0, y1, A, B, dpor, pr);
+}
+
+// =========================================================================
+// adjoint: K iterations (row a8) of the BGK adjoint with a frozen relaxation
+// time, moment-form objectives.  phihat streams like the primal populations;
+// the frozen data of a row waits for the later levels beside it.  Nothing
+// arrives at the outlet from beyond; what leaves through it arrives on the
+// lane beyond the outlet and enters the next level's virtual-column term from
+// there (level 0 and the last level: the pv buffers).
+// =========================================================================
+
+struct MarchAdj {
+  int les;  // per-cell omega
+  double omega0;
+};
+
+template <typename T, int K, bool SRC, int EDGE>
+__device__ __forceinline__ void march2d_adjoint(const Geo& g, const ObjBox& ob, const MarchAdj& ac, const Strip& st,
+                                                const int y0, const int y1, const T* __restrict__ A,
+                                                T* __restrict__ B, const T* __restrict__ prep,
+                                                const double* __restrict__ src, const double* __restrict__ oprep,
+                                                const T* __restrict__ pv_in, T* __restrict__ pv_out) {
+  using L = Lat<9>;
+  constexpr int NB = K > 1 ? K - 1 : 1;
+  const bool walls = g.bcy != BC_PERIODIC;
+  const int none = -0x40000000;
+  const int row_first = walls ? 0 : none, row_last = walls ? g.ny - 1 : none;
+  const int r0 = y0 - (K - 1), r_end = y1 + K - 2;
+  const uint64_t pstep = uni64((uint64_t)g.plane * sizeof(T));
+  RowPtr pa(A, r0, g.nx, g.ny, (int)sizeof(T)), pp(prep, r0, g.nx, g.ny, (int)sizeof(T));
+  const uint32_t off = lane_offset((uint32_t)st.x * (uint32_t)sizeof(T));
+  const uint32_t offb[3] = {lane_offset((uint32_t)st.xm * (uint32_t)sizeof(T)), off,
+                            lane_offset((uint32_t)st.xp * (uint32_t)sizeof(T))};
+  const uint32_t rowb = (uint32_t)g.nx * (uint32_t)sizeof(T);
+  uint64_t below = uni64((uint64_t)B + (uint64_t)rowb * (uint64_t)(int64_t)(y0 - 1));
+  struct Frozen {
+    T tx, ty, d, om;
+  };
+  const bool reg_lane = SRC && st.x >= ob.lo[0] && st.x < ob.lo[0] + ob.rn[0];
+  const uint32_t reg_x = lane_offset(8 * (uint32_t)(st.x - ob.lo[0]));
+  // The source waits in registers beside the frozen data where these suffice;
+  // the FP64 passes of four steps read it again at each level (from L2).
+  constexpr bool QREG = SRC && (K == 2 || sizeof(T) == 4);
+  double qcur[6];  // of the row loaded last
+  T q[QREG ? K : 1][6];
+  // the objective's source on row y, zero outside its region
+  auto load_source = [&](int y, double (&a)[6]) {
+    uint64_t base[6];  // formed ahead of the masked loads
+    base[0] = uni64((uint64_t)src + 8 * (uint64_t)(Coef<9>::A0 * ob.rplane + (int64_t)ob.rn[0] * (y - ob.lo[1])));
+#pragma unroll
+    for (int m = 1; m < 6; ++m) {
+      base[m] = base[m - 1] + 8 * (uint64_t)ob.rplane;
+      asm("" : "+s"(base[m]));
+    }
+#pragma unroll
+    for (int m = 0; m < 6; ++m) a[m] = 0.0;
+    if (reg_lane && y >= ob.lo[1] && y < ob.lo[1] + ob.rn[1]) {
+#pragma unroll
+      for (int m = 0; m < 6; ++m) a[m] = *lane_ptr<const double>(base[m], reg_x);
+    }
+  };
+  auto load = [&](T (&s)[9], Frozen& f) {
+    uint64_t pb = pa.base;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      s[k] = *lane_ptr<const T>(pb, off);
+      pb += pstep;
+      asm("" : "+s"(pb));
+    }
+    f.tx = *lane_ptr<const T>(pp.base, off);
+    f.ty = *lane_ptr<const T>(pp.base + pstep, off);
+    f.d = *lane_ptr<const T>(pp.base + 2 * pstep, off);
+    f.om = *lane_ptr<const T>(pp.base + (ac.les ? 3 : 2) * pstep, off);
+    if (QREG) load_source(pa.y, qcur);
+    pa.next();
+    pp.next();
+  };
+  // outlet rows r0 + lane: 1/rho, u, and the adjoint on the virtual column
+  T iro = (T)0, uox = (T)0, uoy = (T)0, pv0[3] = {(T)0, (T)0, (T)0};
+  if (EDGE && st.any_outlet) {
+    const int row = wrap_row(r0 + (int)(threadIdx.x & 63), g.ny);
+    iro = (T)1 / (T)oprep[row];
+    uox = (T)oprep[g.gplane + row];
+    uoy = (T)oprep[2 * g.gplane + row];
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+      if (L::cx[k] == -1) pv0[n++] = pv_in[k * g.gplane + row];
+  }
+  Wait<T> w[NB];
+  T cur[9];
+  Frozen fcur, f[K];
+  auto step = [&](const int r, auto phase) {
+    constexpr int PH = decltype(phase)::value;
+    T s[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s[k] = cur[k];
+#pragma unroll
+    for (int t = K - 1; t > 0; --t) f[t] = f[t - 1];
+    f[0] = fcur;
+    if (QREG) {
+#pragma unroll
+      for (int t = K - 1; t > 0; --t)
+#pragma unroll
+        for (int m = 0; m < 6; ++m) q[QREG ? t : 0][m] = q[QREG ? t - 1 : 0][m];
+#pragma unroll
+      for (int m = 0; m < 6; ++m) q[0][m] = (T)qcur[m];
+    }
+#pragma unroll
+    for (int t = 0; t < K; ++t) {
+      const int row = r - t;
+      if (t == 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        load(cur, fcur);
+      }
+      if (EDGE == 2 || t == 1) __builtin_amdgcn_sched_barrier(0);
+      if (t == K - 1 && row < y0) return;
+      const int y = row < 0 || row >= g.ny ? wave_uniform(wrap_row(row, g.ny)) : row;
+      if (SRC && !QREG) load_source(y, qcur);
+      T pv[9];
+      if (EDGE && st.any_outlet) {
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          if (L::cx[k] != -1) continue;
+          if (t == 0) {
+            pv[k] = lane_value(pv0[n], row - r0);
+            // beyond the outlet: no adjoint inflow (a wall's bounce-back stays)
+            const bool kept = walls && ((L::cy[k] > 0 && y == 0) || (L::cy[k] < 0 && y == g.ny - 1));
+            s[k] = st.outlet && !kept ? (T)0 : s[k];
+          } else {
+            pv[k] = lane_shift(s[L::opp[k]], -1);
+            const bool beyond = walls && ((L::cy[k] < 0 && y == 0) || (L::cy[k] > 0 && y == g.ny - 1));
+            pv[k] = beyond ? (T)0 : pv[k];
+          }
+          ++n;
+        }
+      }
+      T lam[9], c[9];
+      adjoint_bgk<9, T>(s, f[t].tx, f[t].ty, (T)0, f[t].d, ac.les ? f[t].om : (T)ac.omega0, lam);
+      if (EDGE && st.any_outlet) {
+        T lo[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) lo[k] = lam[k];
+        const int i = row - r0;
+        adjoint_outlet<9, T>(pv, lane_value(iro, i), lane_value(uox, i), lane_value(uoy, i), (T)0, lo);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) lam[k] = st.outlet ? lo[k] : lam[k];
+      }
+      if (SRC) {  // zero outside the objective's region
+#pragma unroll
+        for (int m = 0; m < 6; ++m)
+          if (!QREG) q[0][m] = (T)qcur[m];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lam[i] -= quad_eval<9, T>(q[QREG ? t : 0], i);
+      }
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        c[k] = lam[L::opp[k]];
+        if (EDGE && L::cx[k] == 1) c[k] = st.inlet ? (T)0 : c[k];  // lambda = 0 at the pinned inlet
+      }
+      const T o[3] = {(T)0, (T)0, (T)0};
+      if (t == K - 1) {
+        push_row<EDGE, false, T, T>(g, st, walls, row, below, offb, pstep, rowb, c, o);
+        below += rowb;
+        if (EDGE && st.any_outlet) {
+          const bool put = st.own && st.outlet;
+#pragma unroll
+          for (int k = 0; k < 9; ++k) {
+            if (L::cx[k] != -1) continue;
+            int vy = y - L::cy[k];
+            const bool cell = !walls || (vy >= 0 && vy < g.ny);
+            vy = vy < 0 ? vy + g.ny : (vy >= g.ny ? vy - g.ny : vy);
+            if (put && cell) pv_out[k * g.gplane + vy] = lam[k];
+          }
+        }
+      } else {
+        const int at_wall = row == row_first ? -1 : (row == row_last ? 1 : (row == row_last + 1 ? 2 : 0));
+        hand_on<EDGE, T>((PH + t) & 1, st, at_wall, c, o, w[t % NB], s);
+      }
+    }
+  };
+
+  load(cur, fcur);
+  for (int r = r0;; r += 2) {
+    step(r, std::integral_constant<int, 0>{});
+    if (r + 1 > r_end) break;
+    step(r + 1, std::integral_constant<int, 1>{});
+    if (r + 2 > r_end) break;
+  }
+}
+
+// Per iteration, single sweep -> pass: 8192 x 4096, drag plane, FP64 982 -> 329
+// us, FP32 480 -> 174; dissipation box over 6/11 of it (48 bytes of FP64
+// source a cell beside the 52 or 104 of phi and the frozen data) 1169 -> 449 and
+// 653 -> 250; 1100 x 410 FP32 7.4 -> 6.6 and 7.6 -> 6.8, 220 x 41 FP64
+// 4.1 -> 3.7.  On the small ones the strips that hold the outlet column set the
+// time: its virtual-column term doubles the instructions of a level.
+// With a third wavefront per SIMD the passes of four spill (FP32 1100 x 410
+// 6.6 -> 8.1 us).
+template <typename T, int K>
+__global__ __launch_bounds__(256, (sizeof(T) == 8 || K > 2 ? 2 : 4)) void k_march2d_adjoint(
+    const Geo g, const ObjBox ob, const MarchAdj ac, const March2 m, const T* __restrict__ A, T* __restrict__ B,
+    const T* __restrict__ prep, const double* __restrict__ src, const double* __restrict__ oprep,
+    const T* __restrict__ pv_in, T* __restrict__ pv_out) {
+  const int id = sweep_tile((int)blockIdx.x, (int)gridDim.x) * 4 + wave_uniform((int)(threadIdx.x >> 6));
+  if (id >= m.strips * m.chunks) return;
+  const int chunk = wave_uniform(id / m.strips);
+  const Strip st = make_strip<K>(g, id - chunk * m.strips);
+  const int y0 = chunk * m.rows, y1 = y0 + m.rows < g.ny ? y0 + m.rows : g.ny;
+  const bool walls = g.bcy != BC_PERIODIC;
+  const bool at_walls = walls && (y0 < K || y1 > g.ny - K);
+  // whether any row of the march (halo included) can hold region cells
+  const bool rows = !walls || (y1 + K - 2 >= ob.lo[1] && y0 - (K - 1) < ob.lo[1] + ob.rn[1]);
+  const bool src_here =
+      ob.active && rows && __ballot(st.x >= ob.lo[0] && st.x < ob.lo[0] + ob.rn[0]) != 0;
+  if (at_walls)
+    march2d_adjoint<T, K, true, 2>(g, ob, ac, st, y0, y1, A, B, prep, src, oprep, pv_in, pv_out);
+  else if (st.ends)
+    march2d_adjoint<T, K, true, 1>(g, ob, ac, st, y0, y1, A, B, prep, src, oprep, pv_in, pv_out);
+  else if (src_here)
+    march2d_adjoint<T, K, true, 0>(g, ob, ac, st, y0, y1, A, B, prep, src, oprep, pv_in, pv_out);
+  else
+    march2d_adjoint<T, K, false, 0>(g, ob, ac, st, y0, y1, A, B, prep, src, oprep, pv_in, pv_out);
 }
 
 }  // namespace hlbm

@@ -1,0 +1,48 @@
+// hlbm_march2d_adjoint.hip -- launcher of the D2Q9 multi-iteration adjoint
+// passes.
+#include <cmath>
+#include <cstdlib>
+#include <utility>
+
+#include "hlbm_march2d.hpp"
+
+namespace hlbm {
+
+namespace {
+template <typename T, int K>
+void march2d_adjoint_pass(hlbm_lattice_s* L) {
+  const March2 m = march2d_plan(L, K, sizeof(T) == 8);
+  const MarchAdj ac{L->adj_les, L->adj_omega};
+  const dim3 grid((unsigned)((m.strips * m.chunks + 3) / 4));
+  k_march2d_adjoint<T, K><<<grid, 256, 0, L->stream>>>(make_geo(L), make_obj(L), ac, m, (const T*)L->phi,
+                                                       (T*)L->phi2, (const T*)L->prep, L->src, L->oprep,
+                                                       (const T*)L->pv[L->pvcur], (T*)L->pv[L->pvcur ^ 1]);
+}
+}  // namespace
+
+// Four iterations a pass on lattices with work for every SIMD, two on smaller
+// ones, where the halo of four levels costs more than the launch it saves
+// (400 x 160 FP32: 3.8 us an iteration with two, 4.5 with four; 1024 x 512 with
+// the dissipation box 8.1 and 7.3, FP64 with the drag plane 12.5 and 11.6).
+int adjoint_pass_steps(const hlbm_lattice_s* L, int64_t left) {
+#ifdef HLBM_DEV
+  if (getenv("HLBM_K")) { int k = atoi(getenv("HLBM_K")); if (k <= 1) return 1; if (left >= k) return k; }
+#endif
+  return left >= 4 && L->n >= 400000 ? 4 : (left >= 2 ? 2 : 1);
+}
+
+hipError_t launch_adjoint_pass(hlbm_lattice_s* L, int K) {
+  const bool f64 = L->desc.precision == HLBM_FP64;
+  if (K == 4) {
+    if (f64) march2d_adjoint_pass<double, 4>(L); else march2d_adjoint_pass<float, 4>(L);
+  } else if (K == 2) {
+    if (f64) march2d_adjoint_pass<double, 2>(L); else march2d_adjoint_pass<float, 2>(L);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  const hipError_t e = hipGetLastError();
+  if (e == hipSuccess) std::swap(L->phi, L->phi2);
+  return e;
+}
+
+}  // namespace hlbm

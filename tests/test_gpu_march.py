@@ -45,3 +45,45 @@ def test_primal_passes_equal_single_steps_2d(prec, bc):
             assert np.array_equal(a.probe(), b.probe()), (nx, ny, steps)
         a.close()
         b.close()
+
+
+REGIONS_2D = {"ffa": lambda nx, ny: ((min(nx - 2, 60), 0, 0), (min(nx - 2, 60), ny - 1, 0)),
+              "diss": lambda nx, ny: ((1, ny // 5, 0), (nx - 2, ny - 1, 0))}
+
+
+def _adjoints(H, a, b, source, iters, singles):
+    """Runs `iters` iterations on a by its own launches and on b by single packed iterations."""
+    if singles == 0:
+        for L in (a, b):
+            L.solve_adjoint(source, tau_adj=0.6, turb=H.TURB_FROZEN, max_iters=0)
+    g = H.Group()
+    g.set([b], [H.GROUP_ADJOINT])
+    for _ in range(iters):
+        g.step(1)
+    g.synchronize()
+    g.close()
+    a.solve_adjoint(source, tau_adj=0.6, turb=H.TURB_FROZEN, max_iters=iters, restart=False)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("bc", [(2, 1, 0), (2, 0, 0), (0, 0, 0), (0, 1, 0)])
+def test_adjoint_passes_equal_single_iterations_2d(prec, bc):
+    from paper_2606_31707_amd import hlbm as H
+    for i, (nx, ny) in enumerate(SIZES_2D):
+        cs = (0.0, 0.1)[i % 2]
+        for obj in ("ffa", "diss"):
+            lo, hi = REGIONS_2D[obj](nx, ny)
+            say("adjoint passes", prec, bc, nx, ny, cs, obj)
+            a, b = (lattice(H, H.D2Q9, (nx, ny, 1), prec, bc, 0, cs) for _ in range(2))
+            for L in (a, b):
+                L.set_objective(H.OBJ_FFA if obj == "ffa" else H.OBJ_DISS, lo, hi, u0=0.04)
+                L.run_primal(3)
+                L.run_primal(5, accumulate=True)
+            done = 0
+            for iters in (4, 6, 2, 14):
+                _adjoints(H, a, b, H.SOURCE_MEAN, iters, done)
+                done += iters
+                assert np.array_equal(a.adjoint(), b.adjoint()), (nx, ny, obj, done)
+                assert np.array_equal(a.gradient(), b.gradient()), (nx, ny, obj, done)
+            a.close()
+            b.close()
