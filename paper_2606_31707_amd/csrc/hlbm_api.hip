@@ -906,9 +906,9 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
     L->adj_diff = turb_diff ? 1 : 0;
     L->adj_omega = 1.0 / tau_adj;
   }
-  const bool passes = adjoint_passes_of(&L->desc, L->obj_kind);
+  const bool passes = adjoint_passes_of(&L->desc);
   if (passes) lat_alloc_second(L, &L->phi2, as * L->q * plane);
-  const bool multi = L->phi2 != nullptr && passes && !turb_diff && !stream_capturing(L->stream);
+  const bool multi = L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !stream_capturing(L->stream);
   int64_t iters = o->max_iters + (o->max_iters & 1);
   int64_t M = o->check_every > 0 ? o->check_every : 100;
   M += (M & 1);

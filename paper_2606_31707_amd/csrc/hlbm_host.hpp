@@ -58,16 +58,16 @@ inline int nb_of(int stencil) { return 1 + dim_of(stencil) + nsym_of(stencil); }
 // there stays on its row, which a strip does not provide for), one-row
 // channels (their row is beside both walls), and rows whose byte offsets
 // exceed 32 bits; for the adjoint also the HRR collision (its frozen data would
-// have to wait for the later levels as well) and J_MEA.
+// have to wait for the later levels as well).  J_MEA takes single steps too, but counts the second phi
+// array: a window can be given another objective.
 inline bool primal_passes_of(const hlbm_desc* d) {
   return d->stencil == HLBM_D2Q9 && d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
          (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->force[0] == 0.0 && d->force[1] == 0.0 &&
          d->force[2] == 0.0;
 }
-inline bool adjoint_passes_of(const hlbm_desc* d, int objective) {
+inline bool adjoint_passes_of(const hlbm_desc* d) {
   return d->stencil == HLBM_D2Q9 && d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
-         (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->collision == HLBM_COLL_BGK &&
-         objective != HLBM_OBJ_MEA;
+         (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->collision == HLBM_COLL_BGK;
 }
 
 // What is wrong with a descriptor, or nullptr if it is valid.
@@ -135,7 +135,7 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
     b += P * 8 * (dim + 2);                             // gradient data
     b += G * (8 * (1 + dim) + 2 * as * q);              // outlet data, outlet adjoint values
     b += P * as * q;                                    // residual snapshot
-    if (adjoint_passes_of(desc, objective)) b += P * as * q;  // second phi array (multi-iteration passes)
+    if (adjoint_passes_of(desc)) b += P * as * q;  // second phi array (multi-iteration passes)
   }
   *bytes = b;
   return nullptr;
