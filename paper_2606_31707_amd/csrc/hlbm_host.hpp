@@ -57,11 +57,15 @@ inline int nb_of(int stencil) { return 1 + dim_of(stencil) + nsym_of(stencil); }
 // remain for a body force (tests), walls on the x axis (a value that bounces
 // there stays on its row, which a strip does not provide for), one-row
 // channels (their row is beside both walls), and rows whose byte offsets
-// exceed 32 bits; for the adjoint also the HRR collision (its frozen data would
-// have to wait for the later levels as well).  J_MEA takes single steps too, but counts the second phi
+// exceed 32 bits; in 3D fewer than two planes, and FP16S, whose conversions cost
+// what the saved bytes give (192x96x64 21.5 us a step, 32.5 with passes;
+// 756x168x84 with walls 158 and 198; 768x384x128 565 and 478); for the adjoint
+// also the HRR collision (its frozen data would have to wait for the later
+// levels as well).  J_MEA takes single steps too, but counts the second phi
 // array: a window can be given another objective.
 inline bool primal_passes_of(const hlbm_desc* d) {
-  return d->stencil == HLBM_D2Q9 && d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
+  if (d->stencil == HLBM_D3Q19 && (d->nz < 2 || d->precision == HLBM_FP16S)) return false;
+  return d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
          (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->force[0] == 0.0 && d->force[1] == 0.0 &&
          d->force[2] == 0.0;
 }

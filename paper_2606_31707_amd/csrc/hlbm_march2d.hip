@@ -38,6 +38,18 @@ March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64) {
   return m;
 }
 
+Probe make_probe(const hlbm_lattice_s* L, int K) {
+  Probe pr{{nullptr, nullptr, nullptr, nullptr}, 0, 0, 0};
+  if (L->probe_buf != nullptr && L->probe_cap > 0) {
+    const int64_t nx = L->desc.nx, ny = L->desc.ny;
+    for (int i = 0; i < K; ++i) pr.out[i] = L->probe_buf + (L->probe_n + i) % L->probe_cap;
+    pr.x = (int)(L->probe_cell % nx);
+    pr.y = (int)(L->probe_cell / nx % ny);
+    pr.z = (int)(L->probe_cell / (nx * ny));
+  }
+  return pr;
+}
+
 namespace {
 template <typename S, int K>
 void march2d(hlbm_lattice_s* L) {
@@ -45,12 +57,7 @@ void march2d(hlbm_lattice_s* L) {
   const double cs = L->desc.smagorinsky_cs;
   const MarchColl c{L->desc.tau, 1.0 / L->desc.tau, 18.0 * sqrt(2.0) * cs * cs};
   const March2 m = march2d_plan(L, K, sizeof(S) == 8);
-  Probe pr{{nullptr, nullptr, nullptr, nullptr}, 0, 0};
-  if (L->probe_buf != nullptr && L->probe_cap > 0) {
-    for (int i = 0; i < K; ++i) pr.out[i] = L->probe_buf + (L->probe_n + i) % L->probe_cap;
-    pr.x = (int)(L->probe_cell % L->desc.nx);
-    pr.y = (int)(L->probe_cell / L->desc.nx);
-  }
+  const Probe pr = make_probe(L, K);
   const dim3 grid((unsigned)((m.strips * m.chunks + 3) / 4));
   const S* A = (const S*)L->f;
   S* B = (S*)L->f2;
@@ -76,14 +83,23 @@ void march2d(hlbm_lattice_s* L) {
 int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left) {
   if (accumulate) return 1;
 #ifdef HLBM_DEV
+  if (getenv("HLBM_K") && L->desc.stencil == HLBM_D3Q19) { return atoi(getenv("HLBM_K")) > 1 && left >= 2 ? 2 : 1; }
   if (getenv("HLBM_K")) { int k = atoi(getenv("HLBM_K")); if (k <= 1) return 1; if (left >= k) return k; }
 #endif
+  if (L->desc.stencil == HLBM_D3Q19) return left >= 2 ? 2 : 1;
   const bool two = L->desc.precision == HLBM_FP16S && !L->large;
   return left >= 4 && !two ? 4 : (left >= 2 ? 2 : 1);
 }
 
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K) {
   (void)accumulate;
+  hipError_t e = hipSuccess;
+  if (L->desc.stencil == HLBM_D3Q19) {
+    if (K != 2) return hipErrorInvalidValue;
+    e = launch_march3d(L);
+    if (e == hipSuccess) std::swap(L->f, L->f2);
+    return e;
+  }
   switch (L->desc.precision * 8 + K) {
     case 0 + 2: march2d<double, 2>(L); break;
     case 0 + 4: march2d<double, 4>(L); break;
@@ -93,7 +109,7 @@ hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K) {
     case 16 + 4: march2d<_Float16, 4>(L); break;
     default: return hipErrorInvalidValue;
   }
-  const hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e == hipSuccess) std::swap(L->f, L->f2);
   return e;
 }

@@ -39,6 +39,7 @@ struct March2 {
   int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
 };
 March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64);
+hipError_t launch_march3d(hlbm_lattice_s* L);  // two D3Q19 steps (hlbm_march3d.hip)
 
 // Values of the lane one to the left (cx = +1 moves them right) / right.
 // DPP wave_shr:1 / wave_shl:1; the end lanes get 0, which nobody uses.
@@ -276,8 +277,10 @@ __device__ __forceinline__ T lane_value(T v, int i) {
 // Velocity probe of a pass: step t of it records into out[t].
 struct Probe {
   double* out[4];  // null: none
-  int x, y;
+  int x, y, z;
 };
+
+Probe make_probe(const hlbm_lattice_s* L, int K);
 
 // Scalars of the collision (no body force: such lattices take single steps).
 struct MarchColl {

@@ -87,3 +87,26 @@ def test_adjoint_passes_equal_single_iterations_2d(prec, bc):
                 assert np.array_equal(a.gradient(), b.gradient()), (nx, ny, obj, done)
             a.close()
             b.close()
+
+
+SIZES_3D = [(3, 2, 2), (62, 14, 5), (63, 15, 4), (64, 6, 3), (130, 29, 9), (20, 7, 12)]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("bc", [(2, 0, 0), (2, 1, 0), (2, 1, 1), (0, 0, 0), (0, 1, 1), (2, 0, 1)])
+def test_primal_passes_equal_single_steps_3d(prec, bc):
+    from paper_2606_31707_amd import hlbm as H
+    for i, size in enumerate(SIZES_3D):
+        coll, cs = ((0, 0.0), (0, 0.1), (1, 0.0), (1, 0.1))[i % 4]
+        say("primal passes", prec, bc, size, coll, cs)
+        a, b = (lattice(H, H.D3Q19, size, prec, bc, coll, cs) for _ in range(2))
+        for L in (a, b):
+            L.set_probe(min(size[0] - 1, size[0] // 2 + 1), size[1] // 2, size[2] // 2)
+        for steps in (4, 7, 5, 2):
+            a.run_primal(steps)
+            for _ in range(steps):
+                b.run_primal(1)
+            assert np.array_equal(a.populations(), b.populations()), (size, steps)
+            assert np.array_equal(a.probe(), b.probe()), (size, steps)
+        a.close()
+        b.close()
