@@ -407,7 +407,12 @@ hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out) {
   };
   if ((s = lat_alloc(L, &L->f, L->ssize * L->q * L->plane)) != HLBM_OK) return bail(s);
   if ((s = lat_alloc(L, &L->dpor, L->dsize * L->plane)) != HLBM_OK) return bail(s);
-  if (primal_passes_of(&L->desc)) lat_alloc_second(L, &L->f2, L->ssize * L->q * L->plane);
+  if (primal_passes_of(&L->desc)) {
+    lat_alloc_second(L, &L->f2, L->ssize * L->q * L->plane);
+    if (L->f2 && desc->precision == HLBM_FP64 &&
+        (s = lat_alloc(L, &L->rcopy2, L->asize * region_copy_stride(L->q, (int)L->asize) * L->gplane)) != HLBM_OK)
+      return bail(s);
+  }
   if ((s = lat_alloc(L, &L->ghost, L->ssize * L->q * L->gplane)) != HLBM_OK) return bail(s);
   if ((s = ensure_partials(L, 2 * n_blocks(L) + 8)) != HLBM_OK) return bail(s);
   if (hipHostMalloc((void**)&L->red_host, 4 * sizeof(double)) != hipSuccess)
@@ -433,7 +438,7 @@ void hlbm_destroy(hlbm_lattice L) {
   (void)hipStreamSynchronize(L->stream);
   void* bufs[] = {L->f,   L->f2,    L->dpor,  L->ghost, L->acc_rho, L->acc_j, L->acc_f, L->acc_tau, L->acc_obj, L->acc_pend,
                   L->phi, L->phi2, L->prep,  L->src,   L->gdat,    L->oprep, L->pv[0], L->pv[1],   L->snap,
-                  L->red, L->usnap, L->probe_buf, L->mea_flag, L->mea_src, L->rcopy, L->tan_f, L->tan_ghost,
+                  L->red, L->usnap, L->probe_buf, L->mea_flag, L->mea_src, L->rcopy, L->rcopy2, L->tan_f, L->tan_ghost,
                   L->tan_v, L->tan_rec};
   for (void* p : bufs) dev_free(p);
   if (L->red_host) (void)hipHostFree(L->red_host);

@@ -117,7 +117,10 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
                           (uint64_t)desc->nz;
   // populations, porosity, outlet values, reduction partials, steady-check snapshot
   uint64_t b = P * (q * ss + ds) + G * q * ss + 8 * (2 * blocks + 8) + 8 * P * dim;
-  if (primal_passes_of(desc)) b += P * q * ss;  // second population array (multi-step passes)
+  if (primal_passes_of(desc)) {
+    b += P * q * ss;  // second population array (multi-step passes)
+    if (desc->precision == HLBM_FP64) b += G * (uint64_t)region_copy_stride(q, (int)as) * as;  // a step's region records
+  }
   if (region_cells > 0) {  // objective terms and adjoint source over the region
     const uint64_t rp = (uint64_t)round_up(region_cells, 128);
     b += 2 * 8 * rp * ncoef;

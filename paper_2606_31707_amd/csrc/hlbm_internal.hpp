@@ -51,6 +51,7 @@ struct hlbm_lattice_s {
   int64_t rplane = 0;
   double u0 = 0.0, p0 = 1.0 / 3.0;
   void* rcopy = nullptr;              // rplane records: region cells' pre-collision state (region_copy_used)
+  void* rcopy2 = nullptr;             // FP64: gplane records of the first step of a window pass
   unsigned char* mea_flag = nullptr;  // rplane: J_MEA surface nodes of the region
   double* mea_src = nullptr;          // q * rplane: J_MEA's constant dJ/df_k over the region
   int mea_dirty = 1;                  // flags to rebuild (porosity or region changed)
@@ -184,6 +185,16 @@ hipError_t launch_primal_step(hlbm_lattice_s* L, int accumulate);
 // L->f, writes L->f2 and swaps the two.
 int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left);
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K);
+hipError_t launch_window_pass(hlbm_lattice_s* L, int K);  // K window steps
+int window_pass_steps(const hlbm_lattice_s* L, int64_t left);
+// Objective terms of a small region: from records (one of region_copy_stride
+// values per cell and step, in step order), from the canonical state (parity 0)
+struct Records {
+  const void* rec[4];
+  int n;
+};
+hipError_t launch_region_records(hlbm_lattice_s* L, const Records& rc);
+hipError_t launch_region_state(hlbm_lattice_s* L);
 hipError_t launch_gather(hlbm_lattice_s* L, double* out_dev);
 hipError_t launch_scatter(hlbm_lattice_s* L, const double* in_dev);
 hipError_t launch_moments(hlbm_lattice_s* L, double* rho_dev, double* u_dev);

@@ -416,6 +416,26 @@ __device__ __forceinline__ void accumulate_terms(double* acc, int64_t stride, in
   for (int m = 0; m < N; ++m) acc[m * stride + r] = o[m] + v[m];
 }
 
+// Pre-collision state and porosity of region cell r: one record of whole
+// 128-byte lines, as 16-byte vectors.
+template <int Q, typename T>
+__device__ __forceinline__ void store_record(void* rec, int64_t r, const T (&s)[Q], T d) {
+  constexpr int RC = region_copy_stride(Q, (int)sizeof(T));
+  constexpr int V = 16 / (int)sizeof(T);
+  typedef T TV __attribute__((ext_vector_type(V)));
+  TV* rc = (TV*)((T*)rec + r * RC);
+#pragma unroll
+  for (int v = 0; v < RC / V; ++v) {
+    TV t;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int k = v * V + i;
+      t[i] = k < Q ? s[k < Q ? k : 0] : (k == Q ? d : (T)0);
+    }
+    rc[v] = t;
+  }
+}
+
 // ---- J_MEA, the momentum-exchange drag (Sec. 4, Eq. obj_mea) -------------
 // J = (1/A) sum_{x in surface} sum_i xi_i,x (f_i(x + xi_i) - f_opp(i)(x)) is
 // linear in f.  Collected by the slot each term reads it is
@@ -937,23 +957,7 @@ __device__ __forceinline__ void primal_cell(const Geo& g, const Coll& c, const O
   }
   if constexpr (ACC == 3) {  // a small region's cells hand their state to the region pass
     int64_t rr;
-    if (acc.rcopy && region_index<Q>(ob, x, y, z, rr)) {
-      // one record of whole 128-byte lines per cell, written as 16-byte vectors
-      constexpr int RC = region_copy_stride(Q, (int)sizeof(T));
-      constexpr int V = 16 / (int)sizeof(T);
-      typedef T TV __attribute__((ext_vector_type(V)));
-      TV* rc = (TV*)((T*)acc.rcopy + rr * RC);
-#pragma unroll
-      for (int v = 0; v < RC / V; ++v) {
-        TV t;
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-          const int k = v * V + i;
-          t[i] = k < Q ? s[k < Q ? k : 0] : (k == Q ? d : (T)0);
-        }
-        rc[v] = t;
-      }
-    }
+    if (acc.rcopy && region_index<Q>(ob, x, y, z, rr)) store_record<Q, T>(acc.rcopy, rr, s, d);
   }
 
   T drho, jx, jy, jz;
@@ -1466,24 +1470,33 @@ __global__ __launch_bounds__(256) void k_window_region(const Geo g, const ObjBox
   accumulate_terms<Coef<Q>::N>(acc_obj, ob.rplane, r, terms);
 }
 
-// The same objective terms from the copy of the region cells' pre-collision
-// state and porosity that the window sweep wrote (moment-form objectives):
-// one lane per region cell reading its own record, instead of one cache line
-// per population and cell of the lattice.
+// The same objective terms from the copies of the region cells' pre-collision
+// state and porosity that the window sweep wrote, one per step (moment-form
+// objectives): one lane per region cell reading its own records, instead of
+// one cache line per population and cell of the lattice.
 template <int Q, typename T>
-__global__ __launch_bounds__(256) void k_window_region_copy(const ObjBox ob, const T* __restrict__ rc,
+__global__ __launch_bounds__(256) void k_window_region_copy(const ObjBox ob, const Records rc,
                                                             double* __restrict__ acc_obj) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (!ob.active || r >= (int64_t)ob.rn[0] * ob.rn[1] * ob.rn[2]) return;
-  const T* rec = rc + r * region_copy_stride(Q, (int)sizeof(T));
-  double sd[Q];
+  constexpr int N = Coef<Q>::N;
+  double sum[N];
 #pragma unroll
-  for (int k = 0; k < Q; ++k) sd[k] = (double)rec[k];
-  double dr, ax, ay, az, P[6], terms[Coef<Q>::N];
-  cell_moments<Q, double>(sd, dr, ax, ay, az);
-  neq_flux<Q, double>(sd, dr, ax, ay, az, 1.0 / (1.0 + dr), P);
-  objective_terms<Q>(ob, (double)rec[Q], dr, ax, ay, az, P, terms);
-  accumulate_terms<Coef<Q>::N>(acc_obj, ob.rplane, r, terms);
+  for (int m = 0; m < N; ++m) sum[m] = acc_obj[m * ob.rplane + r];
+  for (int i = 0; i < rc.n; ++i) {
+    const T* rec = (const T*)rc.rec[i] + r * region_copy_stride(Q, (int)sizeof(T));
+    double sd[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) sd[k] = (double)rec[k];
+    double dr, ax, ay, az, P[6], terms[N];
+    cell_moments<Q, double>(sd, dr, ax, ay, az);
+    neq_flux<Q, double>(sd, dr, ax, ay, az, 1.0 / (1.0 + dr), P);
+    objective_terms<Q>(ob, (double)rec[Q], dr, ax, ay, az, P, terms);
+#pragma unroll
+    for (int m = 0; m < N; ++m) sum[m] = sum[m] + terms[m];
+  }
+#pragma unroll
+  for (int m = 0; m < N; ++m) acc_obj[m * ob.rplane + r] = sum[m];
 }
 
 // Completes the grouped window accumulation when a run ends inside a group:

@@ -145,7 +145,7 @@ static void primal_mode(hlbm_lattice_s* L, int accumulate) {
     const dim3 rg((unsigned)((rcells + 255) / 256));  // one lane per region cell
     if (!mea && L->rcopy) {  // the sweep copies the region cells' state, the pass follows it
       primal_variant<Q, S, 3, HRR>(L);
-      k_window_region_copy<Q, T><<<rg, 256, 0, L->stream>>>(make_obj(L), (const T*)L->rcopy, L->acc_obj);
+      k_window_region_copy<Q, T><<<rg, 256, 0, L->stream>>>(make_obj(L), Records{{L->rcopy}, 1}, L->acc_obj);
       return;
     }
     if (mea)
@@ -190,6 +190,26 @@ static hipError_t primal_impl(hlbm_lattice_s* L, int accumulate) {
 hipError_t launch_primal_step(hlbm_lattice_s* L, int accumulate) {
   HLBM_DISPATCH(L, primal_impl, L, accumulate);
 }
+
+static dim3 region_grid(const hlbm_lattice_s* L) {  // one lane per region cell
+  return dim3((unsigned)(((int64_t)L->rn[0] * L->rn[1] * L->rn[2] + 255) / 256));
+}
+template <int Q, typename S>
+static hipError_t region_records_impl(hlbm_lattice_s* L, const Records& rc) {
+  k_window_region_copy<Q, typename Prec<S>::T><<<region_grid(L), 256, 0, L->stream>>>(make_obj(L), rc, L->acc_obj);
+  return hipGetLastError();
+}
+hipError_t launch_region_records(hlbm_lattice_s* L, const Records& rc) {
+  HLBM_DISPATCH(L, region_records_impl, L, rc);
+}
+template <int Q, typename S>
+static hipError_t region_state_impl(hlbm_lattice_s* L) {
+  k_window_region<Q, S, false><<<region_grid(L), 256, 0, L->stream>>>(
+      make_geo(L), make_obj(L), (const S*)L->f, (const S*)L->ghost, 0, (const typename Prec<S>::Dd*)L->dpor,
+      L->acc_obj);
+  return hipGetLastError();
+}
+hipError_t launch_region_state(hlbm_lattice_s* L) { HLBM_DISPATCH(L, region_state_impl, L); }
 
 int64_t pend_slot_elems(const hlbm_lattice_s* L) {
   return L->plane * (2 + L->dim + (L->desc.track_mean_populations ? L->q : 0));

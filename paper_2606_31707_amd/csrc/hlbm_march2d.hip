@@ -1,6 +1,5 @@
 // hlbm_march2d.hip -- launchers of the D2Q9 multi-step passes.
 #include <cmath>
-#include <cstdlib>
 #include <utility>
 
 #include "hlbm_march2d.hpp"
@@ -31,9 +30,6 @@ March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64) {
       m.rows = rows;
     }
   }
-#ifdef HLBM_DEV
-  if (getenv("HLBM_ROWS")) m.rows = atoi(getenv("HLBM_ROWS"));
-#endif
   m.chunks = (ny + m.rows - 1) / m.rows;
   return m;
 }
@@ -81,22 +77,18 @@ void march2d(hlbm_lattice_s* L) {
 // loads and conversions rather than bytes bound a pass (1100 x 410: 4.6 us a
 // step with two, 5.0 with four; 8192 x 4096: 172 and 110).
 int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left) {
-  if (accumulate) return 1;
-#ifdef HLBM_DEV
-  if (getenv("HLBM_K") && L->desc.stencil == HLBM_D3Q19) { return atoi(getenv("HLBM_K")) > 1 && left >= 2 ? 2 : 1; }
-  if (getenv("HLBM_K")) { int k = atoi(getenv("HLBM_K")); if (k <= 1) return 1; if (left >= k) return k; }
-#endif
+  if (accumulate) return window_pass_steps(L, left);
   if (L->desc.stencil == HLBM_D3Q19) return left >= 2 ? 2 : 1;
   const bool two = L->desc.precision == HLBM_FP16S && !L->large;
   return left >= 4 && !two ? 4 : (left >= 2 ? 2 : 1);
 }
 
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K) {
-  (void)accumulate;
+  if (accumulate) return launch_window_pass(L, K);
   hipError_t e = hipSuccess;
   if (L->desc.stencil == HLBM_D3Q19) {
     if (K != 2) return hipErrorInvalidValue;
-    e = launch_march3d(L);
+    e = launch_march3d(L, false);
     if (e == hipSuccess) std::swap(L->f, L->f2);
     return e;
   }

@@ -39,7 +39,8 @@ struct March2 {
   int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
 };
 March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64);
-hipError_t launch_march3d(hlbm_lattice_s* L);  // two D3Q19 steps (hlbm_march3d.hip)
+hipError_t launch_window2d(hlbm_lattice_s* L, int K);  // K D2Q9 window steps (hlbm_window2d.hip)
+hipError_t launch_march3d(hlbm_lattice_s* L, bool window);  // two D3Q19 steps (hlbm_march3d.hip)
 
 // Values of the lane one to the left (cx = +1 moves them right) / right.
 // DPP wave_shr:1 / wave_shl:1; the end lanes get 0, which nobody uses.
@@ -282,6 +283,19 @@ struct Probe {
 
 Probe make_probe(const hlbm_lattice_s* L, int K);
 
+// Mean-flow window of a pass (BGK).  Every step adds its values to the FP64 sums in
+// step order, as single steps do; the sums pass through the levels in
+// registers, so that memory holds them once a pass.  Objective terms: of a
+// small region the levels record the cells' pre-collision state for the
+// region pass (rec), of a large one (LARGE kernels) they add the terms (obj).
+struct Window {
+  double *rho, *j, *tau;
+  ObjBox ob;
+  double* obj;
+  void* rec[4];  // records of level t (null: none); element type: the arithmetic type
+};
+Window make_window(const hlbm_lattice_s* L);
+
 // Scalars of the collision (no body force: such lattices take single steps).
 struct MarchColl {
   double tau0, omega0, kS;
@@ -299,15 +313,19 @@ struct MarchColl {
 // every iteration (no branches): rows outside what a level needs are
 // computed from whatever is there and reach no row that is stored.
 // EDGE: 0 none, 1 the strip holds an inlet or outlet column, 2 the rows come
-// near a wall or the probe (with or without an end).
-template <typename S, int K, bool HRR, bool SMAG, int EDGE>
+// near a wall, the probe or a small objective region (with or without an end).
+// ACC: 0 plain, 1 window sums, 2 window sums and the terms of a large region.
+template <typename S, int K, bool HRR, bool SMAG, int EDGE, int ACC>
 __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip& st, const int y0, const int y1,
                                         const S* __restrict__ A, S* __restrict__ B,
-                                        const typename Prec<S>::Dd* __restrict__ dpor, const Probe& pr) {
+                                        const typename Prec<S>::Dd* __restrict__ dpor, const Probe& pr,
+                                        const Window& wn) {
   using L = Lat<9>;
   using T = typename Prec<S>::T;
   using Dd = typename Prec<S>::Dd;
   constexpr int NB = K > 1 ? K - 1 : 1;
+  // window sums: drho, j, tau_eff; ACC 2: and the objective terms of the region's cells
+  constexpr int NO = Coef<9>::N, NW = SMAG ? 4 : 3, NT = ACC == 2 ? NW + NO : NW;
   const bool walls = g.bcy != BC_PERIODIC;
   const int none = -0x40000000;
   const int row_first = walls ? 0 : none, row_last = walls ? g.ny - 1 : none;
@@ -346,6 +364,38 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
     in1 = (T)to_store<S>(inlet_value<9, T>(1, ui));
     in3 = (T)to_store<S>(inlet_value<9, T>(3, ui));
   }
+  // window: rows of the sums, lanes that add to them and lanes in the region
+  const uint32_t off8 = lane_offset((uint32_t)st.x * 8u);
+  RowPtr pw(nullptr, r0, g.nx, g.ny, 8);
+  uint64_t out_row = uni64((uint64_t)g.nx * 8u * (uint64_t)(int64_t)y0);
+  const uint64_t sums[4] = {uni64((uint64_t)wn.rho), uni64((uint64_t)wn.j), uni64((uint64_t)wn.j + (uint64_t)g.plane * 8),
+                            uni64((uint64_t)wn.tau)};
+  const bool adds = ACC && st.own && !st.inlet;
+  const int rx = st.gx - wn.ob.lo[0];
+  const bool in_cols = ACC && wn.ob.active && adds && rx >= 0 && rx < wn.ob.rn[0];
+  // region rows of this chunk (empty where the strip has no region column)
+  const bool any_col = ACC && __ballot(in_cols) != 0;
+  const int reg0 = any_col ? (wn.ob.lo[1] > y0 ? wn.ob.lo[1] : y0) : 0;
+  const int reg1 = any_col ? (wn.ob.lo[1] + wn.ob.rn[1] < y1 ? wn.ob.lo[1] + wn.ob.rn[1] : y1) : 0;
+  // the terms' slots: lanes outside the region's columns read its nearest one and write nothing
+  const uint32_t offr =
+      lane_offset(8u * (uint32_t)(ACC == 2 ? (rx < 0 ? 0 : (rx < wn.ob.rn[0] ? rx : wn.ob.rn[0] - 1)) : 0));
+  auto term_slot = [&](const int row, const int m) {
+    return lane_ptr<double>(uni64((uint64_t)(wn.obj + m * wn.ob.rplane +
+                                             (int64_t)wn.ob.rn[0] * (int64_t)(row - wn.ob.lo[1]))), offr);
+  };
+  double wcur[NT], hold[NB][NT];
+  auto load_sums = [&](const int row) {
+    if (ACC && row >= y0 && row < y1) {
+#pragma unroll
+      for (int a = 0; a < NW; ++a) wcur[a] = *lane_ptr<const double>(sums[a] + pw.base, off8);
+    }
+    if (ACC == 2 && row >= reg0 && row < reg1) {
+#pragma unroll
+      for (int m = 0; m < NO; ++m) wcur[NT - NO + m] = *term_slot(row, m);
+    }
+    if (ACC) pw.next();
+  };
   Wait<T> w[NB];
   T cur[9], dcur, d[K];
   auto step = [&](const int r, auto phase) {
@@ -356,12 +406,16 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
 #pragma unroll
     for (int t = K - 1; t > 0; --t) d[t] = d[t - 1];
     d[0] = dcur;
+    double sum[NT];
+#pragma unroll
+    for (int a = 0; a < NT; ++a) sum[a] = wcur[a];
 #pragma unroll
     for (int t = 0; t < K; ++t) {
       const int row = r - t;
       if (t == 1) {  // level 0 has used the row: load the next one (past the last: in bounds, unused)
         __builtin_amdgcn_sched_barrier(0);
         load(cur, dcur);
+        load_sums(r + 1);
       }
       if (EDGE == 2 || t == 1) __builtin_amdgcn_sched_barrier(0);  // EDGE 2: levels kept apart (registers)
       if (t == K - 1 && row < y0) return;
@@ -371,6 +425,44 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
       const T ir = recip(rho);
       if (EDGE == 2 && probe_lane && row == pr.y) *pr.out[t] = (double)(jy * ir);
       relaxation<9, T, HRR>(c, SMAG, s, drho, jx, jy, jz, ir, omega, taue, p2);
+      if (ACC) {
+        sum[0] = sum[0] + (double)drho;
+        sum[1] = sum[1] + (double)jx;
+        sum[2] = sum[2] + (double)jy;
+        if (SMAG) sum[NW - 1] = sum[NW - 1] + (double)taue;
+        if (ACC == 2 && row >= reg0 && row < reg1) {
+          double sd[9], terms[NO], dr, ax, ay, az, P[6];
+#pragma unroll
+          for (int k = 0; k < 9; ++k) sd[k] = (double)s[k];
+          cell_moments<9, double>(sd, dr, ax, ay, az);
+          neq_flux<9, double>(sd, dr, ax, ay, az, 1.0 / (1.0 + dr), P);
+          objective_terms<9>(wn.ob, (double)d[t], dr, ax, ay, az, P, terms);
+#pragma unroll
+          for (int m = 0; m < NO; ++m) sum[NT - NO + m] = sum[NT - NO + m] + terms[m];
+          if (t == K - 1 && in_cols) {
+#pragma unroll
+            for (int m = 0; m < NO; ++m) *term_slot(row, m) = sum[NT - NO + m];
+          }
+        }
+        if (t == K - 1) {
+          if (adds) {
+#pragma unroll
+            for (int a = 0; a < NW; ++a) *lane_ptr<double>(sums[a] + out_row, off8) = sum[a];
+          }
+          out_row += (uint64_t)g.nx * 8u;
+        } else {  // to the next level, one row later
+#pragma unroll
+          for (int a = 0; a < NT; ++a) {
+            const double v = hold[t % NB][a];
+            hold[t % NB][a] = sum[a];
+            sum[a] = v;
+          }
+        }
+        if (ACC == 1 && EDGE == 2 && row >= reg0 && row < reg1) {
+          if (in_cols && wn.rec[t])
+            store_record<9, T>(wn.rec[t], (int64_t)rx + (int64_t)wn.ob.rn[0] * (int64_t)(row - wn.ob.lo[1]), s, d[t]);
+        }
+      }
       collide_cell<9, T, HRR>(c, s, drho, jx, jy, jz, rho, ir, d[t], omega, p2);
       if (EDGE == 1 || (EDGE == 2 && st.ends)) {
         const T ux = jx * ir, uy = jy * ir, uz = jz * ir;
@@ -399,6 +491,7 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
   };
 
   load(cur, dcur);
+  load_sums(r0);
   for (int r = r0;; r += 2) {
     step(r, std::integral_constant<int, 0>{});
     if (r + 1 > r_end) break;
@@ -412,6 +505,11 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
 template <typename S, int K>
 constexpr int march2d_waves() {
   return sizeof(S) == 8 ? (K > 2 ? 2 : 3) : (K > 2 ? 4 : 6);
+}
+// With window sums, which wait in registers as well.
+template <typename S, int K, bool LARGE>
+constexpr int window2d_waves() {
+  return LARGE || sizeof(S) == 8 || K > 2 ? 2 : 4;
 }
 
 // K primal steps (rows a3, a4).  HRR, SMAG: collision model, closure.
@@ -427,12 +525,39 @@ __global__ __launch_bounds__(256, (march2d_waves<S, K>())) void k_march2d(const 
   const int y0 = chunk * m.rows, y1 = y0 + m.rows < g.ny ? y0 + m.rows : g.ny;
   const bool at_walls = g.bcy != BC_PERIODIC && (y0 < K || y1 > g.ny - K);
   const bool probed = pr.out[0] != nullptr && pr.y >= y0 && pr.y < y1 && __ballot(st.own && st.gx == pr.x) != 0;
+  const Window wn{};
   if (at_walls || probed)
-    march2d<S, K, HRR, SMAG, 2>(g, c, st, y0, y1, A, B, dpor, pr);
+    march2d<S, K, HRR, SMAG, 2, 0>(g, c, st, y0, y1, A, B, dpor, pr, wn);
   else if (st.ends)
-    march2d<S, K, HRR, SMAG, 1>(g, c, st, y0, y1, A, B, dpor, pr);
+    march2d<S, K, HRR, SMAG, 1, 0>(g, c, st, y0, y1, A, B, dpor, pr, wn);
   else
-    march2d<S, K, HRR, SMAG, 0>(g, c, st, y0, y1, A, B, dpor, pr);
+    march2d<S, K, HRR, SMAG, 0, 0>(g, c, st, y0, y1, A, B, dpor, pr, wn);
+}
+
+// K primal steps of a mean-flow window (BGK).  LARGE: the objective region is
+// a sizeable part of the lattice, its terms are added by the sweep.
+template <typename S, int K, bool SMAG, bool LARGE>
+__global__ __launch_bounds__(256, (window2d_waves<S, K, LARGE>())) void k_window2d(
+    const Geo g, const MarchColl mc, const March2 m, const S* __restrict__ A, S* __restrict__ B,
+    const typename Prec<S>::Dd* __restrict__ dpor, const Probe pr, const Window wn) {
+  const Coll c = mc.coll();
+  const int id = sweep_tile((int)blockIdx.x, (int)gridDim.x) * 4 + wave_uniform((int)(threadIdx.x >> 6));
+  if (id >= m.strips * m.chunks) return;
+  const int chunk = wave_uniform(id / m.strips);
+  const Strip st = make_strip<K>(g, id - chunk * m.strips);
+  const int y0 = chunk * m.rows, y1 = y0 + m.rows < g.ny ? y0 + m.rows : g.ny;
+  const bool at_walls = g.bcy != BC_PERIODIC && (y0 < K || y1 > g.ny - K);
+  const bool probed = pr.out[0] != nullptr && pr.y >= y0 && pr.y < y1 && __ballot(st.own && st.gx == pr.x) != 0;
+  const ObjBox& ob = wn.ob;
+  const bool recorded = !LARGE && ob.active && y0 < ob.lo[1] + ob.rn[1] && y1 > ob.lo[1] &&
+                        __ballot(st.own && st.gx >= ob.lo[0] && st.gx < ob.lo[0] + ob.rn[0]) != 0;
+  constexpr int ACC = LARGE ? 2 : 1;
+  if (at_walls || probed || recorded)
+    march2d<S, K, false, SMAG, 2, ACC>(g, c, st, y0, y1, A, B, dpor, pr, wn);
+  else if (st.ends)
+    march2d<S, K, false, SMAG, 1, ACC>(g, c, st, y0, y1, A, B, dpor, pr, wn);
+  else
+    march2d<S, K, false, SMAG, 0, ACC>(g, c, st, y0, y1, A, B, dpor, pr, wn);
 }
 
 // =========================================================================

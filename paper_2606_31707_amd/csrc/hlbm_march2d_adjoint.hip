@@ -1,7 +1,6 @@
 // hlbm_march2d_adjoint.hip -- launcher of the D2Q9 multi-iteration adjoint
 // passes.
 #include <cmath>
-#include <cstdlib>
 #include <utility>
 
 #include "hlbm_march2d.hpp"
@@ -25,9 +24,6 @@ void march2d_adjoint_pass(hlbm_lattice_s* L) {
 // (400 x 160 FP32: 3.8 us an iteration with two, 4.5 with four; 1024 x 512 with
 // the dissipation box 8.1 and 7.3, FP64 with the drag plane 12.5 and 11.6).
 int adjoint_pass_steps(const hlbm_lattice_s* L, int64_t left) {
-#ifdef HLBM_DEV
-  if (getenv("HLBM_K")) { int k = atoi(getenv("HLBM_K")); if (k <= 1) return 1; if (left >= k) return k; }
-#endif
   return left >= 4 && L->n >= 400000 ? 4 : (left >= 2 ? 2 : 1);
 }
 

@@ -26,7 +26,7 @@ March3 march3d_plan(const hlbm_lattice_s* L, int R) {
 
 namespace {
 template <typename S>
-void march3d_pass(hlbm_lattice_s* L) {
+void march3d_pass(hlbm_lattice_s* L, bool window) {
   constexpr int R = march3d_rows<typename Prec<S>::T>();
   const double cs = L->desc.smagorinsky_cs;
   const MarchColl c{L->desc.tau, 1.0 / L->desc.tau, 18.0 * sqrt(2.0) * cs * cs};
@@ -37,7 +37,13 @@ void march3d_pass(hlbm_lattice_s* L) {
   const S* A = (const S*)L->f;
   S* B = (S*)L->f2;
   const auto* dp = (const typename Prec<S>::Dd*)L->dpor;
-  if (L->desc.collision == HLBM_COLL_HRR) {
+  if (window) {
+    const Window wn = make_window(L);
+    if (cs > 0.0)
+      k_window3d<S, true><<<grid, block, 0, L->stream>>>(g, c, m, A, B, dp, pr, wn);
+    else
+      k_window3d<S, false><<<grid, block, 0, L->stream>>>(g, c, m, A, B, dp, pr, wn);
+  } else if (L->desc.collision == HLBM_COLL_HRR) {
     if (cs > 0.0)
       k_march3d<S, true, true><<<grid, block, 0, L->stream>>>(g, c, m, A, B, dp, pr);
     else
@@ -51,11 +57,11 @@ void march3d_pass(hlbm_lattice_s* L) {
 }
 }  // namespace
 
-hipError_t launch_march3d(hlbm_lattice_s* L) {
+hipError_t launch_march3d(hlbm_lattice_s* L, bool window) {
   if (L->desc.precision == HLBM_FP64)
-    march3d_pass<double>(L);
+    march3d_pass<double>(L, window);
   else
-    march3d_pass<float>(L);
+    march3d_pass<float>(L, window);
   return hipGetLastError();
 }
 

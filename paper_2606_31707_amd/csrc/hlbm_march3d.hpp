@@ -241,11 +241,11 @@ __device__ __forceinline__ void push3(const Geo& g, const Tile3& t, const int z,
   }
 }
 
-template <typename S, bool HRR, bool SMAG, bool ENDS, bool WALLS>
+template <typename S, bool HRR, bool SMAG, bool ENDS, bool WALLS, bool ACC>
 __device__ __forceinline__ void march3d(const Geo& g, const Coll& c, const March3& m, const int tx, const int ty,
                                         const int z0, const int z1, const S* __restrict__ A, S* __restrict__ B,
                                         const typename Prec<S>::Dd* __restrict__ dpor, const Probe& pr,
-                                        typename Prec<S>::T* __restrict__ lds) {
+                                        const Window& wn, typename Prec<S>::T* __restrict__ lds) {
   using L = Lat<19>;
   using T = typename Prec<S>::T;
   using Dd = typename Prec<S>::Dd;
@@ -280,14 +280,39 @@ __device__ __forceinline__ void march3d(const Geo& g, const Coll& c, const March
   }
   const bool probe_lane = pr.out[0] != nullptr && t.own && !t.inlet && t.gx == pr.x && t.gy == pr.y;
   const int probe_z = __ballot(probe_lane) != 0 ? pr.z : -0x40000000;
+  // window: sums drho, j, tau_eff and, where the wavefront holds region cells, their planes
+  constexpr int NW = SMAG ? 5 : 4;
+  const uint64_t sums[5] = {uni64((uint64_t)wn.rho), uni64((uint64_t)wn.j), uni64((uint64_t)(wn.j + g.plane)),
+                            uni64((uint64_t)(wn.j + 2 * g.plane)), uni64((uint64_t)wn.tau)};
+  const uint32_t off8 = lane_offset((uint32_t)t.x * 8u);
+  const bool adds = ACC && t.own && !t.inlet;
+  const ObjBox& ob = wn.ob;
+  const bool in_region = ACC && ob.active && adds && t.gx >= ob.lo[0] && t.gx < ob.lo[0] + ob.rn[0] &&
+                         t.gy >= ob.lo[1] && t.gy < ob.lo[1] + ob.rn[1];
+  const bool any_region = ACC && __ballot(in_region) != 0;
+  const int reg0 = any_region ? (ob.lo[2] > z0 ? ob.lo[2] : z0) : 0;
+  const int reg1 = any_region ? (ob.lo[2] + ob.rn[2] < z1 ? ob.lo[2] + ob.rn[2] : z1) : 0;
+  T v0[NW], v1[NW];  // this level's values
   // one cell of either level: collision, ends
-  auto collide = [&](const int lv, const int z, T (&s)[19], const T d, T (&o)[5]) {
+  auto collide = [&](const int lv, const int z, T (&s)[19], const T d, T (&o)[5], T (&val)[NW]) {
     T drho, jx, jy, jz, omega, taue, p2[6];
     cell_moments<19, T>(s, drho, jx, jy, jz);
     const T rho = (T)1 + drho;
     const T ir = recip(rho);
     if (z == probe_z && z >= z0 && z < z1 && probe_lane) *pr.out[lv] = (double)(jy * ir);
     relaxation<19, T, HRR>(c, SMAG, s, drho, jx, jy, jz, ir, omega, taue, p2);
+    if (ACC) {
+      val[0] = drho;
+      val[1] = jx;
+      val[2] = jy;
+      val[3] = jz;
+      if (SMAG) val[NW - 1] = taue;
+      if (__builtin_expect(z >= reg0 && z < reg1, 0) && wn.rec[lv] != nullptr && in_region)
+        store_record<19, T>(wn.rec[lv],
+                            (int64_t)(t.gx - ob.lo[0]) +
+                                (int64_t)ob.rn[0] * ((t.gy - ob.lo[1]) + (int64_t)ob.rn[1] * (z - ob.lo[2])),
+                            s, d);
+    }
     collide_cell<19, T, HRR>(c, s, drho, jx, jy, jz, rho, ir, d, omega, p2);
     if (ENDS) {
       const T ux = jx * ir, uy = jy * ir, uz = jz * ir;
@@ -301,7 +326,7 @@ __device__ __forceinline__ void march3d(const Geo& g, const Coll& c, const March
     }
   };
   Wait3<T> w;
-  T cur[19], dcur, d1 = (T)0;
+  T cur[19], dcur, d1 = (T)0, wait[NW];  // wait: level 0's values of the last plane
   load(cur, dcur);
   int buf = 0;
   for (int z = z0 - 1; z <= z1; ++z) {
@@ -309,9 +334,15 @@ __device__ __forceinline__ void march3d(const Geo& g, const Coll& c, const March
 #pragma unroll
     for (int k = 0; k < 19; ++k) s[k] = cur[k];
     T d0 = dcur;
-    collide(0, z, s, d0, o);
+    collide(0, z, s, d0, o, v0);
     __builtin_amdgcn_sched_barrier(0);
     load(cur, dcur);  // the next plane (past the last: in bounds, unused)
+    double sum[NW];
+    const uint64_t at8 = (uint64_t)g.nx * 8u * ((uint64_t)t.y + (uint64_t)g.ny * (uint64_t)(int64_t)(z - 1));
+    if (ACC && z > z0 && t.own_row) {
+#pragma unroll
+      for (int a = 0; a < NW; ++a) sum[a] = *lane_ptr<const double>(sums[a] + at8, off8);
+    }
     __builtin_amdgcn_sched_barrier(0);
     int n = 0;
 #pragma unroll
@@ -327,17 +358,25 @@ __device__ __forceinline__ void march3d(const Geo& g, const Coll& c, const March
     hand_on3<R, WALLS, T>(g, t, z, lds + buf * (10 * R * 64), s, w, s1);
     buf ^= 1;
     if (z > z0 && t.own_row) {
-      collide(1, z - 1, s1, d1, o);
+      collide(1, z - 1, s1, d1, o, v1);
+      if (ACC && adds) {
+#pragma unroll
+        for (int a = 0; a < NW; ++a)
+          *lane_ptr<double>(sums[a] + at8, off8) = (sum[a] + (double)wait[a]) + (double)v1[a];
+      }
       push3<ENDS, WALLS, true, S, T>(g, t, z - 1, B, offb, s1, o);
     }
     d1 = d0;
+#pragma unroll
+    for (int a = 0; a < NW; ++a) wait[a] = v0[a];
   }
 }
 
-template <typename S, bool HRR, bool SMAG>
-__global__ __launch_bounds__(64 * march3d_rows<typename Prec<S>::T>()) void k_march3d(
-    const Geo g, const MarchColl mc, const March3 m, const S* __restrict__ A, S* __restrict__ B,
-    const typename Prec<S>::Dd* __restrict__ dpor, const Probe pr) {
+template <typename S, bool HRR, bool SMAG, bool ACC>
+__device__ __forceinline__ void march3d_tile(const Geo& g, const MarchColl& mc, const March3& m,
+                                             const S* __restrict__ A, S* __restrict__ B,
+                                             const typename Prec<S>::Dd* __restrict__ dpor, const Probe& pr,
+                                             const Window& wn) {
   using T = typename Prec<S>::T;
   constexpr int R = march3d_rows<T>();
   __shared__ T lds[2 * 10 * R * 64 + 2];
@@ -353,15 +392,31 @@ __global__ __launch_bounds__(64 * march3d_rows<typename Prec<S>::T>()) void k_ma
                      (g.bcz != BC_PERIODIC && (z0 == 0 || z1 == g.nz));
   if (walls) {
     if (ends)
-      march3d<S, HRR, SMAG, true, true>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, lds);
+      march3d<S, HRR, SMAG, true, true, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
     else
-      march3d<S, HRR, SMAG, false, true>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, lds);
+      march3d<S, HRR, SMAG, false, true, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
   } else {
     if (ends)
-      march3d<S, HRR, SMAG, true, false>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, lds);
+      march3d<S, HRR, SMAG, true, false, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
     else
-      march3d<S, HRR, SMAG, false, false>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, lds);
+      march3d<S, HRR, SMAG, false, false, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
   }
+}
+
+template <typename S, bool HRR, bool SMAG>
+__global__ __launch_bounds__(64 * march3d_rows<typename Prec<S>::T>()) void k_march3d(
+    const Geo g, const MarchColl mc, const March3 m, const S* __restrict__ A, S* __restrict__ B,
+    const typename Prec<S>::Dd* __restrict__ dpor, const Probe pr) {
+  const Window wn{};
+  march3d_tile<S, HRR, SMAG, false>(g, mc, m, A, B, dpor, pr, wn);
+}
+
+// The same with the sums of a mean-flow window (BGK).
+template <typename S, bool SMAG>
+__global__ __launch_bounds__(64 * march3d_rows<typename Prec<S>::T>()) void k_window3d(
+    const Geo g, const MarchColl mc, const March3 m, const S* __restrict__ A, S* __restrict__ B,
+    const typename Prec<S>::Dd* __restrict__ dpor, const Probe pr, const Window wn) {
+  march3d_tile<S, false, SMAG, true>(g, mc, m, A, B, dpor, pr, wn);
 }
 
 }  // namespace hlbm

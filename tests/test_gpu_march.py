@@ -110,3 +110,68 @@ def test_primal_passes_equal_single_steps_3d(prec, bc):
             assert np.array_equal(a.probe(), b.probe()), (size, steps)
         a.close()
         b.close()
+
+
+# A small region (its terms through records), a large one (terms in the sweep; single steps in 3D),
+# none.
+def regions(size):
+    nx, ny, nz = size
+    x = min(nx - 2, 60)
+    return [None, ("ffa", (x, 0, 0), (x, max(0, ny // 2 - 1), nz - 1)), ("diss", (1, ny // 5, 0), (nx - 2, ny - 1, nz - 1)),
+            ("diss", (x, ny // 2, nz // 2), (min(nx - 1, x + 3), ny // 2, nz // 2))]
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("dim,bc", [(2, (2, 1, 0)), (2, (2, 0, 0)), (2, (0, 0, 0)), (2, (0, 1, 0)), (3, (2, 0, 0)),
+                                    (3, (2, 1, 0)), (3, (0, 1, 1))])
+def test_window_passes_equal_single_steps(dim, prec, bc):
+    """Sums, objective means, probe and state of window passes, bitwise against single steps; runs
+    whose remainder steps leave pending values, and a plain run before an odd start."""
+    from paper_2606_31707_amd import hlbm as H
+    kinds = {"ffa": H.OBJ_FFA, "diss": H.OBJ_DISS}
+    sizes = [(63, 5, 1), (117, 16, 1), (130, 30, 1), (233, 41, 1)] if dim == 2 else [(63, 15, 4), (130, 29, 9), (20, 7, 12)]
+    for i, size in enumerate(sizes):
+        for j, region in enumerate(regions(size)):
+            cs = (0.0, 0.1)[(i + j) % 2]
+            say("window passes", dim, prec, bc, size, cs, region)
+            a, b = (lattice(H, H.D2Q9 if dim == 2 else H.D3Q19, size, prec, bc, 0, cs) for _ in range(2))
+            for L in (a, b):
+                L.set_probe(min(size[0] - 1, size[0] // 2 + 1), size[1] // 2, size[2] // 2)
+                if region:
+                    L.set_objective(kinds[region[0]], region[1], region[2], u0=0.04)
+            for steps, accumulate in ((9, True), (3, False), (8, True), (2, True)):
+                a.run_primal(steps, accumulate=accumulate)
+                for _ in range(steps):
+                    b.run_primal(1, accumulate=accumulate)
+                assert np.array_equal(a.populations(), b.populations()), (size, region, steps)
+                assert np.array_equal(a.probe(), b.probe()), (size, region, steps)
+            for f in [H.FIELD_MEAN_RHO, H.FIELD_MEAN_U] + ([H.FIELD_MEAN_TAU] if cs > 0 else []):
+                assert np.array_equal(a.field(f), b.field(f)), (size, region, f)
+            if region:
+                assert a.objective(1) == b.objective(1), (size, region)
+                grads = []
+                for L in (a, b):
+                    L.solve_adjoint(H.SOURCE_MEAN, turb=H.TURB_FROZEN, max_iters=4)
+                    grads.append(L.gradient())
+                assert np.array_equal(*grads), (size, region)
+            a.close()
+            b.close()
+
+
+@pytest.mark.parametrize("prec,size,cs", [(1, (4099, 1700, 1), 0.1), (2, (5003, 2500, 1), 0.0)])
+def test_window_passes_with_a_large_region_beyond_the_caches(prec, size, cs):
+    """Four steps a pass with the region's terms in the sweep (lattices larger than the caches)."""
+    from paper_2606_31707_amd import hlbm as H
+    say("large window passes", prec, size, cs)
+    out = []
+    for single in (False, True):
+        L = lattice(H, H.D2Q9, size, prec, (2, 1, 0), 0, cs)
+        L.set_objective(H.OBJ_DISS, (1, size[1] // 5, 0), (size[0] - 2, size[1] - 1, 0), u0=0.04)
+        for _ in range(9 if single else 1):
+            L.run_primal(1 if single else 9, accumulate=True)
+        L.solve_adjoint(H.SOURCE_MEAN, turb=H.TURB_FROZEN, max_iters=2)
+        out.append((L.objective(1), L.field(H.FIELD_MEAN_U), L.field(H.FIELD_U), L.gradient()))
+        L.close()
+    assert out[0][0] == out[1][0]
+    for a, b in zip(out[0][1:], out[1][1:]):
+        assert np.array_equal(a, b)
