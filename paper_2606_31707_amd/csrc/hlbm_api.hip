@@ -1153,8 +1153,104 @@ extern "C" void hlbm_group_destroy(hlbm_group g) {
   delete[] g->members;
   delete[] g->modes;
   delete[] g->counts0;
+  delete[] g->arrays;
   delete g;
 }
+
+namespace {
+// Builds and uploads the packed tables of the members as they are now.
+hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int32_t* modes, int32_t count) {
+  hlbm_status s;
+  const size_t ps = packed_primal_size(), as = packed_adjoint_size();
+  std::vector<unsigned char> tp, ta;
+  std::vector<int> fp, fa;
+  std::vector<hlbm_lattice_s*> lp, la;
+  // two-step passes: if every member of a list takes them and all are at the same parity
+  bool pass_p = true, pass_a = true;
+  for (int i = 0; i < count; ++i) {
+    const bool adj = modes[i] == HLBM_GROUP_ADJOINT;
+    std::vector<hlbm_lattice_s*>& l = adj ? la : lp;
+    const int par = adj ? (int)(lats[i]->adj_iters & 1) : lats[i]->parity;
+    if (l.empty()) (adj ? g->parity_adjoint : g->parity_primal) = par;
+    (adj ? pass_a : pass_p) &=
+        packed_pass_member(lats[i], modes[i]) && par == (adj ? g->parity_adjoint : g->parity_primal);
+    l.push_back(lats[i]);
+  }
+  std::vector<March2> mp(lp.size()), ma(la.size());
+  const int blocks_p = pass_p ? packed_pass_plan(lp.data(), (int)lp.size(), mp.data()) : 0;
+  const int blocks_a = pass_a ? packed_pass_plan(la.data(), (int)la.size(), ma.data()) : 0;
+  int bp = 0, ba = 0, qp = 0, qa = 0;  // first blocks: single steps, passes
+  std::vector<int> gp, ga;
+  for (int i = 0; i < count; ++i) {
+    hlbm_lattice_s* L = lats[i];
+    const int blocks = tiles_x_of(L) * tiles_y_of(L) * L->desc.nz;
+    if (modes[i] == HLBM_GROUP_ADJOINT) {
+      const March2& m = ma[fa.size()];
+      ta.resize(ta.size() + as);
+      fill_packed_adjoint(L, ba, qa, m, ta.data() + ta.size() - as);
+      fa.push_back(ba);
+      ga.push_back(qa);
+      ba += blocks;
+      qa += (m.strips * m.chunks + 3) / 4;
+    } else {
+      const March2& m = mp[fp.size()];
+      tp.resize(tp.size() + ps);
+      fill_packed_primal(L, modes[i] == HLBM_GROUP_PRIMAL_WINDOW, bp, qp, m, tp.data() + tp.size() - ps);
+      fp.push_back(bp);
+      gp.push_back(qp);
+      bp += blocks;
+      qp += (m.strips * m.chunks + 3) / 4;
+    }
+  }
+  const int n_primal = (int)fp.size(), n_adjoint = (int)fa.size();
+  fp.insert(fp.end(), gp.begin(), gp.end());  // the second half: first blocks of a pass
+  fa.insert(fa.end(), ga.begin(), ga.end());
+  auto upload = [&](std::vector<unsigned char>& t, std::vector<int>& f, size_t esz, void** tab, int** first,
+                    size_t* cap) -> hlbm_status {
+    const size_t m = f.size() / 2;
+    if (m == 0) return HLBM_OK;
+    if (m > *cap) {
+      dev_free(*tab);
+      dev_free(*first);
+      *tab = nullptr;
+      *first = nullptr;
+      *cap = 0;
+      hlbm_status st;
+      if ((st = dev_alloc(tab, esz * m)) != HLBM_OK) return st;
+      if ((st = dev_alloc((void**)first, sizeof(int) * 2 * m)) != HLBM_OK) return st;
+      *cap = m;
+    }
+    HIP_TRY(hipMemcpyAsync(*tab, t.data(), esz * m, hipMemcpyHostToDevice, g->stream));
+    HIP_TRY(hipMemcpyAsync(*first, f.data(), sizeof(int) * 2 * m, hipMemcpyHostToDevice, g->stream));
+    return HLBM_OK;
+  };
+  if ((s = upload(tp, fp, ps, &g->tab_primal, &g->first_primal, &g->cap_primal)) != HLBM_OK) return s;
+  if ((s = upload(ta, fa, as, &g->tab_adjoint, &g->first_adjoint, &g->cap_adjoint)) != HLBM_OK) return s;
+  HIP_TRY(hipStreamSynchronize(g->stream));  // host tables go out of scope
+  void** arrays = count ? new void*[2 * count] : nullptr;
+  for (int i = 0; i < count; ++i) {
+    const bool adj = modes[i] == HLBM_GROUP_ADJOINT;
+    arrays[2 * i] = adj ? lats[i]->phi : lats[i]->f;
+    arrays[2 * i + 1] = adj ? lats[i]->phi2 : lats[i]->f2;
+  }
+  delete[] g->arrays;
+  g->arrays = arrays;
+  g->n_primal = n_primal;
+  g->n_adjoint = n_adjoint;
+  g->blocks_primal = bp;
+  g->blocks_adjoint = ba;
+  g->pass_primal = blocks_p;
+  g->pass_adjoint = blocks_a;
+  g->flip_primal = g->flip_adjoint = g->pv_adjoint = 0;
+  g->steps_since_set = 0;
+  return HLBM_OK;
+}
+
+void group_counts(hlbm_group_s* g) {
+  for (int i = 0; i < g->count; ++i)
+    g->counts0[i] = g->modes[i] == HLBM_GROUP_ADJOINT ? g->members[i]->adj_iters : g->members[i]->steps;
+}
+}  // namespace
 
 extern "C" hlbm_status hlbm_group_set(hlbm_group g, const hlbm_lattice* lats, const int32_t* modes, int32_t count) {
   if (!g) return fail(HLBM_E_INVALID, "null group");
@@ -1178,47 +1274,7 @@ extern "C" hlbm_status hlbm_group_set(hlbm_group g, const hlbm_lattice* lats, co
     if (modes[i] == HLBM_GROUP_PRIMAL_WINDOW && (s = ensure_window(lats[i])) != HLBM_OK) return s;
     HIP_TRY(hipStreamSynchronize(lats[i]->stream));
   }
-  const size_t ps = packed_primal_size(), as = packed_adjoint_size();
-  std::vector<unsigned char> tp, ta;
-  std::vector<int> fp, fa;
-  int bp = 0, ba = 0;
-  for (int i = 0; i < count; ++i) {
-    hlbm_lattice_s* L = lats[i];
-    const int blocks = tiles_x_of(L) * tiles_y_of(L) * L->desc.nz;
-    if (modes[i] == HLBM_GROUP_ADJOINT) {
-      ta.resize(ta.size() + as);
-      fill_packed_adjoint(L, ba, ta.data() + ta.size() - as);
-      fa.push_back(ba);
-      ba += blocks;
-    } else {
-      tp.resize(tp.size() + ps);
-      fill_packed_primal(L, modes[i] == HLBM_GROUP_PRIMAL_WINDOW, bp, tp.data() + tp.size() - ps);
-      fp.push_back(bp);
-      bp += blocks;
-    }
-  }
-  auto upload = [&](std::vector<unsigned char>& t, std::vector<int>& f, size_t esz, void** tab, int** first,
-                    size_t* cap) -> hlbm_status {
-    const size_t m = f.size();
-    if (m == 0) return HLBM_OK;
-    if (m > *cap) {
-      dev_free(*tab);
-      dev_free(*first);
-      *tab = nullptr;
-      *first = nullptr;
-      *cap = 0;
-      hlbm_status st;
-      if ((st = dev_alloc(tab, esz * m)) != HLBM_OK) return st;
-      if ((st = dev_alloc((void**)first, sizeof(int) * m)) != HLBM_OK) return st;
-      *cap = m;
-    }
-    HIP_TRY(hipMemcpyAsync(*tab, t.data(), esz * m, hipMemcpyHostToDevice, g->stream));
-    HIP_TRY(hipMemcpyAsync(*first, f.data(), sizeof(int) * m, hipMemcpyHostToDevice, g->stream));
-    return HLBM_OK;
-  };
-  if ((s = upload(tp, fp, ps, &g->tab_primal, &g->first_primal, &g->cap_primal)) != HLBM_OK) return s;
-  if ((s = upload(ta, fa, as, &g->tab_adjoint, &g->first_adjoint, &g->cap_adjoint)) != HLBM_OK) return s;
-  HIP_TRY(hipStreamSynchronize(g->stream));  // host tables go out of scope
+  if ((s = group_tables(g, lats, modes, count)) != HLBM_OK) return s;
   delete[] g->members;
   delete[] g->modes;
   delete[] g->counts0;
@@ -1228,37 +1284,63 @@ extern "C" hlbm_status hlbm_group_set(hlbm_group g, const hlbm_lattice* lats, co
   for (int i = 0; i < count; ++i) {
     g->members[i] = lats[i];
     g->modes[i] = modes[i];
-    g->counts0[i] = modes[i] == HLBM_GROUP_ADJOINT ? lats[i]->adj_iters : lats[i]->steps;
   }
   g->count = count;
-  g->n_primal = (int)fp.size();
-  g->n_adjoint = (int)fa.size();
-  g->blocks_primal = bp;
-  g->blocks_adjoint = ba;
+  group_counts(g);
   g->stencil = count ? lats[0]->desc.stencil : -1;
   g->precision = count ? lats[0]->desc.precision : -1;
   g->collision = count ? lats[0]->desc.collision : 0;
-  g->steps_since_set = 0;
   return HLBM_OK;
 }
 
 namespace {
-// The n packed launches of a step run (each step one primal and/or one
-// adjoint launch; AA parity from the step count since the last set).
-hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n) {
-  for (int64_t k = 0; k < n; ++k) {
-    const int step = (int)((g->steps_since_set + k) & 1);
-    hipError_t e;
-    if (g->n_primal > 0 &&
-        (e = launch_primal_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_primal,
-                                  g->first_primal, g->n_primal, g->blocks_primal, step)) != hipSuccess)
-      return e;
-    if (g->n_adjoint > 0 &&
-        (e = launch_adjoint_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_adjoint,
-                                   g->first_adjoint, g->n_adjoint, g->blocks_adjoint, step)) != hipSuccess)
-      return e;
+// Where a run leaves the two-array state of the lists.
+struct GroupFlips {
+  int primal, adjoint, pv;
+};
+
+// The packed launches of an n-step run: passes of two steps where a list takes
+// them (members at parity 0, two steps left), single steps otherwise (AA parity
+// from the step count since the last set).  dry: only says where it ends.
+hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, GroupFlips* end, bool dry) {
+  GroupFlips at{g->flip_primal, g->flip_adjoint, g->pv_adjoint};
+  hipError_t e = hipSuccess;
+  int64_t kp = g->n_primal > 0 ? 0 : n, ka = g->n_adjoint > 0 ? 0 : n;
+  while ((kp < n || ka < n) && e == hipSuccess) {
+    if (kp <= ka && kp < n) {
+      const int64_t k = g->steps_since_set + kp;
+      if (passes && g->pass_primal > 0 && ((g->parity_primal + k) & 1) == 0 && n - kp >= 2) {
+        if (!dry)
+          e = launch_primal_packed_pass(g->stream, g->precision, g->tab_primal, g->first_primal + g->n_primal,
+                                        g->n_primal, g->pass_primal, at.primal);
+        at.primal ^= 1;
+        kp += 2;
+      } else {
+        if (!dry)
+          e = launch_primal_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_primal,
+                                   g->first_primal, g->n_primal, g->blocks_primal, (int)(k & 1), at.primal);
+        kp += 1;
+      }
+    } else {
+      const int64_t k = g->steps_since_set + ka;
+      if (passes && g->pass_adjoint > 0 && ((g->parity_adjoint + k) & 1) == 0 && n - ka >= 2) {
+        if (!dry)
+          e = launch_adjoint_packed_pass(g->stream, g->precision, g->tab_adjoint, g->first_adjoint + g->n_adjoint,
+                                         g->n_adjoint, g->pass_adjoint, at.adjoint, at.pv);
+        at.adjoint ^= 1;
+        ka += 2;
+      } else {
+        if (!dry)
+          e = launch_adjoint_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_adjoint,
+                                    g->first_adjoint, g->n_adjoint, g->blocks_adjoint, (int)(k & 1), at.adjoint,
+                                    at.pv);
+        ka += 1;
+      }
+      at.pv ^= 1;  // a launch reads and writes the outlet buffers once
+    }
   }
-  return hipSuccess;
+  *end = at;
+  return e;
 }
 
 // Runs of at least this many steps on a group's own stream are launched as
@@ -1270,13 +1352,16 @@ constexpr int64_t kGraphMinSteps = 16;
 // Captures the run into a graph unless the last one had the same launch
 // arguments, then launches it.  Returns false (nothing enqueued) if capture
 // is not possible, so that the caller launches the kernels directly.
-bool launch_group_graph(hlbm_group_s* g, int64_t n) {
-  const uint64_t key[13] = {(uint64_t)g->stencil, (uint64_t)g->precision, (uint64_t)g->collision,
+bool launch_group_graph(hlbm_group_s* g, int64_t n, bool passes) {
+  const uint64_t key[17] = {(uint64_t)g->stencil, (uint64_t)g->precision, (uint64_t)g->collision,
                             (uint64_t)(uintptr_t)g->tab_primal, (uint64_t)(uintptr_t)g->first_primal,
                             (uint64_t)g->n_primal, (uint64_t)g->blocks_primal,
                             (uint64_t)(uintptr_t)g->tab_adjoint, (uint64_t)(uintptr_t)g->first_adjoint,
                             (uint64_t)g->n_adjoint, (uint64_t)g->blocks_adjoint, (uint64_t)n,
-                            (uint64_t)(g->steps_since_set & 1)};
+                            (uint64_t)(g->steps_since_set & 1), (uint64_t)passes, (uint64_t)g->pass_primal,
+                            (uint64_t)g->pass_adjoint,
+                            (uint64_t)(g->parity_primal | g->parity_adjoint << 1 | g->flip_primal << 2 |
+                                       g->flip_adjoint << 3 | g->pv_adjoint << 4)};
   if (!g->gexec || std::memcmp(key, g->gkey, sizeof key) != 0) {
     if (g->gexec) {
       (void)hipGraphExecDestroy(g->gexec);
@@ -1286,7 +1371,8 @@ bool launch_group_graph(hlbm_group_s* g, int64_t n) {
       (void)hipGetLastError();
       return false;
     }
-    const hipError_t e = enqueue_group_steps(g, n);
+    GroupFlips end;
+    const hipError_t e = enqueue_group_steps(g, n, passes, &end, false);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(g->stream, &graph);
     hipGraphExec_t exec = nullptr;
@@ -1316,24 +1402,50 @@ extern "C" hlbm_status hlbm_group_step(hlbm_group g, int64_t n) {
     if (now != g->counts0[i] + g->steps_since_set)
       return fail(HLBM_E_STATE, "member %d was advanced outside the group since hlbm_group_set", i);
   }
+  // Two-step passes need both arrays of every member where the tables have them
+  // (they may have been given back for memory), and the same arrays in every
+  // replay of a caller's capture.
+  bool passes = !stream_capturing(g->stream), moved = false;
+  for (int i = 0; i < g->count; ++i) {
+    const hlbm_lattice_s* L = g->members[i];
+    const bool adj = g->modes[i] == HLBM_GROUP_ADJOINT;
+    const int flip = adj ? g->flip_adjoint : g->flip_primal;
+    moved = moved || (adj ? L->phi : L->f) != g->arrays[2 * i + flip];
+    passes = passes && (adj ? L->phi2 : L->f2) == g->arrays[2 * i + (flip ^ 1)];
+  }
+  if (moved) {  // by runs outside the group whose counts were reset since
+    if (stream_capturing(g->stream)) return fail(HLBM_E_STATE, "a member's arrays moved since hlbm_group_set");
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    hlbm_status s = group_tables(g, g->members, g->modes, g->count);
+    if (s != HLBM_OK) return s;
+    group_counts(g);
+    passes = true;
+  }
+  GroupFlips end;
+  HIP_TRY(enqueue_group_steps(g, n, passes, &end, true));
   bool done = false;
   if (n >= kGraphMinSteps && g->stream != nullptr && g->graph_ok) {
-    done = launch_group_graph(g, n);
+    done = launch_group_graph(g, n, passes);
     if (!done) g->graph_ok = false;  // from now on the plain launches below
   }
-  if (!done) HIP_TRY(enqueue_group_steps(g, n));
+  if (!done) HIP_TRY(enqueue_group_steps(g, n, passes, &end, false));
   for (int i = 0; i < g->count; ++i) {
     hlbm_lattice_s* L = g->members[i];
     if (g->modes[i] == HLBM_GROUP_ADJOINT) {
       L->adj_iters += n;
-      L->pvcur ^= (int)(n & 1);
+      L->pvcur ^= end.pv ^ g->pv_adjoint;
+      if (end.adjoint != g->flip_adjoint) std::swap(L->phi, L->phi2);
     } else {
       L->parity ^= (int)(n & 1);
       L->steps += n;
+      if (end.primal != g->flip_primal) std::swap(L->f, L->f2);
       if (g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW) L->nsamp += n;
       L->adj_ready = 0;
     }
   }
+  g->flip_primal = end.primal;
+  g->flip_adjoint = end.adjoint;
+  g->pv_adjoint = end.pv;
   g->steps_since_set += n;
   return HLBM_OK;
 }

@@ -162,6 +162,11 @@ struct Acc {
 };
 
 
+// Chunking of a D2Q9 multi-step pass.
+struct March2 {
+  int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
+};
+
 Geo make_geo(const hlbm_lattice_s* L);
 ObjBox make_obj(const hlbm_lattice_s* L);
 Coll make_coll(const hlbm_lattice_s* L);
@@ -220,12 +225,23 @@ int tiles_x_of(const hlbm_lattice_s* L);
 int tiles_y_of(const hlbm_lattice_s* L);
 size_t packed_primal_size();
 size_t packed_adjoint_size();
-void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block, void* out);
-void fill_packed_adjoint(const hlbm_lattice_s* L, int first_block, void* out);
+void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block, int first_pass, const March2& m,
+                        void* out);
+void fill_packed_adjoint(const hlbm_lattice_s* L, int first_block, int first_pass, const March2& m, void* out);
+// One step (iteration) of every member.  flip: which of a member's two arrays
+// holds its state; pv: outlet buffer toggles since the table was built.
 hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                const int* first, int nm, int blocks, int step);
+                                const int* first, int nm, int blocks, int step, int flip);
 hipError_t launch_adjoint_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                 const int* first, int nm, int blocks, int step);
+                                 const int* first, int nm, int blocks, int step, int flip, int pv);
+// Two steps (iterations) of every member in one pass: whether a member can take
+// it, the chunks of each member (returns the blocks), the launches.
+bool packed_pass_member(const hlbm_lattice_s* L, int mode);
+int packed_pass_plan(hlbm_lattice_s* const* L, int count, March2* m);
+hipError_t launch_primal_packed_pass(hipStream_t st, int precision, const void* tab, const int* first, int nm,
+                                     int blocks, int flip);
+hipError_t launch_adjoint_packed_pass(hipStream_t st, int precision, const void* tab, const int* first, int nm,
+                                      int blocks, int flip, int pv);
 
 }  // namespace hlbm
 
@@ -241,10 +257,20 @@ struct hlbm_group_s {
   int* first_adjoint = nullptr;
   size_t cap_primal = 0, cap_adjoint = 0;  // members the device tables hold
   int64_t steps_since_set = 0;
+  // Two-step passes of the packed members (blocks of a launch; 0: single steps
+  // only), which go back and forth between two arrays per member: flip is the
+  // one that holds the state (0: as of the set).  parity: the members' common
+  // AA parity at the set; pv_adjoint: outlet buffer toggles since the set (one a
+  // launch).
+  int pass_primal = 0, pass_adjoint = 0;
+  int parity_primal = 0, parity_adjoint = 0;
+  int flip_primal = 0, flip_adjoint = 0;
+  int pv_adjoint = 0;
+  void** arrays = nullptr;  // each member's two arrays at the set
   // the last multi-step run of packed launches, captured as a HIP graph
   // (kernel nodes only) and replayed while the launch arguments repeat
   hipGraphExec_t gexec = nullptr;
-  uint64_t gkey[13] = {};  // launch arguments the graph was captured with
+  uint64_t gkey[17] = {};  // launch arguments the graph was captured with
   bool graph_ok = true;    // false after a failed capture: plain launches
   hlbm_lattice_s** members = nullptr;
   int32_t* modes = nullptr;

@@ -1531,12 +1531,14 @@ struct PackedPrimal {
   Coll c;
   ObjBox ob;
   Acc acc;
-  void* A;
+  void* A[2];      // population array, second array of the two-step passes
   const void* dpor;
   void* ghost;
   int parity0;     // AA parity when the table was built
   int accumulate;  // window accumulation on
-  int first_block, tiles_x, tiles_y, pad_;
+  int first_block, tiles_x, tiles_y;
+  int first_pass;  // first block in a two-step pass
+  March2 march;
 };
 
 __device__ __forceinline__ int packed_member(const int* __restrict__ first, int nm, int b) {
@@ -1547,7 +1549,8 @@ __device__ __forceinline__ int packed_member(const int* __restrict__ first, int 
 
 template <int Q, typename S, bool HRR>
 __global__ __launch_bounds__(256) void k_primal_packed(const PackedPrimal* __restrict__ tab,
-                                                       const int* __restrict__ first, int nm, int step) {
+                                                       const int* __restrict__ first, int nm, int step,
+                                                       int flip) {
   using Dd = typename Prec<S>::Dd;
   const int b = sweep_tile((int)blockIdx.x, (int)gridDim.x);
   const PackedPrimal& P = tab[packed_member(first, nm, b)];
@@ -1558,7 +1561,7 @@ __global__ __launch_bounds__(256) void k_primal_packed(const PackedPrimal* __res
   if (x >= P.g.nx || y >= P.g.ny) return;
   const int64_t c0 = wave_uniform64(cell_of(P.g, tx * BX, ty * BY, z));
   const uint32_t lo = lane_offset(threadIdx.x + (uint32_t)P.g.nx * threadIdx.y);
-  S* A = (S*)P.A;
+  S* A = (S*)P.A[flip];
   const Dd* dp = (const Dd*)P.dpor;
   S* gh = (S*)P.ghost;
   const int mode = P.accumulate ? (P.ob.kind == OBJ_MEA ? 2 : 1) : 0;
@@ -2618,19 +2621,22 @@ struct PackedAdjoint {
   Geo g;
   ObjBox ob;
   AdjC ac;
-  void* A;
+  void* A[2];  // phi, second array of the two-iteration passes
   const void* prep;
   const double* src;
   const double* oprep;
   void* pv[2];
   int iter0;   // adjoint iterations done when the table was built
   int pvcur0;  // outlet buffer holding the latest values at that time
-  int first_block, tiles_x, tiles_y, pad_;
+  int first_block, tiles_x, tiles_y;
+  int first_pass;  // first block in a two-iteration pass
+  March2 march;
 };
 
 template <int Q, typename SA, bool HRR>
 __global__ __launch_bounds__(256) void k_adjoint_packed(const PackedAdjoint* __restrict__ tab,
-                                                        const int* __restrict__ first, int nm, int step) {
+                                                        const int* __restrict__ first, int nm, int step,
+                                                        int flip, int pv) {
   const int b = sweep_tile((int)blockIdx.x, (int)gridDim.x);
   const PackedAdjoint& P = tab[packed_member(first, nm, b)];
   const int lb = b - P.first_block;
@@ -2640,10 +2646,10 @@ __global__ __launch_bounds__(256) void k_adjoint_packed(const PackedAdjoint* __r
   if (x >= P.g.nx || y >= P.g.ny) return;
   const int64_t c0 = wave_uniform64(cell_of(P.g, tx * BX, ty * BY, z));
   const uint32_t lo = lane_offset(threadIdx.x + (uint32_t)P.g.nx * threadIdx.y);
-  const int cur = (P.pvcur0 + step) & 1;
+  const int cur = (P.pvcur0 + pv) & 1;
   const SA* pin = (const SA*)P.pv[cur];
   SA* pout = (SA*)P.pv[cur ^ 1];
-  SA* A = (SA*)P.A;
+  SA* A = (SA*)P.A[flip];
   const SA* pr = (const SA*)P.prep;
   const bool odd = ((P.iter0 + step) & 1) != 0;
   if (P.ob.kind == OBJ_MEA) {

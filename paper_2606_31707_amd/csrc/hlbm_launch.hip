@@ -555,7 +555,8 @@ namespace hlbm {
 int tiles_x_of(const hlbm_lattice_s* L) { return (L->desc.nx + BX - 1) / BX; }
 int tiles_y_of(const hlbm_lattice_s* L) { return (L->desc.ny + BY - 1) / BY; }
 
-void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block, void* out) {
+void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block, int first_pass, const March2& m,
+                        void* out) {
   PackedPrimal* P = (PackedPrimal*)out;
   P->g = make_geo(L);
   P->c = make_coll(L);
@@ -565,7 +566,8 @@ void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block
   const bool smag = L->desc.smagorinsky_cs > 0.0;
   P->acc = Acc{L->acc_rho, L->acc_j, L->desc.track_mean_populations ? L->acc_f : nullptr,
                smag ? L->acc_tau : nullptr, L->acc_obj};
-  P->A = L->f;
+  P->A[0] = L->f;
+  P->A[1] = L->f2;
   P->dpor = L->dpor;
   P->ghost = L->ghost;
   P->parity0 = L->parity;
@@ -573,17 +575,19 @@ void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block
   P->first_block = first_block;
   P->tiles_x = tiles_x_of(L);
   P->tiles_y = tiles_y_of(L);
-  P->pad_ = 0;
+  P->first_pass = first_pass;
+  P->march = m;
 }
 
-void fill_packed_adjoint(const hlbm_lattice_s* L, int first_block, void* out) {
+void fill_packed_adjoint(const hlbm_lattice_s* L, int first_block, int first_pass, const March2& m, void* out) {
   PackedAdjoint* P = (PackedAdjoint*)out;
   P->g = make_geo(L);
   P->ob = make_obj(L);
   P->ac.les = L->adj_les;
   P->ac.diff = L->adj_diff;
   P->ac.omega0 = L->adj_omega;
-  P->A = L->phi;
+  P->A[0] = L->phi;
+  P->A[1] = L->phi2;
   P->prep = L->prep;
   P->src = L->src;
   P->oprep = L->oprep;
@@ -594,7 +598,8 @@ void fill_packed_adjoint(const hlbm_lattice_s* L, int first_block, void* out) {
   P->first_block = first_block;
   P->tiles_x = tiles_x_of(L);
   P->tiles_y = tiles_y_of(L);
-  P->pad_ = 0;
+  P->first_pass = first_pass;
+  P->march = m;
 }
 
 size_t packed_primal_size() { return sizeof(PackedPrimal); }
@@ -602,25 +607,25 @@ size_t packed_adjoint_size() { return sizeof(PackedAdjoint); }
 
 template <int Q, typename S>
 static void primal_packed(hipStream_t st, bool hrr, const PackedPrimal* t, const int* first, int nm, int blocks,
-                          int step) {
+                          int step, int flip) {
   const dim3 grid((unsigned)blocks);
   if (hrr)
-    k_primal_packed<Q, S, true><<<grid, kBlock, 0, st>>>(t, first, nm, step);
+    k_primal_packed<Q, S, true><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip);
   else
-    k_primal_packed<Q, S, false><<<grid, kBlock, 0, st>>>(t, first, nm, step);
+    k_primal_packed<Q, S, false><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip);
 }
 
 hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                const int* first, int nm, int blocks, int step) {
+                                const int* first, int nm, int blocks, int step, int flip) {
   const PackedPrimal* t = (const PackedPrimal*)tab;
   const bool hrr = collision == HLBM_COLL_HRR;
   switch (stencil * 3 + precision) {
-    case 0: primal_packed<9, double>(st, hrr, t, first, nm, blocks, step); break;
-    case 1: primal_packed<9, float>(st, hrr, t, first, nm, blocks, step); break;
-    case 2: primal_packed<9, _Float16>(st, hrr, t, first, nm, blocks, step); break;
-    case 3: primal_packed<19, double>(st, hrr, t, first, nm, blocks, step); break;
-    case 4: primal_packed<19, float>(st, hrr, t, first, nm, blocks, step); break;
-    case 5: primal_packed<19, _Float16>(st, hrr, t, first, nm, blocks, step); break;
+    case 0: primal_packed<9, double>(st, hrr, t, first, nm, blocks, step, flip); break;
+    case 1: primal_packed<9, float>(st, hrr, t, first, nm, blocks, step, flip); break;
+    case 2: primal_packed<9, _Float16>(st, hrr, t, first, nm, blocks, step, flip); break;
+    case 3: primal_packed<19, double>(st, hrr, t, first, nm, blocks, step, flip); break;
+    case 4: primal_packed<19, float>(st, hrr, t, first, nm, blocks, step, flip); break;
+    case 5: primal_packed<19, _Float16>(st, hrr, t, first, nm, blocks, step, flip); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -628,28 +633,28 @@ hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int 
 
 template <int Q, typename SA>
 static void adjoint_packed(hipStream_t st, bool hrr, const PackedAdjoint* t, const int* first, int nm, int blocks,
-                           int step) {
+                           int step, int flip, int pv) {
   const dim3 grid((unsigned)blocks);
   if (hrr)
-    k_adjoint_packed<Q, SA, true><<<grid, kBlock, 0, st>>>(t, first, nm, step);
+    k_adjoint_packed<Q, SA, true><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip, pv);
   else
-    k_adjoint_packed<Q, SA, false><<<grid, kBlock, 0, st>>>(t, first, nm, step);
+    k_adjoint_packed<Q, SA, false><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip, pv);
 }
 
 hipError_t launch_adjoint_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                 const int* first, int nm, int blocks, int step) {
+                                 const int* first, int nm, int blocks, int step, int flip, int pv) {
   const PackedAdjoint* t = (const PackedAdjoint*)tab;
   const bool f64 = precision == HLBM_FP64, hrr = collision == HLBM_COLL_HRR;
   if (stencil == HLBM_D2Q9) {
     if (f64)
-      adjoint_packed<9, double>(st, hrr, t, first, nm, blocks, step);
+      adjoint_packed<9, double>(st, hrr, t, first, nm, blocks, step, flip, pv);
     else
-      adjoint_packed<9, float>(st, hrr, t, first, nm, blocks, step);
+      adjoint_packed<9, float>(st, hrr, t, first, nm, blocks, step, flip, pv);
   } else {
     if (f64)
-      adjoint_packed<19, double>(st, hrr, t, first, nm, blocks, step);
+      adjoint_packed<19, double>(st, hrr, t, first, nm, blocks, step, flip, pv);
     else
-      adjoint_packed<19, float>(st, hrr, t, first, nm, blocks, step);
+      adjoint_packed<19, float>(st, hrr, t, first, nm, blocks, step, flip, pv);
   }
   return hipGetLastError();
 }

@@ -35,10 +35,9 @@
 namespace hlbm {
 
 // Strips and row chunks of a pass (host: march2d_plan).
-struct March2 {
-  int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
-};
 March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64);
+// Rows per chunk for lattices of the given strips and rows advanced together.
+int march2d_rows(const int* strips, const int* ny, int count, int K, bool f64, int most);
 hipError_t launch_window2d(hlbm_lattice_s* L, int K);  // K D2Q9 window steps (hlbm_window2d.hip)
 hipError_t launch_march3d(hlbm_lattice_s* L, bool window);  // two D3Q19 steps (hlbm_march3d.hip)
 
@@ -314,8 +313,9 @@ struct MarchColl {
 // computed from whatever is there and reach no row that is stored.
 // EDGE: 0 none, 1 the strip holds an inlet or outlet column, 2 the rows come
 // near a wall, the probe or a small objective region (with or without an end).
-// ACC: 0 plain, 1 window sums, 2 window sums and the terms of a large region.
-template <typename S, int K, bool HRR, bool SMAG, int EDGE, int ACC>
+// ACC: 0 plain, 1 window sums, 2 window sums and the terms of a large region,
+// 3 either of the last or plain (no sums: wn.rho null).  SMAG: 2 by c.smag.
+template <typename S, int K, bool HRR, int SMAG, int EDGE, int ACC>
 __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip& st, const int y0, const int y1,
                                         const S* __restrict__ A, S* __restrict__ B,
                                         const typename Prec<S>::Dd* __restrict__ dpor, const Probe& pr,
@@ -325,7 +325,7 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
   using Dd = typename Prec<S>::Dd;
   constexpr int NB = K > 1 ? K - 1 : 1;
   // window sums: drho, j, tau_eff; ACC 2: and the objective terms of the region's cells
-  constexpr int NO = Coef<9>::N, NW = SMAG ? 4 : 3, NT = ACC == 2 ? NW + NO : NW;
+  constexpr int NO = Coef<9>::N, NW = SMAG ? 4 : 3, NT = ACC >= 2 ? NW + NO : NW;
   const bool walls = g.bcy != BC_PERIODIC;
   const int none = -0x40000000;
   const int row_first = walls ? 0 : none, row_last = walls ? g.ny - 1 : none;
@@ -369,8 +369,9 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
   RowPtr pw(nullptr, r0, g.nx, g.ny, 8);
   uint64_t out_row = uni64((uint64_t)g.nx * 8u * (uint64_t)(int64_t)y0);
   const uint64_t sums[4] = {uni64((uint64_t)wn.rho), uni64((uint64_t)wn.j), uni64((uint64_t)wn.j + (uint64_t)g.plane * 8),
-                            uni64((uint64_t)wn.tau)};
-  const bool adds = ACC && st.own && !st.inlet;
+                            uni64((uint64_t)(SMAG == 2 && !wn.tau ? wn.rho : wn.tau))};
+  const bool sums_on = ACC && (ACC != 3 || wn.rho != nullptr), tau_on = SMAG != 2 || wn.tau != nullptr;
+  const bool adds = sums_on && st.own && !st.inlet;
   const int rx = st.gx - wn.ob.lo[0];
   const bool in_cols = ACC && wn.ob.active && adds && rx >= 0 && rx < wn.ob.rn[0];
   // region rows of this chunk (empty where the strip has no region column)
@@ -379,18 +380,18 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
   const int reg1 = any_col ? (wn.ob.lo[1] + wn.ob.rn[1] < y1 ? wn.ob.lo[1] + wn.ob.rn[1] : y1) : 0;
   // the terms' slots: lanes outside the region's columns read its nearest one and write nothing
   const uint32_t offr =
-      lane_offset(8u * (uint32_t)(ACC == 2 ? (rx < 0 ? 0 : (rx < wn.ob.rn[0] ? rx : wn.ob.rn[0] - 1)) : 0));
+      lane_offset(8u * (uint32_t)(ACC >= 2 ? (rx < 0 ? 0 : (rx < wn.ob.rn[0] ? rx : wn.ob.rn[0] - 1)) : 0));
   auto term_slot = [&](const int row, const int m) {
     return lane_ptr<double>(uni64((uint64_t)(wn.obj + m * wn.ob.rplane +
                                              (int64_t)wn.ob.rn[0] * (int64_t)(row - wn.ob.lo[1]))), offr);
   };
   double wcur[NT], hold[NB][NT];
   auto load_sums = [&](const int row) {
-    if (ACC && row >= y0 && row < y1) {
+    if (sums_on && row >= y0 && row < y1) {
 #pragma unroll
       for (int a = 0; a < NW; ++a) wcur[a] = *lane_ptr<const double>(sums[a] + pw.base, off8);
     }
-    if (ACC == 2 && row >= reg0 && row < reg1) {
+    if (ACC >= 2 && row >= reg0 && row < reg1) {
 #pragma unroll
       for (int m = 0; m < NO; ++m) wcur[NT - NO + m] = *term_slot(row, m);
     }
@@ -424,13 +425,13 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
       const T rho = (T)1 + drho;
       const T ir = recip(rho);
       if (EDGE == 2 && probe_lane && row == pr.y) *pr.out[t] = (double)(jy * ir);
-      relaxation<9, T, HRR>(c, SMAG, s, drho, jx, jy, jz, ir, omega, taue, p2);
+      relaxation<9, T, HRR>(c, SMAG == 2 ? c.smag != 0 : SMAG == 1, s, drho, jx, jy, jz, ir, omega, taue, p2);
       if (ACC) {
         sum[0] = sum[0] + (double)drho;
         sum[1] = sum[1] + (double)jx;
         sum[2] = sum[2] + (double)jy;
         if (SMAG) sum[NW - 1] = sum[NW - 1] + (double)taue;
-        if (ACC == 2 && row >= reg0 && row < reg1) {
+        if (ACC >= 2 && row >= reg0 && row < reg1) {
           double sd[9], terms[NO], dr, ax, ay, az, P[6];
 #pragma unroll
           for (int k = 0; k < 9; ++k) sd[k] = (double)s[k];
@@ -447,7 +448,8 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
         if (t == K - 1) {
           if (adds) {
 #pragma unroll
-            for (int a = 0; a < NW; ++a) *lane_ptr<double>(sums[a] + out_row, off8) = sum[a];
+            for (int a = 0; a < NW; ++a)
+              if (a < 3 || tau_on) *lane_ptr<double>(sums[a] + out_row, off8) = sum[a];
           }
           out_row += (uint64_t)g.nx * 8u;
         } else {  // to the next level, one row later

@@ -175,3 +175,87 @@ def test_window_passes_with_a_large_region_beyond_the_caches(prec, size, cs):
     assert out[0][0] == out[1][0]
     for a, b in zip(out[0][1:], out[1][1:]):
         assert np.array_equal(a, b)
+
+
+def _members(H, prec, stream=None):
+    """Plain, window (small region, large region, none) and adjoint members of different sizes and ends."""
+    out = []
+    specs = [((96, 48), (2, 1, 0), 0.0, "ffa", 0), ((61, 17), (2, 0, 0), 0.1, "diss", 1), ((130, 33), (2, 1, 0), 0.1, "ffa", 1),
+             ((70, 9), (0, 1, 0), 0.0, None, 1), ((117, 40), (2, 1, 0), 0.0, "diss", 2), ((20, 30), (2, 0, 0), 0.1, "ffa", 2)]
+    for i, ((nx, ny), bc, cs, obj, mode) in enumerate(specs):
+        L = lattice(H, H.D2Q9, (nx, ny, 1), prec, bc, 0, cs, seed=i, **({} if stream is None else {"stream": stream}))
+        if obj:
+            lo, hi = REGIONS_2D[obj](nx, ny)
+            L.set_objective(H.OBJ_FFA if obj == "ffa" else H.OBJ_DISS, lo, hi, u0=0.04)
+        L.run_primal(2)
+        if mode == 2:
+            L.solve_adjoint(H.SOURCE_STEADY, turb=H.TURB_FROZEN, max_iters=0)
+        out.append((L, mode))
+    return out
+
+
+def _same(H, a, b, where):
+    for i, ((A, mode), (B, _)) in enumerate(zip(a, b)):
+        assert np.array_equal(A.populations(), B.populations()), (where, i)
+        if mode == 1:
+            for f in (H.FIELD_MEAN_RHO, H.FIELD_MEAN_U):
+                assert np.array_equal(A.field(f), B.field(f)), (where, i)
+            if i != 3:
+                assert A.objective(1) == B.objective(1), (where, i)
+        if mode == 2:
+            assert np.array_equal(A.gradient(), B.gradient()), (where, i)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_packed_passes_equal_packed_single_steps(prec, own_stream):
+    """Runs with odd and even remainders, replayed graphs, members that a run outside the group
+    left in their other array, and primal members at different parities (single steps)."""
+    import torch
+    from paper_2606_31707_amd import hlbm as H
+    stream = torch.cuda.Stream() if own_stream else None
+    h = stream.cuda_stream if own_stream else None
+    say("packed passes", prec, own_stream)
+    a, b = _members(H, prec, h), _members(H, prec, h)
+    ga, gb = (H.Group(h) if own_stream else H.Group() for _ in range(2))
+    for g, m in ((ga, a), (gb, b)):
+        g.set([L for L, _ in m], [mode for _, mode in m])
+    for n in (2, 7, 20, 20, 18, 3, 20, 20):
+        ga.step(n)
+        for _ in range(n):
+            gb.step(1)
+        ga.synchronize()
+        gb.synchronize()
+        _same(H, a, b, n)
+    # a run outside the group ends in the other array; the reset brings the step count back
+    for m in (a, b):
+        L = m[0][0]
+        u = np.zeros((3, L.n))
+        L.run_primal(2)
+        L.init_equilibrium(1.0, u)
+    for g, m in ((ga, a), (gb, b)):
+        g.set([L for L, mode in m if mode < 2], [mode for _, mode in m if mode < 2])
+    for m in (a, b):
+        L = m[0][0]
+        L.run_primal(2)
+        L.init_equilibrium(1.01, u)
+    ga.step(6)
+    for _ in range(6):
+        gb.step(1)
+    ga.synchronize()
+    gb.synchronize()
+    _same(H, a[:4], b[:4], "moved")
+    # members at different parities
+    for m in (a, b):
+        m[1][0].run_primal(1)
+    for g, m in ((ga, a), (gb, b)):
+        g.set([L for L, mode in m if mode < 2], [mode for _, mode in m if mode < 2])
+    ga.step(5)
+    for _ in range(5):
+        gb.step(1)
+    ga.synchronize()
+    gb.synchronize()
+    _same(H, a[:4], b[:4], "parity")
+    for m in (a, b):
+        for L, _ in m:
+            L.close()
