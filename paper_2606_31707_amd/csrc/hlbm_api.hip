@@ -1176,16 +1176,17 @@ hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int
         packed_pass_member(lats[i], modes[i]) && par == (adj ? g->parity_adjoint : g->parity_primal);
     l.push_back(lats[i]);
   }
-  std::vector<March2> mp(lp.size()), ma(la.size());
-  const int blocks_p = pass_p ? packed_pass_plan(lp.data(), (int)lp.size(), mp.data()) : 0;
-  const int blocks_a = pass_a ? packed_pass_plan(la.data(), (int)la.size(), ma.data()) : 0;
+  std::vector<hlbm_lattice_s*> both(lp);
+  both.insert(both.end(), la.begin(), la.end());
+  std::vector<March2> plan(both.size());
+  packed_pass_plan(both.data(), (int)both.size(), plan.data());
   int bp = 0, ba = 0, qp = 0, qa = 0;  // first blocks: single steps, passes
   std::vector<int> gp, ga;
   for (int i = 0; i < count; ++i) {
     hlbm_lattice_s* L = lats[i];
     const int blocks = tiles_x_of(L) * tiles_y_of(L) * L->desc.nz;
     if (modes[i] == HLBM_GROUP_ADJOINT) {
-      const March2& m = ma[fa.size()];
+      const March2& m = plan[lp.size() + fa.size()];
       ta.resize(ta.size() + as);
       fill_packed_adjoint(L, ba, qa, m, ta.data() + ta.size() - as);
       fa.push_back(ba);
@@ -1193,7 +1194,7 @@ hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int
       ba += blocks;
       qa += (m.strips * m.chunks + 3) / 4;
     } else {
-      const March2& m = mp[fp.size()];
+      const March2& m = plan[fp.size()];
       tp.resize(tp.size() + ps);
       fill_packed_primal(L, modes[i] == HLBM_GROUP_PRIMAL_WINDOW, bp, qp, m, tp.data() + tp.size() - ps);
       fp.push_back(bp);
@@ -1239,8 +1240,8 @@ hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int
   g->n_adjoint = n_adjoint;
   g->blocks_primal = bp;
   g->blocks_adjoint = ba;
-  g->pass_primal = blocks_p;
-  g->pass_adjoint = blocks_a;
+  g->pass_primal = pass_p ? qp : 0;
+  g->pass_adjoint = pass_a ? qa : 0;
   g->flip_primal = g->flip_adjoint = g->pv_adjoint = 0;
   g->steps_since_set = 0;
   return HLBM_OK;
@@ -1307,37 +1308,29 @@ hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, GroupFli
   hipError_t e = hipSuccess;
   int64_t kp = g->n_primal > 0 ? 0 : n, ka = g->n_adjoint > 0 ? 0 : n;
   while ((kp < n || ka < n) && e == hipSuccess) {
-    if (kp <= ka && kp < n) {
-      const int64_t k = g->steps_since_set + kp;
-      if (passes && g->pass_primal > 0 && ((g->parity_primal + k) & 1) == 0 && n - kp >= 2) {
-        if (!dry)
-          e = launch_primal_packed_pass(g->stream, g->precision, g->tab_primal, g->first_primal + g->n_primal,
-                                        g->n_primal, g->pass_primal, at.primal);
-        at.primal ^= 1;
-        kp += 2;
-      } else {
-        if (!dry)
-          e = launch_primal_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_primal,
-                                   g->first_primal, g->n_primal, g->blocks_primal, (int)(k & 1), at.primal);
-        kp += 1;
-      }
-    } else {
-      const int64_t k = g->steps_since_set + ka;
-      if (passes && g->pass_adjoint > 0 && ((g->parity_adjoint + k) & 1) == 0 && n - ka >= 2) {
-        if (!dry)
-          e = launch_adjoint_packed_pass(g->stream, g->precision, g->tab_adjoint, g->first_adjoint + g->n_adjoint,
-                                         g->n_adjoint, g->pass_adjoint, at.adjoint, at.pv);
-        at.adjoint ^= 1;
-        ka += 2;
-      } else {
-        if (!dry)
-          e = launch_adjoint_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_adjoint,
-                                    g->first_adjoint, g->n_adjoint, g->blocks_adjoint, (int)(k & 1), at.adjoint,
-                                    at.pv);
-        ka += 1;
-      }
-      at.pv ^= 1;  // a launch reads and writes the outlet buffers once
+    const int64_t sp = g->steps_since_set + kp, sa = g->steps_since_set + ka;
+    // the list that is behind goes first; both in one launch where both take a pass
+    const bool do_p = kp < n && kp <= ka, do_a = ka < n && ka <= kp;
+    const bool two_p = do_p && passes && g->pass_primal > 0 && ((g->parity_primal + sp) & 1) == 0 && n - kp >= 2;
+    const bool two_a = do_a && passes && g->pass_adjoint > 0 && ((g->parity_adjoint + sa) & 1) == 0 && n - ka >= 2;
+    if (!dry && (two_p || two_a)) {
+      const PackedPasses p{
+          {g->tab_primal, g->first_primal + g->n_primal, g->n_primal, two_p ? g->pass_primal : 0, at.primal},
+          {g->tab_adjoint, g->first_adjoint + g->n_adjoint, g->n_adjoint, two_a ? g->pass_adjoint : 0, at.adjoint},
+          at.pv};
+      e = launch_packed_pass(g->stream, g->precision, p);
     }
+    if (!dry && do_p && !two_p && e == hipSuccess)
+      e = launch_primal_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_primal, g->first_primal,
+                               g->n_primal, g->blocks_primal, (int)(sp & 1), at.primal);
+    if (!dry && do_a && !two_a && e == hipSuccess)
+      e = launch_adjoint_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_adjoint,
+                                g->first_adjoint, g->n_adjoint, g->blocks_adjoint, (int)(sa & 1), at.adjoint, at.pv);
+    at.primal ^= two_p;
+    at.adjoint ^= two_a;
+    at.pv ^= do_a;  // a launch reads and writes the outlet buffers once
+    kp += do_p ? (two_p ? 2 : 1) : 0;
+    ka += do_a ? (two_a ? 2 : 1) : 0;
   }
   *end = at;
   return e;

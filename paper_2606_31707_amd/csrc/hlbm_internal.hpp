@@ -235,13 +235,19 @@ hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int 
 hipError_t launch_adjoint_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
                                  const int* first, int nm, int blocks, int step, int flip, int pv);
 // Two steps (iterations) of every member in one pass: whether a member can take
-// it, the chunks of each member (returns the blocks), the launches.
+// it, the chunks of each member, the launch.
 bool packed_pass_member(const hlbm_lattice_s* L, int mode);
-int packed_pass_plan(hlbm_lattice_s* const* L, int count, March2* m);
-hipError_t launch_primal_packed_pass(hipStream_t st, int precision, const void* tab, const int* first, int nm,
-                                     int blocks, int flip);
-hipError_t launch_adjoint_packed_pass(hipStream_t st, int precision, const void* tab, const int* first, int nm,
-                                      int blocks, int flip, int pv);
+void packed_pass_plan(hlbm_lattice_s* const* L, int count, March2* m);
+struct PackedList {
+  const void* tab;
+  const int* first;
+  int nm, blocks, flip;
+};
+struct PackedPasses {
+  PackedList primal, adjoint;  // blocks 0: none
+  int pv;
+};
+hipError_t launch_packed_pass(hipStream_t st, int precision, const PackedPasses& p);
 
 }  // namespace hlbm
 

@@ -14,29 +14,22 @@ namespace hlbm {
 // caches, where neighbouring chunks share their halo rows in L2
 // (8192 x 4096 FP32: 8 rows 167 us, 16 rows 169, 58 rows 184; FP16S, whose
 // rows are half as long, 150, 117 and 110).
-int march2d_rows(const int* strips, const int* ny, int count, int K, bool f64, int most) {
-  int best_rows = 1, ny_max = 1;
+March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64) {
+  const int W = 64 - 2 * (K - 1), ny = L->desc.ny;
+  March2 m;
+  m.strips = (L->desc.nx + W - 1) / W;
+  const int most = L->desc.precision == HLBM_FP16S ? 24 : 12;
   double best = 0.0;
-  for (int i = 0; i < count; ++i) ny_max = ny[i] > ny_max ? ny[i] : ny_max;
-  for (int rows = 1; rows <= most && rows <= ny_max; ++rows) {
-    int64_t groups = 0;
-    for (int i = 0; i < count; ++i) groups += ((int64_t)strips[i] * ((ny[i] + rows - 1) / rows) + 3) / 4;
+  for (int rows = 1; rows <= most && rows <= ny; ++rows) {
+    const int64_t groups = ((int64_t)m.strips * ((ny + rows - 1) / rows) + 3) / 4;
     const double per_cu = groups <= 1024 ? (double)((groups + 255) / 256) : groups / 256.0;
     const double share = f64 ? 0.55 + 0.47 * per_cu : (per_cu <= 2.0 ? 1.0 : 0.1 + 0.42 * per_cu);
     const double cost = (rows + 2 * (K - 1)) * share;
     if (rows == 1 || cost < best) {
       best = cost;
-      best_rows = rows;
+      m.rows = rows;
     }
   }
-  return best_rows;
-}
-
-March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64) {
-  const int W = 64 - 2 * (K - 1), ny = L->desc.ny;
-  March2 m;
-  m.strips = (L->desc.nx + W - 1) / W;
-  m.rows = march2d_rows(&m.strips, &ny, 1, K, f64, L->desc.precision == HLBM_FP16S ? 24 : 12);
   m.chunks = (ny + m.rows - 1) / m.rows;
   return m;
 }

@@ -36,8 +36,6 @@ namespace hlbm {
 
 // Strips and row chunks of a pass (host: march2d_plan).
 March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64);
-// Rows per chunk for lattices of the given strips and rows advanced together.
-int march2d_rows(const int* strips, const int* ny, int count, int K, bool f64, int most);
 hipError_t launch_window2d(hlbm_lattice_s* L, int K);  // K D2Q9 window steps (hlbm_window2d.hip)
 hipError_t launch_march3d(hlbm_lattice_s* L, bool window);  // two D3Q19 steps (hlbm_march3d.hip)
 

@@ -1,15 +1,14 @@
 // hlbm_packed2d.hip -- packed launches that take two steps (or adjoint iterations)
 // of every member in one pass over memory (D2Q9, BGK).
 //
-// A tick of small lattices is bound by latency: every launch waits for its
-// slowest wavefront's chain of loads, collisions and stores.  One pass does
-// two steps with one such chain, of the rows of a chunk; the rows are chosen
-// for the wavefronts of all members together.  One kernel body serves plain
-// and window members (closure, sums and objective terms by runtime flags): the
-// strips that hold an inlet, an outlet or walls take longest in lattices of a
-// few strips, so that faster bodies for the others would save nothing.
-#include <cmath>
-#include <vector>
+// A tick of small lattices is bound by the instructions of its slowest wavefronts
+// (one to three a SIMD; loads two rows ahead changed nothing).  A pass takes two
+// steps with one read and one write, and one launch holds the primal and the
+// adjoint members.  One body serves all window members (closure, sums and
+// objective terms by runtime flags), one the plain ones: bodies for strips
+// without ends or walls as well outgrow the instruction cache and the registers
+// (19.7 us a step instead of 16.5).  12 members of 128 x 64 to 512 x 256, FP32: single
+// steps 27.1 us a step, passes 15.8.
 
 #include "hlbm_march2d.hpp"
 
@@ -17,10 +16,8 @@ namespace hlbm {
 
 namespace {
 template <typename S>
-__global__ __launch_bounds__(256, 2) void k_primal_packed2d(const PackedPrimal* __restrict__ tab,
-                                                            const int* __restrict__ first, int nm, int flip) {
-  const int b = (int)blockIdx.x;
-  const PackedPrimal& P = tab[packed_member(first, nm, b)];
+__device__ __forceinline__ void packed_primal(const PackedPasses& p, const int b) {
+  const PackedPrimal& P = ((const PackedPrimal*)p.primal.tab)[packed_member(p.primal.first, p.primal.nm, b)];
   const int id = (b - P.first_pass) * 4 + wave_uniform((int)(threadIdx.x >> 6));
   const March2 m = P.march;
   if (id >= m.strips * m.chunks) return;
@@ -38,16 +35,19 @@ __global__ __launch_bounds__(256, 2) void k_primal_packed2d(const PackedPrimal* 
     wn.obj = P.acc.obj;
   }
   const Probe pr{{nullptr, nullptr, nullptr, nullptr}, 0, 0, 0};
-  march2d<S, 2, false, 2, 2, 3>(g, c, st, y0, y1, (const S*)P.A[flip], (S*)P.A[flip ^ 1],
-                                (const typename Prec<S>::Dd*)P.dpor, pr, wn);
+  const int flip = p.primal.flip;
+  const S* A = (const S*)P.A[flip];
+  S* B = (S*)P.A[flip ^ 1];
+  const auto* dp = (const typename Prec<S>::Dd*)P.dpor;
+  if (P.accumulate)
+    march2d<S, 2, false, 2, 2, 3>(g, c, st, y0, y1, A, B, dp, pr, wn);
+  else
+    march2d<S, 2, false, 2, 2, 0>(g, c, st, y0, y1, A, B, dp, pr, wn);
 }
 
 template <typename T>
-__global__ __launch_bounds__(256, 2) void k_adjoint_packed2d(const PackedAdjoint* __restrict__ tab,
-                                                             const int* __restrict__ first, int nm, int flip,
-                                                             int pv) {
-  const int b = (int)blockIdx.x;
-  const PackedAdjoint& P = tab[packed_member(first, nm, b)];
+__device__ __forceinline__ void packed_adjoint(const PackedPasses& p, const int b) {
+  const PackedAdjoint& P = ((const PackedAdjoint*)p.adjoint.tab)[packed_member(p.adjoint.first, p.adjoint.nm, b)];
   const int id = (b - P.first_pass) * 4 + wave_uniform((int)(threadIdx.x >> 6));
   const March2 m = P.march;
   if (id >= m.strips * m.chunks) return;
@@ -56,9 +56,18 @@ __global__ __launch_bounds__(256, 2) void k_adjoint_packed2d(const PackedAdjoint
   const Strip st = make_strip<2>(g, id - chunk * m.strips);
   const int y0 = chunk * m.rows, y1 = y0 + m.rows < g.ny ? y0 + m.rows : g.ny;
   const MarchAdj ac{P.ac.les, P.ac.omega0};
-  const int cur = (P.pvcur0 + pv) & 1;
-  march2d_adjoint<T, 2, true, 2>(g, P.ob, ac, st, y0, y1, (const T*)P.A[flip], (T*)P.A[flip ^ 1],
-                                 (const T*)P.prep, P.src, P.oprep, (const T*)P.pv[cur], (T*)P.pv[cur ^ 1]);
+  const int cur = (P.pvcur0 + p.pv) & 1, flip = p.adjoint.flip;
+  march2d_adjoint<T, 2, true, 2>(g, P.ob, ac, st, y0, y1, (const T*)P.A[flip], (T*)P.A[flip ^ 1], (const T*)P.prep,
+                                 P.src, P.oprep, (const T*)P.pv[cur], (T*)P.pv[cur ^ 1]);
+}
+
+template <typename S>
+__global__ __launch_bounds__(256, 2) void k_packed2d(const PackedPasses p) {
+  const int b = (int)blockIdx.x;
+  if (b < p.primal.blocks)
+    packed_primal<S>(p, b);
+  else
+    packed_adjoint<typename Prec<S>::T>(p, b - p.primal.blocks);
 }
 }  // namespace
 
@@ -69,44 +78,29 @@ bool packed_pass_member(const hlbm_lattice_s* L, int mode) {
   return L->f2 != nullptr && (mode == HLBM_GROUP_PRIMAL || (!L->desc.track_mean_populations && !mea));
 }
 
-int packed_pass_plan(hlbm_lattice_s* const* L, int count, March2* m) {
-  if (count == 0) return 0;
-  std::vector<int> strips(count), ny(count);
+// Rows per chunk: 4, or 3 where the wavefronts of all members are few (at most
+// two workgroups a CU), so that each has less to do.  us a step with 3, 4, 7 and 12
+// rows: 12 members of 128 x 64 to 512 x 256, FP32 16.5, 15.8, 15.9, 22.4, FP64 23.2, 21.8,
+// 25.4, 35.4; 4 of them, FP32, 7.6, 8.6, 10.9, 16.0; 12 up to 200 x 100 7.0, 7.7, 10.6, 15.8.
+void packed_pass_plan(hlbm_lattice_s* const* L, int count, March2* m) {
+  int groups = 0;
   for (int i = 0; i < count; ++i) {
-    strips[i] = (L[i]->desc.nx + 61) / 62;
-    ny[i] = L[i]->desc.ny;
+    m[i].strips = (L[i]->desc.nx + 61) / 62;
+    groups += (m[i].strips * ((L[i]->desc.ny + 3) / 4) + 3) / 4;
   }
-  const int rows = march2d_rows(strips.data(), ny.data(), count, 2, L[0]->desc.precision == HLBM_FP64, 12);
-  int blocks = 0;
   for (int i = 0; i < count; ++i) {
-    m[i].strips = strips[i];
-    m[i].rows = rows;
-    m[i].chunks = (ny[i] + rows - 1) / rows;
-    blocks += (m[i].strips * m[i].chunks + 3) / 4;
+    m[i].rows = groups > 512 ? 4 : 3;
+    m[i].chunks = (L[i]->desc.ny + m[i].rows - 1) / m[i].rows;
   }
-  return blocks;
 }
 
-hipError_t launch_primal_packed_pass(hipStream_t st, int precision, const void* tab, const int* first, int nm,
-                                     int blocks, int flip) {
-  const PackedPrimal* t = (const PackedPrimal*)tab;
-  const dim3 grid((unsigned)blocks);
+hipError_t launch_packed_pass(hipStream_t st, int precision, const PackedPasses& p) {
+  const dim3 grid((unsigned)(p.primal.blocks + p.adjoint.blocks));
   switch (precision) {
-    case HLBM_FP64: k_primal_packed2d<double><<<grid, 256, 0, st>>>(t, first, nm, flip); break;
-    case HLBM_FP32: k_primal_packed2d<float><<<grid, 256, 0, st>>>(t, first, nm, flip); break;
-    default: k_primal_packed2d<_Float16><<<grid, 256, 0, st>>>(t, first, nm, flip); break;
+    case HLBM_FP64: k_packed2d<double><<<grid, 256, 0, st>>>(p); break;
+    case HLBM_FP32: k_packed2d<float><<<grid, 256, 0, st>>>(p); break;
+    default: k_packed2d<_Float16><<<grid, 256, 0, st>>>(p); break;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_adjoint_packed_pass(hipStream_t st, int precision, const void* tab, const int* first, int nm,
-                                      int blocks, int flip, int pv) {
-  const PackedAdjoint* t = (const PackedAdjoint*)tab;
-  const dim3 grid((unsigned)blocks);
-  if (precision == HLBM_FP64)
-    k_adjoint_packed2d<double><<<grid, 256, 0, st>>>(t, first, nm, flip, pv);
-  else
-    k_adjoint_packed2d<float><<<grid, 256, 0, st>>>(t, first, nm, flip, pv);
   return hipGetLastError();
 }
 
