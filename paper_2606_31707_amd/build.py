@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libhlbm.so")
 CANARY_PATH = os.path.join(HERE, "libhlbm_canary.so")
-SOURCES = ["hlbm_launch.hip", "hlbm_march2d.hip", "hlbm_march2d_adjoint.hip", "hlbm_march3d.hip",
+SOURCES = ["hlbm_launch.hip", "hlbm_march2d.hip", "hlbm_march2d_adjoint.hip", "hlbm_march3d.hip", "hlbm_march3d_adjoint.hip",
            "hlbm_window2d.hip", "hlbm_packed2d.hip", "hlbm_api.hip"]
 ARCH = os.environ.get("HLBM_OFFLOAD_ARCH", "gfx950")
 CANARY_DEFINES = ["-DHLBM_TILE_BX=64", "-DHLBM_XCD_REMAP=0"]

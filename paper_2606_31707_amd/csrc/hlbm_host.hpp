@@ -62,7 +62,11 @@ inline int nb_of(int stencil) { return 1 + dim_of(stencil) + nsym_of(stencil); }
 // 756x168x84 with walls 158 and 198; 768x384x128 565 and 478); for the adjoint
 // also the HRR collision (its frozen data would have to wait for the later
 // levels as well).  J_MEA takes single steps too, but counts the second phi
-// array: a window can be given another objective.
+// array: a window can be given another objective.  The 3D adjoint passes are
+// bound by their instructions and pay only in FP64 beyond the caches (us an
+// iteration, single / pass: FP64 756x168x84 798 / 533, 300x128x64 175 / 137,
+// 240x110x66 (279 MB) 109 / 100, 192x96x64 (189 MB) 57 / 73; FP32 768x384x128
+// 1195 / 1439, 192x96x64 34 / 44).
 inline bool primal_passes_of(const hlbm_desc* d) {
   if (d->stencil == HLBM_D3Q19 && (d->nz < 2 || d->precision == HLBM_FP16S)) return false;
   return d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
@@ -70,7 +74,10 @@ inline bool primal_passes_of(const hlbm_desc* d) {
          d->force[2] == 0.0;
 }
 inline bool adjoint_passes_of(const hlbm_desc* d) {
-  return d->stencil == HLBM_D2Q9 && d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
+  if (d->stencil == HLBM_D3Q19 &&
+      (d->nz < 2 || d->precision != HLBM_FP64 || (int64_t)d->nx * d->ny * d->nz * 160 <= ((int64_t)256 << 20)))
+    return false;
+  return d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
          (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->collision == HLBM_COLL_BGK;
 }
 

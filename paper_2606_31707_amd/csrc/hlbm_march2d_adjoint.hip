@@ -24,10 +24,12 @@ void march2d_adjoint_pass(hlbm_lattice_s* L) {
 // (400 x 160 FP32: 3.8 us an iteration with two, 4.5 with four; 1024 x 512 with
 // the dissipation box 8.1 and 7.3, FP64 with the drag plane 12.5 and 11.6).
 int adjoint_pass_steps(const hlbm_lattice_s* L, int64_t left) {
+  if (L->desc.stencil == HLBM_D3Q19) return left >= 2 ? 2 : 1;
   return left >= 4 && L->n >= 400000 ? 4 : (left >= 2 ? 2 : 1);
 }
 
 hipError_t launch_adjoint_pass(hlbm_lattice_s* L, int K) {
+  if (L->desc.stencil == HLBM_D3Q19) return K == 2 ? launch_march3d_adjoint(L) : hipErrorInvalidValue;
   const bool f64 = L->desc.precision == HLBM_FP64;
   if (K == 4) {
     if (f64) march2d_adjoint_pass<double, 4>(L); else march2d_adjoint_pass<float, 4>(L);

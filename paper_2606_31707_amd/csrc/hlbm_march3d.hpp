@@ -32,6 +32,8 @@ struct March3 {
   int tx, ty, chunks, planes;  // tiles along x and y, chunks along z, planes per chunk
 };
 
+March3 march3d_plan(const hlbm_lattice_s* L, int R);
+
 // Rows of a workgroup: three wavefronts a SIMD in FP32 (16 rows and four
 // wavefronts, which share fewer recomputed rows but have 128 registers each:
 // 870 instead of 845 us at 768x384x128, 227 instead of 203 at 756x168x84); two
@@ -372,6 +374,28 @@ __device__ __forceinline__ void march3d(const Geo& g, const Coll& c, const March
   }
 }
 
+// The tile and planes of a workgroup, and whether they hold an inlet or outlet
+// column, a row or a plane beside a wall.
+struct Tile3Id {
+  int tx, ty, z0, z1;
+  bool ends, walls;
+};
+template <int R>
+__device__ __forceinline__ Tile3Id tile3_id(const Geo& g, const March3& m) {
+  Tile3Id t;
+  const int id = sweep_tile((int)blockIdx.x, (int)gridDim.x);
+  const int per = m.tx * m.ty;
+  const int chunk = wave_uniform(id / per), r = id - chunk * per;
+  t.ty = wave_uniform(r / m.tx);
+  t.tx = r - t.ty * m.tx;
+  t.z0 = chunk * m.planes;
+  t.z1 = t.z0 + m.planes < g.nz ? t.z0 + m.planes : g.nz;
+  t.ends = g.bcx == BC_INOUT && (t.tx == 0 || t.tx * 62 + 62 >= g.nx - 1);
+  t.walls = (g.bcy != BC_PERIODIC && (t.ty == 0 || (t.ty + 1) * (R - 2) >= g.ny)) ||
+            (g.bcz != BC_PERIODIC && (t.z0 == 0 || t.z1 == g.nz));
+  return t;
+}
+
 template <typename S, bool HRR, bool SMAG, bool ACC>
 __device__ __forceinline__ void march3d_tile(const Geo& g, const MarchColl& mc, const March3& m,
                                              const S* __restrict__ A, S* __restrict__ B,
@@ -381,22 +405,15 @@ __device__ __forceinline__ void march3d_tile(const Geo& g, const MarchColl& mc, 
   constexpr int R = march3d_rows<T>();
   __shared__ T lds[2 * 10 * R * 64 + 2];
   const Coll c = mc.coll();
-  const int id = sweep_tile((int)blockIdx.x, (int)gridDim.x);
-  const int per = m.tx * m.ty;
-  const int chunk = wave_uniform(id / per), r = id - chunk * per;
-  const int ty = wave_uniform(r / m.tx), tx = r - ty * m.tx;
-  const int z0 = chunk * m.planes, z1 = z0 + m.planes < g.nz ? z0 + m.planes : g.nz;
-  const bool ends = g.bcx == BC_INOUT && (tx == 0 || tx * 62 + 62 >= g.nx - 1);
-  // workgroups that hold a row or a plane beside a wall
-  const bool walls = (g.bcy != BC_PERIODIC && (ty == 0 || (ty + 1) * (R - 2) >= g.ny)) ||
-                     (g.bcz != BC_PERIODIC && (z0 == 0 || z1 == g.nz));
-  if (walls) {
-    if (ends)
+  const Tile3Id id = tile3_id<R>(g, m);
+  const int tx = id.tx, ty = id.ty, z0 = id.z0, z1 = id.z1;
+  if (id.walls) {
+    if (id.ends)
       march3d<S, HRR, SMAG, true, true, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
     else
       march3d<S, HRR, SMAG, false, true, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
   } else {
-    if (ends)
+    if (id.ends)
       march3d<S, HRR, SMAG, true, false, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);
     else
       march3d<S, HRR, SMAG, false, false, ACC>(g, c, m, tx, ty, z0, z1, A, B, dpor, pr, wn, lds);

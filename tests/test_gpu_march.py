@@ -177,6 +177,27 @@ def test_window_passes_with_a_large_region_beyond_the_caches(prec, size, cs):
         assert np.array_equal(a, b)
 
 
+# FP64 lattices just beyond the caches: rows and planes beside walls in and next to a tile's halo.
+@pytest.mark.parametrize("size,bc,obj", [((124, 121, 113), (2, 0, 0), "ffa"), ((125, 121, 113), (2, 1, 1), "diss"),
+                                         ((190, 94, 97), (2, 0, 1), "diss"), ((61, 127, 221), (2, 1, 0), "ffa"),
+                                         ((130, 115, 115), (0, 1, 1), "ffa")])
+def test_adjoint_passes_equal_single_iterations_3d(size, bc, obj):
+    from paper_2606_31707_amd import hlbm as H
+    nx, ny, nz = size
+    (lx, ly, _), (hx, hy, _) = REGIONS_2D[obj](nx, ny)
+    say("adjoint passes", size, bc, obj)
+    a, b = (lattice(H, H.D3Q19, size, 0, bc, 0, 0.1 if obj == "ffa" else 0.0) for _ in range(2))
+    for L in (a, b):
+        L.set_objective(H.OBJ_FFA if obj == "ffa" else H.OBJ_DISS, (lx, ly, nz // 3), (hx, hy, nz - 1), u0=0.04)
+        L.run_primal(4, accumulate=True)
+    _adjoints(H, a, b, H.SOURCE_MEAN, 4, 0)
+    _adjoints(H, a, b, H.SOURCE_MEAN, 2, 4)
+    assert np.array_equal(a.adjoint(), b.adjoint())
+    assert np.array_equal(a.gradient(), b.gradient())
+    a.close()
+    b.close()
+
+
 def _members(H, prec, stream=None):
     """Plain, window (small region, large region, none) and adjoint members of different sizes and ends."""
     out = []
