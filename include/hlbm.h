@@ -185,8 +185,9 @@ hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out);
 /* Free every device buffer of the handle (synchronises its stream). */
 void hlbm_destroy(hlbm_lattice lat);
 /* Device bytes a lattice of this descriptor holds at most for one query:
- * populations, porosity, outlet values, reduction partials and the steady-
- * check snapshot; the objective's region buffers for region_cells cells of
+ * populations (with the second array of the multi-step passes, which is held
+ * only while a quarter of the device's memory stays free), porosity, outlet
+ * values, reduction partials and the steady-check snapshot; the objective's region buffers for region_cells cells of
  * kind `objective` (0 cells: no objective); with_window != 0 the FP64 window
  * sums; with_adjoint != 0 the adjoint populations, frozen data, gradient data
  * and residual snapshot.  A velocity probe and the forward tangent's buffers
@@ -253,7 +254,10 @@ hlbm_status hlbm_set_objective(hlbm_lattice lat, int32_t kind, const int32_t lo[
 
 /* ---- primal and window (rows a3, a4, a5) --------------------------------- */
 
-/* Advance n_steps collide-and-stream steps (in-place AA pattern).  If
+/* Advance n_steps collide-and-stream steps (in-place AA pattern, or two or
+ * four steps in one pass between two population arrays where the lattice has
+ * a second one: the same results bit for bit; a captured run takes single
+ * steps).  If
  * accumulate != 0 every step adds its pre-collision state to the FP64 window
  * (rho, j, optional f, tau_eff, objective terms and dJ/df, dJ/dd
  * coefficients).  If steady_tol > 0, every check_every steps the call stops
@@ -324,8 +328,9 @@ hlbm_status hlbm_synchronize(hlbm_lattice lat);
  * every = 0 switches it off; every call clears the statistics.  kind: 0
  * primal sweep, 1 primal step with window accumulation (sweep plus the
  * region pass of a small objective region), 2 adjoint sweep.
- * hlbm_profile_get returns the mean time per launch in microseconds and the
- * number of launches timed (blocks finished so far). */
+ * hlbm_profile_get returns the mean time per sweep in microseconds and the
+ * number of sweeps timed (blocks finished so far); a launch that takes several
+ * steps in one pass counts as that many. */
 hlbm_status hlbm_profile_enable(hlbm_lattice lat, int32_t every);
 hlbm_status hlbm_profile_get(hlbm_lattice lat, int32_t kind, double* mean_us, int64_t* sampled);
 /* Velocity probe: every primal step records u_y of cell (x, y, z) (the
@@ -339,7 +344,7 @@ hlbm_status hlbm_get_probe(hlbm_lattice lat, double* out, int64_t capacity, int6
  * step of an FP32 or FP16 lattice is counted as the mean over a group of
  * four steps: its FP64 sums are read and written once per group, the first
  * three steps leaving their values as FP32 for the fourth (see
- * hlbm_run_primal). */
+ * hlbm_run_primal).  Multi-step passes move fewer bytes than this per step. */
 hlbm_status hlbm_bytes_per_update(hlbm_lattice lat, double* primal, double* primal_window,
                                   double* adjoint);
 /* Bandwidth probe (a measurement, not a step of the method): n_launches
