@@ -272,6 +272,23 @@ hlbm_status prof_collect_all(hlbm_lattice_s* L) {
   return HLBM_OK;
 }
 
+// Every call leaves the state in the array it found it in (a caller's captured
+// work, packed tables): passes are taken in pairs where the steps left allow
+// it.  K: the steps a pass could take, left: steps left in the call, odd: an
+// odd number of passes is behind.
+int paired_pass(int K, int64_t left, bool odd) {
+  if (odd || K == 1) return K;
+  if (K == 4) return left >= 6 ? 4 : 2;  // two passes of two at the end
+  return left >= 4 ? 2 : 1;
+}
+// A call that stops between two passes (a criterion met) copies the state back.
+hlbm_status settle_arrays(hlbm_lattice_s* L, void*& cur, void*& second, const void* start, size_t bytes) {
+  if (cur == start) return HLBM_OK;
+  HIP_TRY(hipMemcpyAsync(second, cur, bytes, hipMemcpyDeviceToDevice, L->stream));
+  std::swap(cur, second);
+  return HLBM_OK;
+}
+
 bool stream_capturing(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
@@ -743,6 +760,8 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
   // Multi-step passes swap the two population arrays: a captured run, whose
   // replays start from the same array every time, takes single steps.
   const bool multi = L->f2 != nullptr && !stream_capturing(L->stream);
+  void* const start = L->f;
+  const size_t state_bytes = L->ssize * L->q * L->plane;
   // snapshot of u at the start of a steady run
   if (steady_tol > 0.0) {
     int nbl = 0;
@@ -758,7 +777,9 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
     int64_t chunk = n_steps - done;
     if (steady_tol > 0.0 && chunk > check_every) chunk = check_every;
     for (int64_t k = 0; k < chunk;) {
-      const int K = multi && L->parity == 0 ? primal_pass_steps(L, accumulate, chunk - k) : 1;
+      const int K = multi && L->parity == 0 ? paired_pass(primal_pass_steps(L, accumulate, chunk - k),
+                                                          n_steps - done - k, L->f != start)
+                                            : 1;
       s = timed_launch(L, accumulate ? 1 : 0, chunk - k, K, [&]() {
         return K > 1 ? launch_primal_pass(L, accumulate, K) : launch_primal_step(L, accumulate);
       });
@@ -777,6 +798,7 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
       if ((s = reduce_to_host(L, nbl, 1, mm)) != HLBM_OK) return s;
       if (!std::isfinite(mm[0]) || !std::isfinite(mm[1])) {
         if (steps_done) *steps_done = done;
+        if ((s = settle_arrays(L, L->f, L->f2, start, state_bytes)) != HLBM_OK) return s;
         if ((s = flush_window(L)) != HLBM_OK) return s;
         return fail(HLBM_E_DIVERGED, "non-finite velocity after %lld steps", (long long)L->steps);
       }
@@ -787,6 +809,7 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
     }
   }
   if (steps_done) *steps_done = done;
+  if ((s = settle_arrays(L, L->f, L->f2, start, state_bytes)) != HLBM_OK) return s;
   if ((s = flush_window(L)) != HLBM_OK) return s;
   if (steady_tol > 0.0 && !converged) result = HLBM_W_NOT_CONVERGED;
   L->adj_ready = 0;
@@ -914,6 +937,8 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
   const bool passes = adjoint_passes_of(&L->desc);
   if (passes) lat_alloc_second(L, &L->phi2, as * L->q * plane);
   const bool multi = L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !stream_capturing(L->stream);
+  void* const start = L->phi;
+  const size_t phi_bytes = as * L->q * plane;
   int64_t iters = o->max_iters + (o->max_iters & 1);
   int64_t M = o->check_every > 0 ? o->check_every : 100;
   M += (M & 1);
@@ -930,7 +955,9 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
     int64_t chunk = iters - done;
     if (o->tol > 0.0 && chunk > M) chunk = M;
     for (int64_t k = 0; k < chunk;) {
-      const int K = multi && (L->adj_iters & 1) == 0 ? adjoint_pass_steps(L, chunk - k) : 1;
+      const int K = multi && (L->adj_iters & 1) == 0
+                        ? paired_pass(adjoint_pass_steps(L, chunk - k), iters - done - k, L->phi != start)
+                        : 1;
       s = timed_launch(L, 2, chunk - k, K, [&]() { return K > 1 ? launch_adjoint_pass(L, K) : launch_adjoint_step(L); });
       if (s != HLBM_OK) return s;
       L->pvcur ^= 1;  // a pass reads and writes the outlet buffers once
@@ -949,6 +976,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
           rep->iters = done;
           rep->residual = res;
         }
+        if ((s = settle_arrays(L, L->phi, L->phi2, start, phi_bytes)) != HLBM_OK) return s;
         return fail(HLBM_E_DIVERGED, "adjoint diverged after %lld iterations (residual %g, smallest %g)",
                     (long long)L->adj_iters, res, min_res);
       }
@@ -958,6 +986,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
       }
     }
   }
+  if ((s = settle_arrays(L, L->phi, L->phi2, start, phi_bytes)) != HLBM_OK) return s;
   if (o->tol > 0.0) HIP_TRY(hipStreamSynchronize(L->stream));
   if (rep) {
     rep->iters = done;
@@ -1153,7 +1182,7 @@ extern "C" void hlbm_group_destroy(hlbm_group g) {
   delete[] g->members;
   delete[] g->modes;
   delete[] g->counts0;
-  delete[] g->arrays;
+  delete[] g->second;
   delete g;
 }
 
@@ -1228,28 +1257,19 @@ hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int
   if ((s = upload(tp, fp, ps, &g->tab_primal, &g->first_primal, &g->cap_primal)) != HLBM_OK) return s;
   if ((s = upload(ta, fa, as, &g->tab_adjoint, &g->first_adjoint, &g->cap_adjoint)) != HLBM_OK) return s;
   HIP_TRY(hipStreamSynchronize(g->stream));  // host tables go out of scope
-  void** arrays = count ? new void*[2 * count] : nullptr;
-  for (int i = 0; i < count; ++i) {
-    const bool adj = modes[i] == HLBM_GROUP_ADJOINT;
-    arrays[2 * i] = adj ? lats[i]->phi : lats[i]->f;
-    arrays[2 * i + 1] = adj ? lats[i]->phi2 : lats[i]->f2;
-  }
-  delete[] g->arrays;
-  g->arrays = arrays;
+  void** second = count ? new void*[count] : nullptr;
+  for (int i = 0; i < count; ++i) second[i] = modes[i] == HLBM_GROUP_ADJOINT ? lats[i]->phi2 : lats[i]->f2;
+  delete[] g->second;
+  g->second = second;
   g->n_primal = n_primal;
   g->n_adjoint = n_adjoint;
   g->blocks_primal = bp;
   g->blocks_adjoint = ba;
   g->pass_primal = pass_p ? qp : 0;
   g->pass_adjoint = pass_a ? qa : 0;
-  g->flip_primal = g->flip_adjoint = g->pv_adjoint = 0;
+  g->pv_adjoint = 0;
   g->steps_since_set = 0;
   return HLBM_OK;
-}
-
-void group_counts(hlbm_group_s* g) {
-  for (int i = 0; i < g->count; ++i)
-    g->counts0[i] = g->modes[i] == HLBM_GROUP_ADJOINT ? g->members[i]->adj_iters : g->members[i]->steps;
 }
 }  // namespace
 
@@ -1287,7 +1307,8 @@ extern "C" hlbm_status hlbm_group_set(hlbm_group g, const hlbm_lattice* lats, co
     g->modes[i] = modes[i];
   }
   g->count = count;
-  group_counts(g);
+  for (int i = 0; i < count; ++i)
+    g->counts0[i] = modes[i] == HLBM_GROUP_ADJOINT ? lats[i]->adj_iters : lats[i]->steps;
   g->stencil = count ? lats[0]->desc.stencil : -1;
   g->precision = count ? lats[0]->desc.precision : -1;
   g->collision = count ? lats[0]->desc.collision : 0;
@@ -1295,44 +1316,42 @@ extern "C" hlbm_status hlbm_group_set(hlbm_group g, const hlbm_lattice* lats, co
 }
 
 namespace {
-// Where a run leaves the two-array state of the lists.
-struct GroupFlips {
-  int primal, adjoint, pv;
-};
-
-// The packed launches of an n-step run: passes of two steps where a list takes
-// them (members at parity 0, two steps left), single steps otherwise (AA parity
-// from the step count since the last set).  dry: only says where it ends.
-hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, GroupFlips* end, bool dry) {
-  GroupFlips at{g->flip_primal, g->flip_adjoint, g->pv_adjoint};
+// The packed launches of an n-step run: passes of two steps, in pairs, where a
+// list takes them (members at parity 0), single steps otherwise (AA parity
+// from the step count since the last set).  dry: only counts the outlet buffer
+// toggles (*pv; each adjoint launch makes one).
+hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, int* pv, bool dry) {
+  int flip_p = 0, flip_a = 0, at = g->pv_adjoint;
   hipError_t e = hipSuccess;
   int64_t kp = g->n_primal > 0 ? 0 : n, ka = g->n_adjoint > 0 ? 0 : n;
   while ((kp < n || ka < n) && e == hipSuccess) {
     const int64_t sp = g->steps_since_set + kp, sa = g->steps_since_set + ka;
     // the list that is behind goes first; both in one launch where both take a pass
     const bool do_p = kp < n && kp <= ka, do_a = ka < n && ka <= kp;
-    const bool two_p = do_p && passes && g->pass_primal > 0 && ((g->parity_primal + sp) & 1) == 0 && n - kp >= 2;
-    const bool two_a = do_a && passes && g->pass_adjoint > 0 && ((g->parity_adjoint + sa) & 1) == 0 && n - ka >= 2;
+    const bool two_p = do_p && passes && g->pass_primal > 0 && ((g->parity_primal + sp) & 1) == 0 &&
+                       paired_pass(2, n - kp, flip_p != 0) == 2;
+    const bool two_a = do_a && passes && g->pass_adjoint > 0 && ((g->parity_adjoint + sa) & 1) == 0 &&
+                       paired_pass(2, n - ka, flip_a != 0) == 2;
     if (!dry && (two_p || two_a)) {
       const PackedPasses p{
-          {g->tab_primal, g->first_primal + g->n_primal, g->n_primal, two_p ? g->pass_primal : 0, at.primal},
-          {g->tab_adjoint, g->first_adjoint + g->n_adjoint, g->n_adjoint, two_a ? g->pass_adjoint : 0, at.adjoint},
-          at.pv};
+          {g->tab_primal, g->first_primal + g->n_primal, g->n_primal, two_p ? g->pass_primal : 0, flip_p},
+          {g->tab_adjoint, g->first_adjoint + g->n_adjoint, g->n_adjoint, two_a ? g->pass_adjoint : 0, flip_a},
+          at};
       e = launch_packed_pass(g->stream, g->precision, p);
     }
     if (!dry && do_p && !two_p && e == hipSuccess)
       e = launch_primal_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_primal, g->first_primal,
-                               g->n_primal, g->blocks_primal, (int)(sp & 1), at.primal);
+                               g->n_primal, g->blocks_primal, (int)(sp & 1));
     if (!dry && do_a && !two_a && e == hipSuccess)
       e = launch_adjoint_packed(g->stream, g->stencil, g->precision, g->collision, g->tab_adjoint,
-                                g->first_adjoint, g->n_adjoint, g->blocks_adjoint, (int)(sa & 1), at.adjoint, at.pv);
-    at.primal ^= two_p;
-    at.adjoint ^= two_a;
-    at.pv ^= do_a;  // a launch reads and writes the outlet buffers once
+                                g->first_adjoint, g->n_adjoint, g->blocks_adjoint, (int)(sa & 1), at);
+    flip_p ^= two_p;
+    flip_a ^= two_a;
+    at ^= do_a;
     kp += do_p ? (two_p ? 2 : 1) : 0;
     ka += do_a ? (two_a ? 2 : 1) : 0;
   }
-  *end = at;
+  *pv = at;
   return e;
 }
 
@@ -1353,8 +1372,7 @@ bool launch_group_graph(hlbm_group_s* g, int64_t n, bool passes) {
                             (uint64_t)g->n_adjoint, (uint64_t)g->blocks_adjoint, (uint64_t)n,
                             (uint64_t)(g->steps_since_set & 1), (uint64_t)passes, (uint64_t)g->pass_primal,
                             (uint64_t)g->pass_adjoint,
-                            (uint64_t)(g->parity_primal | g->parity_adjoint << 1 | g->flip_primal << 2 |
-                                       g->flip_adjoint << 3 | g->pv_adjoint << 4)};
+                            (uint64_t)(g->parity_primal | g->parity_adjoint << 1 | g->pv_adjoint << 2)};
   if (!g->gexec || std::memcmp(key, g->gkey, sizeof key) != 0) {
     if (g->gexec) {
       (void)hipGraphExecDestroy(g->gexec);
@@ -1364,8 +1382,8 @@ bool launch_group_graph(hlbm_group_s* g, int64_t n, bool passes) {
       (void)hipGetLastError();
       return false;
     }
-    GroupFlips end;
-    const hipError_t e = enqueue_group_steps(g, n, passes, &end, false);
+    int pv = 0;
+    const hipError_t e = enqueue_group_steps(g, n, passes, &pv, false);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(g->stream, &graph);
     hipGraphExec_t exec = nullptr;
@@ -1395,50 +1413,34 @@ extern "C" hlbm_status hlbm_group_step(hlbm_group g, int64_t n) {
     if (now != g->counts0[i] + g->steps_since_set)
       return fail(HLBM_E_STATE, "member %d was advanced outside the group since hlbm_group_set", i);
   }
-  // Two-step passes need both arrays of every member where the tables have them
-  // (they may have been given back for memory), and the same arrays in every
-  // replay of a caller's capture.
-  bool passes = !stream_capturing(g->stream), moved = false;
+  // Two-step passes need the second arrays that the tables name (they may have
+  // been given back for memory); a caller's capture takes single steps.
+  bool passes = !stream_capturing(g->stream);
   for (int i = 0; i < g->count; ++i) {
     const hlbm_lattice_s* L = g->members[i];
-    const bool adj = g->modes[i] == HLBM_GROUP_ADJOINT;
-    const int flip = adj ? g->flip_adjoint : g->flip_primal;
-    moved = moved || (adj ? L->phi : L->f) != g->arrays[2 * i + flip];
-    passes = passes && (adj ? L->phi2 : L->f2) == g->arrays[2 * i + (flip ^ 1)];
+    passes = passes && (g->modes[i] == HLBM_GROUP_ADJOINT ? L->phi2 : L->f2) == g->second[i];
   }
-  if (moved) {  // by runs outside the group whose counts were reset since
-    if (stream_capturing(g->stream)) return fail(HLBM_E_STATE, "a member's arrays moved since hlbm_group_set");
-    HIP_TRY(hipStreamSynchronize(g->stream));
-    hlbm_status s = group_tables(g, g->members, g->modes, g->count);
-    if (s != HLBM_OK) return s;
-    group_counts(g);
-    passes = true;
-  }
-  GroupFlips end;
-  HIP_TRY(enqueue_group_steps(g, n, passes, &end, true));
+  int pv = 0;
+  HIP_TRY(enqueue_group_steps(g, n, passes, &pv, true));
   bool done = false;
   if (n >= kGraphMinSteps && g->stream != nullptr && g->graph_ok) {
     done = launch_group_graph(g, n, passes);
     if (!done) g->graph_ok = false;  // from now on the plain launches below
   }
-  if (!done) HIP_TRY(enqueue_group_steps(g, n, passes, &end, false));
+  if (!done) HIP_TRY(enqueue_group_steps(g, n, passes, &pv, false));
   for (int i = 0; i < g->count; ++i) {
     hlbm_lattice_s* L = g->members[i];
     if (g->modes[i] == HLBM_GROUP_ADJOINT) {
       L->adj_iters += n;
-      L->pvcur ^= end.pv ^ g->pv_adjoint;
-      if (end.adjoint != g->flip_adjoint) std::swap(L->phi, L->phi2);
+      L->pvcur ^= pv ^ g->pv_adjoint;
     } else {
       L->parity ^= (int)(n & 1);
       L->steps += n;
-      if (end.primal != g->flip_primal) std::swap(L->f, L->f2);
       if (g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW) L->nsamp += n;
       L->adj_ready = 0;
     }
   }
-  g->flip_primal = end.primal;
-  g->flip_adjoint = end.adjoint;
-  g->pv_adjoint = end.pv;
+  g->pv_adjoint = pv;
   g->steps_since_set += n;
   return HLBM_OK;
 }

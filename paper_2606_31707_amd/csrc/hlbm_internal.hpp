@@ -228,12 +228,12 @@ size_t packed_adjoint_size();
 void fill_packed_primal(const hlbm_lattice_s* L, int accumulate, int first_block, int first_pass, const March2& m,
                         void* out);
 void fill_packed_adjoint(const hlbm_lattice_s* L, int first_block, int first_pass, const March2& m, void* out);
-// One step (iteration) of every member.  flip: which of a member's two arrays
-// holds its state; pv: outlet buffer toggles since the table was built.
+// One step (iteration) of every member; pv: outlet buffer toggles since the
+// table was built.
 hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                const int* first, int nm, int blocks, int step, int flip);
+                                const int* first, int nm, int blocks, int step);
 hipError_t launch_adjoint_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                 const int* first, int nm, int blocks, int step, int flip, int pv);
+                                 const int* first, int nm, int blocks, int step, int pv);
 // Two steps (iterations) of every member in one pass: whether a member can take
 // it, the chunks of each member, the launch.
 bool packed_pass_member(const hlbm_lattice_s* L, int mode);
@@ -264,15 +264,13 @@ struct hlbm_group_s {
   size_t cap_primal = 0, cap_adjoint = 0;  // members the device tables hold
   int64_t steps_since_set = 0;
   // Two-step passes of the packed members (blocks of a launch; 0: single steps
-  // only), which go back and forth between two arrays per member: flip is the
-  // one that holds the state (0: as of the set).  parity: the members' common
-  // AA parity at the set; pv_adjoint: outlet buffer toggles since the set (one a
-  // launch).
+  // only), back and forth between two arrays per member.  parity: the members'
+  // common AA parity at the set; pv_adjoint: outlet buffer toggles since the
+  // set (one a launch); second: each member's second array at the set.
   int pass_primal = 0, pass_adjoint = 0;
   int parity_primal = 0, parity_adjoint = 0;
-  int flip_primal = 0, flip_adjoint = 0;
   int pv_adjoint = 0;
-  void** arrays = nullptr;  // each member's two arrays at the set
+  void** second = nullptr;
   // the last multi-step run of packed launches, captured as a HIP graph
   // (kernel nodes only) and replayed while the launch arguments repeat
   hipGraphExec_t gexec = nullptr;

@@ -1549,8 +1549,7 @@ __device__ __forceinline__ int packed_member(const int* __restrict__ first, int 
 
 template <int Q, typename S, bool HRR>
 __global__ __launch_bounds__(256) void k_primal_packed(const PackedPrimal* __restrict__ tab,
-                                                       const int* __restrict__ first, int nm, int step,
-                                                       int flip) {
+                                                       const int* __restrict__ first, int nm, int step) {
   using Dd = typename Prec<S>::Dd;
   const int b = sweep_tile((int)blockIdx.x, (int)gridDim.x);
   const PackedPrimal& P = tab[packed_member(first, nm, b)];
@@ -1561,7 +1560,7 @@ __global__ __launch_bounds__(256) void k_primal_packed(const PackedPrimal* __res
   if (x >= P.g.nx || y >= P.g.ny) return;
   const int64_t c0 = wave_uniform64(cell_of(P.g, tx * BX, ty * BY, z));
   const uint32_t lo = lane_offset(threadIdx.x + (uint32_t)P.g.nx * threadIdx.y);
-  S* A = (S*)P.A[flip];
+  S* A = (S*)P.A[0];
   const Dd* dp = (const Dd*)P.dpor;
   S* gh = (S*)P.ghost;
   const int mode = P.accumulate ? (P.ob.kind == OBJ_MEA ? 2 : 1) : 0;
@@ -2636,7 +2635,7 @@ struct PackedAdjoint {
 template <int Q, typename SA, bool HRR>
 __global__ __launch_bounds__(256) void k_adjoint_packed(const PackedAdjoint* __restrict__ tab,
                                                         const int* __restrict__ first, int nm, int step,
-                                                        int flip, int pv) {
+                                                        int pv) {
   const int b = sweep_tile((int)blockIdx.x, (int)gridDim.x);
   const PackedAdjoint& P = tab[packed_member(first, nm, b)];
   const int lb = b - P.first_block;
@@ -2649,7 +2648,7 @@ __global__ __launch_bounds__(256) void k_adjoint_packed(const PackedAdjoint* __r
   const int cur = (P.pvcur0 + pv) & 1;
   const SA* pin = (const SA*)P.pv[cur];
   SA* pout = (SA*)P.pv[cur ^ 1];
-  SA* A = (SA*)P.A[flip];
+  SA* A = (SA*)P.A[0];
   const SA* pr = (const SA*)P.prep;
   const bool odd = ((P.iter0 + step) & 1) != 0;
   if (P.ob.kind == OBJ_MEA) {

@@ -607,25 +607,25 @@ size_t packed_adjoint_size() { return sizeof(PackedAdjoint); }
 
 template <int Q, typename S>
 static void primal_packed(hipStream_t st, bool hrr, const PackedPrimal* t, const int* first, int nm, int blocks,
-                          int step, int flip) {
+                          int step) {
   const dim3 grid((unsigned)blocks);
   if (hrr)
-    k_primal_packed<Q, S, true><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip);
+    k_primal_packed<Q, S, true><<<grid, kBlock, 0, st>>>(t, first, nm, step);
   else
-    k_primal_packed<Q, S, false><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip);
+    k_primal_packed<Q, S, false><<<grid, kBlock, 0, st>>>(t, first, nm, step);
 }
 
 hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                const int* first, int nm, int blocks, int step, int flip) {
+                                const int* first, int nm, int blocks, int step) {
   const PackedPrimal* t = (const PackedPrimal*)tab;
   const bool hrr = collision == HLBM_COLL_HRR;
   switch (stencil * 3 + precision) {
-    case 0: primal_packed<9, double>(st, hrr, t, first, nm, blocks, step, flip); break;
-    case 1: primal_packed<9, float>(st, hrr, t, first, nm, blocks, step, flip); break;
-    case 2: primal_packed<9, _Float16>(st, hrr, t, first, nm, blocks, step, flip); break;
-    case 3: primal_packed<19, double>(st, hrr, t, first, nm, blocks, step, flip); break;
-    case 4: primal_packed<19, float>(st, hrr, t, first, nm, blocks, step, flip); break;
-    case 5: primal_packed<19, _Float16>(st, hrr, t, first, nm, blocks, step, flip); break;
+    case 0: primal_packed<9, double>(st, hrr, t, first, nm, blocks, step); break;
+    case 1: primal_packed<9, float>(st, hrr, t, first, nm, blocks, step); break;
+    case 2: primal_packed<9, _Float16>(st, hrr, t, first, nm, blocks, step); break;
+    case 3: primal_packed<19, double>(st, hrr, t, first, nm, blocks, step); break;
+    case 4: primal_packed<19, float>(st, hrr, t, first, nm, blocks, step); break;
+    case 5: primal_packed<19, _Float16>(st, hrr, t, first, nm, blocks, step); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -633,28 +633,28 @@ hipError_t launch_primal_packed(hipStream_t st, int stencil, int precision, int 
 
 template <int Q, typename SA>
 static void adjoint_packed(hipStream_t st, bool hrr, const PackedAdjoint* t, const int* first, int nm, int blocks,
-                           int step, int flip, int pv) {
+                           int step, int pv) {
   const dim3 grid((unsigned)blocks);
   if (hrr)
-    k_adjoint_packed<Q, SA, true><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip, pv);
+    k_adjoint_packed<Q, SA, true><<<grid, kBlock, 0, st>>>(t, first, nm, step, pv);
   else
-    k_adjoint_packed<Q, SA, false><<<grid, kBlock, 0, st>>>(t, first, nm, step, flip, pv);
+    k_adjoint_packed<Q, SA, false><<<grid, kBlock, 0, st>>>(t, first, nm, step, pv);
 }
 
 hipError_t launch_adjoint_packed(hipStream_t st, int stencil, int precision, int collision, const void* tab,
-                                 const int* first, int nm, int blocks, int step, int flip, int pv) {
+                                 const int* first, int nm, int blocks, int step, int pv) {
   const PackedAdjoint* t = (const PackedAdjoint*)tab;
   const bool f64 = precision == HLBM_FP64, hrr = collision == HLBM_COLL_HRR;
   if (stencil == HLBM_D2Q9) {
     if (f64)
-      adjoint_packed<9, double>(st, hrr, t, first, nm, blocks, step, flip, pv);
+      adjoint_packed<9, double>(st, hrr, t, first, nm, blocks, step, pv);
     else
-      adjoint_packed<9, float>(st, hrr, t, first, nm, blocks, step, flip, pv);
+      adjoint_packed<9, float>(st, hrr, t, first, nm, blocks, step, pv);
   } else {
     if (f64)
-      adjoint_packed<19, double>(st, hrr, t, first, nm, blocks, step, flip, pv);
+      adjoint_packed<19, double>(st, hrr, t, first, nm, blocks, step, pv);
     else
-      adjoint_packed<19, float>(st, hrr, t, first, nm, blocks, step, flip, pv);
+      adjoint_packed<19, float>(st, hrr, t, first, nm, blocks, step, pv);
   }
   return hipGetLastError();
 }

@@ -280,3 +280,39 @@ def test_packed_passes_equal_packed_single_steps(prec, own_stream):
     for m in (a, b):
         for L, _ in m:
             L.close()
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+def test_captured_steps_replay_between_runs_with_passes(dim):
+    """A captured run works on the same array at every replay, whatever runs (odd and even numbers
+    of passes, a steady stop between two passes) come in between."""
+    import torch
+    from paper_2606_31707_amd import hlbm as H
+    size = (70, 30, 1) if dim == 2 else (70, 15, 6)
+    stream = torch.cuda.Stream()
+    a = lattice(H, H.D2Q9 if dim == 2 else H.D3Q19, size, 1, (2, 1, 0), 0, 0.0, stream=stream.cuda_stream)
+    b = lattice(H, H.D2Q9 if dim == 2 else H.D3Q19, size, 1, (2, 1, 0), 0, 0.0)
+    a.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        a.run_primal(2)
+    for steps in (0, 4, 2, 12, 6, 10, 8):
+        say("captured steps", dim, steps)
+        if steps:
+            a.run_primal(steps)
+            b.run_primal(steps)
+        a.synchronize()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        stream.synchronize()
+        b.run_primal(2)
+        assert np.array_equal(a.populations(), b.populations()), steps
+    a.run_primal(400, steady_tol=1.0, check_every=4)  # stops after one pass
+    b.run_primal(4)
+    with torch.cuda.stream(stream):
+        graph.replay()
+    stream.synchronize()
+    b.run_primal(2)
+    assert np.array_equal(a.populations(), b.populations())
+    a.close()
+    b.close()
