@@ -935,8 +935,10 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
     L->adj_omega = 1.0 / tau_adj;
   }
   const bool passes = adjoint_passes_of(&L->desc);
-  if (passes) lat_alloc_second(L, &L->phi2, as * L->q * plane);
-  const bool multi = L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !stream_capturing(L->stream);
+  const bool capturing = stream_capturing(L->stream);
+  if (passes && !capturing) lat_alloc_second(L, &L->phi2, as * L->q * plane);
+  const bool multi =
+      L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !capturing;
   void* const start = L->phi;
   const size_t phi_bytes = as * L->q * plane;
   int64_t iters = o->max_iters + (o->max_iters & 1);
