@@ -940,7 +940,18 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
   const bool multi =
       L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !capturing;
   void* const start = L->phi;
-  const size_t phi_bytes = as * L->q * plane;
+  const int pv_start = L->pvcur;
+  // Where a call leaves phi and the outlet values: the arrays it found them in
+  // (one toggle of the outlet buffers per launch, so a stop after an odd
+  // number of passes leaves both in the other one).
+  auto settle = [&]() -> hlbm_status {
+    if (L->pvcur != pv_start) {
+      HIP_TRY(hipMemcpyAsync(L->pv[pv_start], L->pv[L->pvcur], as * L->q * L->gplane, hipMemcpyDeviceToDevice,
+                             L->stream));
+      L->pvcur = pv_start;
+    }
+    return settle_arrays(L, L->phi, L->phi2, start, as * L->q * plane);
+  };
   int64_t iters = o->max_iters + (o->max_iters & 1);
   int64_t M = o->check_every > 0 ? o->check_every : 100;
   M += (M & 1);
@@ -978,7 +989,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
           rep->iters = done;
           rep->residual = res;
         }
-        if ((s = settle_arrays(L, L->phi, L->phi2, start, phi_bytes)) != HLBM_OK) return s;
+        if ((s = settle()) != HLBM_OK) return s;
         return fail(HLBM_E_DIVERGED, "adjoint diverged after %lld iterations (residual %g, smallest %g)",
                     (long long)L->adj_iters, res, min_res);
       }
@@ -988,7 +999,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
       }
     }
   }
-  if ((s = settle_arrays(L, L->phi, L->phi2, start, phi_bytes)) != HLBM_OK) return s;
+  if ((s = settle()) != HLBM_OK) return s;
   if (o->tol > 0.0) HIP_TRY(hipStreamSynchronize(L->stream));
   if (rep) {
     rep->iters = done;
