@@ -184,20 +184,36 @@ typedef struct {
 hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out);
 /* Free every device buffer of the handle (synchronises its stream). */
 void hlbm_destroy(hlbm_lattice lat);
-/* Device bytes a lattice of this descriptor holds at most for one query:
- * populations (with the second array of the multi-step passes, which is held
- * only while a quarter of the device's memory stays free), porosity, outlet
- * values, reduction partials and the steady-check snapshot; the objective's region buffers for region_cells cells of
+/* The same, holding at most optional_limit bytes of the arrays that only the
+ * multi-step passes use (see hlbm_optional_bytes; hlbm_create: no limit).
+ * Without them the lattice takes single steps, with the same results. */
+hlbm_status hlbm_create_bounded(const hlbm_desc* desc, uint64_t optional_limit, hlbm_lattice* out);
+/* Device bytes a lattice of this descriptor needs at most for one query:
+ * populations, porosity, outlet values, reduction partials and the steady-
+ * check snapshot; the objective's region buffers for region_cells cells of
  * kind `objective` (0 cells: no objective); with_window != 0 the FP64 window
  * sums; with_adjoint != 0 the adjoint populations, frozen data, gradient data
- * and residual snapshot.  A velocity probe and the forward tangent's buffers
- * are not included.  Equals hlbm_device_bytes after such a query (primal
+ * and residual snapshot.  A velocity probe, the forward tangent's buffers and
+ * the optional arrays (hlbm_optional_bytes) are not included.  Equals hlbm_device_bytes after such a query (primal
  * with steady checks and window, adjoint with residual checks, gradient).
  * Errors: INVALID (descriptor, region_cells outside [0, n], kind). */
 hlbm_status hlbm_footprint_bytes(const hlbm_desc* desc, int with_window, int with_adjoint,
                                  int64_t region_cells, int32_t objective, uint64_t* bytes);
-/* Device bytes the handle holds now (every buffer it has allocated). */
+/* Device bytes the handle holds now: every buffer it has allocated except the
+ * optional arrays. */
 hlbm_status hlbm_device_bytes(hlbm_lattice lat, uint64_t* bytes);
+/* Optional arrays: a second population array (and, in FP64, one step's region
+ * records), taken at creation, and with_adjoint != 0 a second phi array, taken
+ * by the first adjoint solve.  The multi-step passes use them.  A lattice takes
+ * them only where a quarter of the device's memory stays free beside them,
+ * gives them back when a buffer it needs does not fit otherwise, and runs single
+ * steps without them.  hlbm_optional_bytes: the bytes a lattice of this
+ * descriptor takes at most; hlbm_optional_held: those the handle holds now;
+ * hlbm_optional_release: gives them back (synchronises the stream) and takes
+ * none from then on. */
+hlbm_status hlbm_optional_bytes(const hlbm_desc* desc, int with_adjoint, uint64_t* bytes);
+hlbm_status hlbm_optional_held(hlbm_lattice lat, uint64_t* bytes);
+hlbm_status hlbm_optional_release(hlbm_lattice lat);
 
 /* ---- geometry and initial state (rows a1, a2) --------------------------- */
 

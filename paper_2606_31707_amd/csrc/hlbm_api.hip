@@ -62,14 +62,17 @@ void lat_free(hlbm_lattice_s* L, void* p) {
   L->allocs.erase(p);
   dev_free(p);
 }
-// The second arrays of the multi-step passes hold nothing between calls: they
-// are given back when a buffer that is needed does not fit beside them.
+// The arrays of the multi-step passes hold nothing between calls: they are
+// given back when a buffer that is needed does not fit beside them.  They are
+// no part of the footprint and of the handle's record.
 bool give_back_second_arrays(hlbm_lattice_s* L) {
-  if (!L->f2 && !L->phi2) return false;
+  if (L->optional_held == 0) return false;
   (void)hipStreamSynchronize(L->stream);
-  lat_free(L, L->f2);
-  lat_free(L, L->phi2);
-  L->f2 = L->phi2 = nullptr;
+  dev_free(L->f2);
+  dev_free(L->rcopy2);
+  dev_free(L->phi2);
+  L->f2 = L->rcopy2 = L->phi2 = nullptr;
+  L->optional_held = 0;
   return true;
 }
 hlbm_status lat_alloc(hlbm_lattice_s* L, void** p, size_t bytes) {
@@ -79,15 +82,21 @@ hlbm_status lat_alloc(hlbm_lattice_s* L, void** p, size_t bytes) {
   if (s == HLBM_OK) L->allocs[*p] = bytes ? bytes : 256;
   return s;
 }
-// A second array is taken only where a quarter of the device's memory stays
-// free beside it: without it the lattice runs single steps in place.
-void lat_alloc_second(hlbm_lattice_s* L, void** p, size_t bytes) {
+// A second array (and, with extra_bytes, what the passes need beside it) is
+// taken only within the handle's limit and where a quarter of the device's
+// memory stays free: without it the lattice runs single steps in place.
+void lat_alloc_second(hlbm_lattice_s* L, void** p, size_t bytes, void** extra = nullptr, size_t extra_bytes = 0) {
+  const size_t all = bytes + extra_bytes;
   size_t avail = 0, total = 0;
-  if (*p || hipMemGetInfo(&avail, &total) != hipSuccess || avail < bytes || avail - bytes < total / 4) return;
-  void* q = nullptr;
-  if (dev_alloc(&q, bytes) != HLBM_OK) return;
-  *p = q;
-  L->allocs[q] = bytes;
+  if (*p || L->optional_limit - L->optional_held < all || hipMemGetInfo(&avail, &total) != hipSuccess ||
+      avail < all || avail - all < total / 4)
+    return;
+  void *a = nullptr, *b = nullptr;
+  if (dev_alloc(&a, bytes) != HLBM_OK) return;
+  if (extra_bytes && dev_alloc(&b, extra_bytes) != HLBM_OK) return dev_free(a);
+  *p = a;
+  if (extra_bytes) *extra = b;
+  L->optional_held += all;
 }
 
 // Scratch of the allocation-free entry point (hlbm_set_porosity_noalloc): a
@@ -375,13 +384,40 @@ hlbm_status hlbm_device_bytes(hlbm_lattice L, uint64_t* bytes) {
   return HLBM_OK;
 }
 
+hlbm_status hlbm_optional_bytes(const hlbm_desc* desc, int with_adjoint, uint64_t* bytes) {
+  hlbm_status s = validate_desc(desc);
+  if (s != HLBM_OK) return s;
+  if (!bytes) return fail(HLBM_E_INVALID, "null output");
+  *bytes = pass_bytes_primal(desc) + (with_adjoint ? pass_bytes_adjoint(desc) : 0);
+  return HLBM_OK;
+}
+
+hlbm_status hlbm_optional_held(hlbm_lattice L, uint64_t* bytes) {
+  CHECK_LAT(L);
+  if (!bytes) return fail(HLBM_E_INVALID, "null output");
+  *bytes = L->optional_held;
+  return HLBM_OK;
+}
+
+hlbm_status hlbm_optional_release(hlbm_lattice L) {
+  CHECK_LAT(L);
+  give_back_second_arrays(L);
+  L->optional_limit = 0;
+  return HLBM_OK;
+}
+
 hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out) {
+  return hlbm_create_bounded(desc, UINT64_MAX, out);
+}
+
+hlbm_status hlbm_create_bounded(const hlbm_desc* desc, uint64_t optional_limit, hlbm_lattice* out) {
   if (!out) return fail(HLBM_E_INVALID, "null output handle");
   *out = nullptr;
   hlbm_status s = validate_desc(desc);
   if (s != HLBM_OK) return s;
   hlbm_lattice_s* L = new hlbm_lattice_s();
   L->desc = *desc;
+  L->optional_limit = optional_limit;
   if (L->desc.stencil == HLBM_D2Q9) L->desc.bc_z = HLBM_BC_PERIODIC;
   L->q = q_of(desc->stencil);
   L->dim = dim_of(desc->stencil);
@@ -425,10 +461,8 @@ hlbm_status hlbm_create(const hlbm_desc* desc, hlbm_lattice* out) {
   if ((s = lat_alloc(L, &L->f, L->ssize * L->q * L->plane)) != HLBM_OK) return bail(s);
   if ((s = lat_alloc(L, &L->dpor, L->dsize * L->plane)) != HLBM_OK) return bail(s);
   if (primal_passes_of(&L->desc)) {
-    lat_alloc_second(L, &L->f2, L->ssize * L->q * L->plane);
-    if (L->f2 && desc->precision == HLBM_FP64 &&
-        (s = lat_alloc(L, &L->rcopy2, L->asize * region_copy_stride(L->q, (int)L->asize) * L->gplane)) != HLBM_OK)
-      return bail(s);
+    const size_t f2 = L->ssize * L->q * L->plane;
+    lat_alloc_second(L, &L->f2, f2, &L->rcopy2, pass_bytes_primal(&L->desc) - f2);
   }
   if ((s = lat_alloc(L, &L->ghost, L->ssize * L->q * L->gplane)) != HLBM_OK) return bail(s);
   if ((s = ensure_partials(L, 2 * n_blocks(L) + 8)) != HLBM_OK) return bail(s);

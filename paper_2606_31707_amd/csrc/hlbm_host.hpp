@@ -61,7 +61,7 @@ inline int nb_of(int stencil) { return 1 + dim_of(stencil) + nsym_of(stencil); }
 // what the saved bytes give (192x96x64 21.5 us a step, 32.5 with passes;
 // 756x168x84 with walls 158 and 198; 768x384x128 565 and 478); for the adjoint
 // also the HRR collision (its frozen data would have to wait for the later
-// levels as well).  J_MEA takes single steps too, but counts the second phi
+// levels as well).  J_MEA takes single steps too, but holds the second phi
 // array: a window can be given another objective.  The 3D adjoint passes are
 // bound by their instructions and pay only in FP64 beyond the caches (us an
 // iteration, single / pass: FP64 756x168x84 798 / 533, 300x128x64 175 / 137,
@@ -124,10 +124,6 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
                           (uint64_t)desc->nz;
   // populations, porosity, outlet values, reduction partials, steady-check snapshot
   uint64_t b = P * (q * ss + ds) + G * q * ss + 8 * (2 * blocks + 8) + 8 * P * dim;
-  if (primal_passes_of(desc)) {
-    b += P * q * ss;  // second population array (multi-step passes)
-    if (desc->precision == HLBM_FP64) b += G * (uint64_t)region_copy_stride(q, (int)as) * as;  // a step's region records
-  }
   if (region_cells > 0) {  // objective terms and adjoint source over the region
     const uint64_t rp = (uint64_t)round_up(region_cells, 128);
     b += 2 * 8 * rp * ncoef;
@@ -149,10 +145,26 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
     b += P * 8 * (dim + 2);                             // gradient data
     b += G * (8 * (1 + dim) + 2 * as * q);              // outlet data, outlet adjoint values
     b += P * as * q;                                    // residual snapshot
-    if (adjoint_passes_of(desc)) b += P * as * q;  // second phi array (multi-iteration passes)
   }
   *bytes = b;
   return nullptr;
+}
+
+// Device bytes of the arrays that only the multi-step passes use, which a
+// lattice does without where they do not fit: the second population array
+// and, in FP64, a window step's region records; the second phi array.
+inline uint64_t pass_bytes_primal(const hlbm_desc* d) {
+  if (!primal_passes_of(d)) return 0;
+  const uint64_t q = q_of(d->stencil), as = asize_of(d->precision);
+  uint64_t b = (uint64_t)plane_stride((int64_t)d->nx * d->ny * d->nz, ssize_of(d->precision)) * q * ssize_of(d->precision);
+  if (d->precision == HLBM_FP64)
+    b += (uint64_t)round_up((int64_t)d->ny * d->nz, 128) * (uint64_t)region_copy_stride((int)q, (int)as) * as;
+  return b;
+}
+inline uint64_t pass_bytes_adjoint(const hlbm_desc* d) {
+  if (!adjoint_passes_of(d)) return 0;
+  return (uint64_t)plane_stride((int64_t)d->nx * d->ny * d->nz, ssize_of(d->precision)) * asize_of(d->precision) *
+         (uint64_t)q_of(d->stencil);
 }
 
 }  // namespace hlbm

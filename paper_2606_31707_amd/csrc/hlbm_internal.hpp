@@ -111,6 +111,9 @@ struct hlbm_lattice_s {
 
   // every device buffer the handle owns, with its size (hlbm_device_bytes)
   std::unordered_map<void*, size_t> allocs;
+  // Arrays of the multi-step passes (f2, rcopy2, phi2), which the handle does
+  // without where they do not fit: bytes held, and the most it may hold.
+  uint64_t optional_held = 0, optional_limit = UINT64_MAX;
 
   // device the handle was created on, and the device address of that GPU's
   // copy of the library's scratch array (the allocation-free entry point)

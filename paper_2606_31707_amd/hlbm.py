@@ -43,6 +43,7 @@ EXPORTS = [
     "hlbm_set_probe", "hlbm_get_probe", "hlbm_reconfigure", "hlbm_group_create", "hlbm_group_destroy",
     "hlbm_group_set", "hlbm_group_step", "hlbm_group_synchronize", "hlbm_run_tangent",
     "hlbm_copy_probe", "hlbm_device_bytes", "hlbm_set_porosity_noalloc",
+    "hlbm_create_bounded", "hlbm_optional_bytes", "hlbm_optional_held", "hlbm_optional_release",
 ]
 
 GROUP_PRIMAL, GROUP_PRIMAL_WINDOW, GROUP_ADJOINT = 0, 1, 2
@@ -132,6 +133,10 @@ def open_library(path: str):
         "hlbm_destroy": (None, [vp]),
         "hlbm_footprint_bytes": (i32, [P(Desc), i32, i32, i64, i32, P(C.c_uint64)]),
         "hlbm_device_bytes": (i32, [vp, P(C.c_uint64)]),
+        "hlbm_create_bounded": (i32, [P(Desc), C.c_uint64, P(vp)]),
+        "hlbm_optional_bytes": (i32, [P(Desc), i32, P(C.c_uint64)]),
+        "hlbm_optional_held": (i32, [vp, P(C.c_uint64)]),
+        "hlbm_optional_release": (i32, [vp]),
         "hlbm_set_porosity": (i32, [vp, vp, i64, i32]),
         "hlbm_set_porosity_noalloc": (i32, [vp, vp, i64]),
         "hlbm_build_cylinder": (i32, [vp, dbl, dbl, dbl, vp, i64, i32, i32, dbl, dbl]),
@@ -228,7 +233,7 @@ def make_desc(stencil=D2Q9, precision=FP64, nx=32, ny=16, nz=1, tau=0.8, cs=0.0,
 
 
 def footprint_bytes(desc: Desc, with_window=True, with_adjoint=True, region_cells=0, objective=OBJ_FFA) -> int:
-    """Device bytes one query on a lattice of this descriptor holds at most
+    """Device bytes one query on a lattice of this descriptor needs at most
     (objective region of region_cells cells of the given kind)."""
     lib = load_library()
     out = C.c_uint64()
@@ -237,14 +242,27 @@ def footprint_bytes(desc: Desc, with_window=True, with_adjoint=True, region_cell
     return int(out.value)
 
 
-class Lattice:
-    """One lattice on the GPU (owns an hlbm_lattice handle)."""
+def optional_bytes(desc: Desc, with_adjoint=True) -> int:
+    """Device bytes of the arrays of the multi-step passes that a lattice of this descriptor
+    takes at most beside its footprint; without them it runs single steps."""
+    lib = load_library()
+    out = C.c_uint64()
+    _check(lib.hlbm_optional_bytes(C.byref(desc), int(with_adjoint), C.byref(out)))
+    return int(out.value)
 
-    def __init__(self, desc: Desc | None = None, lib=None, **kw):
+
+class Lattice:
+    """One lattice on the GPU (owns an hlbm_lattice handle).  optional_limit: the most bytes of
+    the arrays of the multi-step passes it may hold (None: no limit; see optional_bytes)."""
+
+    def __init__(self, desc: Desc | None = None, lib=None, optional_limit=None, **kw):
         self._lib = lib if lib is not None else load_library()
         self.desc = desc if desc is not None else make_desc(**kw)
         h = C.c_void_p()
-        _check(self._lib.hlbm_create(C.byref(self.desc), C.byref(h)))
+        if optional_limit is None:
+            _check(self._lib.hlbm_create(C.byref(self.desc), C.byref(h)))
+        else:
+            _check(self._lib.hlbm_create_bounded(C.byref(self.desc), int(optional_limit), C.byref(h)))
         self._h = h
         self.q = 9 if self.desc.stencil == D2Q9 else 19
         self.n = self.desc.nx * self.desc.ny * self.desc.nz
@@ -417,10 +435,20 @@ class Lattice:
         self.desc.tau, self.desc.smagorinsky_cs, self.desc.u_in = tau, cs, u_in
 
     def device_bytes(self) -> int:
-        """Device bytes this lattice holds now."""
+        """Device bytes this lattice holds now, the optional arrays apart."""
         out = C.c_uint64()
         _check(self._lib.hlbm_device_bytes(self._h, C.byref(out)))
         return int(out.value)
+
+    def optional_held(self) -> int:
+        """Device bytes of the arrays of the multi-step passes this lattice holds now."""
+        out = C.c_uint64()
+        _check(self._lib.hlbm_optional_held(self._h, C.byref(out)))
+        return int(out.value)
+
+    def optional_release(self):
+        """Gives the arrays of the multi-step passes back and takes none from then on."""
+        _check(self._lib.hlbm_optional_release(self._h))
 
     def copy_probe(self, pattern=0, streaming=False, n_launches=20) -> float:
         """Mean microseconds per launch of the bandwidth probe (a plain sweep's

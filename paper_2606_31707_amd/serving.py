@@ -274,6 +274,8 @@ class GPUBackend:
         self.group = H.Group(stream=self.group_stream.cuda_stream)
         self.pool: OrderedDict = OrderedDict()  # key -> list of idle lattices
         self.resident = 0
+        self.optional = {}  # lattices -> bytes of optional arrays (multi-step passes) they may hold
+        self.cap = None     # device-memory cap of the last admission
         self._fp = {}
 
     def _key(self, q: Query):
@@ -306,6 +308,7 @@ class GPUBackend:
         """True if the query fits: a pooled lattice of its shape, or room for a
         new one after evicting idle lattices."""
         k = self._key(q)
+        self.cap = cap
         if self.pool.get(k):
             return True
         need = self.footprint(q)
@@ -318,9 +321,23 @@ class GPUBackend:
             if lst:
                 lat = lst.pop()
                 self.resident -= self.footprint_key(k)
+                self.optional.pop(lat, None)
                 lat.close()
                 return True
         return False
+
+    def _optional_room(self, need: int, want: int) -> int:
+        """Bytes of optional arrays a new lattice of footprint `need` may hold under the cap.  Where the
+        others' leave no room for the footprint itself, they are given back, oldest first."""
+        if self.cap is None:
+            return want
+        room = self.cap - self.resident - need - sum(self.optional.values())
+        for lat in list(self.optional):
+            if room >= 0:
+                break
+            lat.optional_release()
+            room += self.optional.pop(lat)
+        return max(0, min(want, room))
 
     def footprint_key(self, k):
         return self._fp[k]
@@ -338,7 +355,10 @@ class GPUBackend:
             else:
                 stream = self.streams[self._next_stream % len(self.streams)].cuda_stream
                 self._next_stream += 1
-            lat = H.Lattice(self._desc(q, stream))
+            desc = self._desc(q, stream)
+            room = self._optional_room(self.footprint(q), H.optional_bytes(desc))
+            lat = H.Lattice(desc, optional_limit=room)
+            self.optional[lat] = room
             self.resident += self.footprint(q)
         rng = np.random.default_rng(q.seed)
         noise = rng.uniform(0.0, 0.05, q.cells)
