@@ -205,12 +205,13 @@ hlbm_status hlbm_device_bytes(hlbm_lattice lat, uint64_t* bytes);
 /* Optional arrays: a second population array (and, in FP64, one step's region
  * records), taken at creation, and with_adjoint != 0 a second phi array, taken
  * by the first adjoint solve.  The multi-step passes use them.  A lattice takes
- * them only where a quarter of the device's memory stays free beside them,
- * gives them back when a buffer it needs does not fit otherwise, and runs single
- * steps without them.  hlbm_optional_bytes: the bytes a lattice of this
+ * them only where half of the device's memory stays free beside them, and runs
+ * single steps without them.  When an allocation of the library does not fit,
+ * the arrays of every lattice on the device are given back (other threads'
+ * calls that are using them are waited for).  hlbm_optional_bytes: the bytes a lattice of this
  * descriptor takes at most; hlbm_optional_held: those the handle holds now;
- * hlbm_optional_release: gives them back (synchronises the stream) and takes
- * none from then on. */
+ * hlbm_optional_release: gives them back (waits for the device) and takes none
+ * from then on, for a program that needs the room for buffers of its own. */
 hlbm_status hlbm_optional_bytes(const hlbm_desc* desc, int with_adjoint, uint64_t* bytes);
 hlbm_status hlbm_optional_held(hlbm_lattice lat, uint64_t* bytes);
 hlbm_status hlbm_optional_release(hlbm_lattice lat);

@@ -2,6 +2,7 @@
 // lifetime, argument checks, and the host-side loops of the three phases of
 // the paper's Algorithm 1 (primal with window, adjoint, gradient assembly).
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -40,19 +41,93 @@ hlbm_status fail(hlbm_status s, const char* fmt, ...) {
     if ((L) == nullptr) return fail(HLBM_E_INVALID, "null lattice"); \
   } while (0)
 
+void dev_free(void* p) {
+  if (p) (void)hipFree(p);
+}
+
+// The arrays of the multi-step passes (f2, rcopy2, phi2) hold nothing between
+// calls, are no part of a handle's footprint, and are given back, whichever
+// handle holds them, when an allocation of the library does not fit beside
+// them.  Calls that launch passes mark their handles (PassScope), allocate
+// nothing in the meantime but their own optional arrays, and are waited for.
+std::mutex g_opt_mu;
+std::condition_variable g_opt_cv;
+hlbm_lattice_s* g_opt_head = nullptr;
+
+void opt_register(hlbm_lattice_s* L) {
+  std::lock_guard<std::mutex> lock(g_opt_mu);
+  L->opt_next = g_opt_head;
+  if (g_opt_head) g_opt_head->opt_prev = L;
+  g_opt_head = L;
+}
+void opt_unregister(hlbm_lattice_s* L) {
+  std::lock_guard<std::mutex> lock(g_opt_mu);
+  if (L->opt_next) L->opt_next->opt_prev = L->opt_prev;
+  if (L->opt_prev) L->opt_prev->opt_next = L->opt_next;
+  if (g_opt_head == L) g_opt_head = L->opt_next;
+  L->opt_next = L->opt_prev = nullptr;
+}
+struct PassScope {
+  hlbm_lattice_s* const* lats;
+  int n;
+  PassScope(hlbm_lattice_s* const* l, int count) : lats(l), n(count) {
+    std::lock_guard<std::mutex> lock(g_opt_mu);
+    for (int i = 0; i < n; ++i) lats[i]->opt_busy += 1;
+  }
+  ~PassScope() {
+    std::lock_guard<std::mutex> lock(g_opt_mu);
+    for (int i = 0; i < n; ++i) lats[i]->opt_busy -= 1;
+    g_opt_cv.notify_all();
+  }
+  PassScope(const PassScope&) = delete;
+  PassScope& operator=(const PassScope&) = delete;
+};
+// (under g_opt_mu, the device idle)
+void opt_drop(hlbm_lattice_s* L) {
+  dev_free(L->f2);
+  dev_free(L->rcopy2);
+  dev_free(L->phi2);
+  L->f2 = L->rcopy2 = L->phi2 = nullptr;
+  L->optional_held = 0;
+}
+// Gives back the optional arrays of every handle on the current device.  The
+// device is waited for: groups run passes on streams of their own.
+bool opt_reclaim() {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::unique_lock<std::mutex> lock(g_opt_mu);
+  bool any = false;
+  for (hlbm_lattice_s* L = g_opt_head; L;) {
+    if (L->device != dev || L->optional_held == 0) {
+      L = L->opt_next;
+    } else if (L->opt_busy > 0) {
+      g_opt_cv.wait(lock);
+      L = g_opt_head;  // the list may have changed
+    } else {
+      if (hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        return any;
+      }
+      opt_drop(L);
+      any = true;
+    }
+  }
+  return any;
+}
+
 hlbm_status dev_alloc(void** p, size_t bytes) {
   if (*p) return HLBM_OK;
   hipError_t e = hipMalloc(p, bytes ? bytes : 256);
+  if (e == hipErrorOutOfMemory && opt_reclaim()) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes ? bytes : 256);
+  }
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
     return fail(HLBM_E_OOM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
   }
   return HLBM_OK;
-}
-
-void dev_free(void* p) {
-  if (p) (void)hipFree(p);
 }
 
 // Buffers owned by a lattice are allocated and freed through these, which
@@ -62,38 +137,27 @@ void lat_free(hlbm_lattice_s* L, void* p) {
   L->allocs.erase(p);
   dev_free(p);
 }
-// The arrays of the multi-step passes hold nothing between calls: they are
-// given back when a buffer that is needed does not fit beside them.  They are
-// no part of the footprint and of the handle's record.
-bool give_back_second_arrays(hlbm_lattice_s* L) {
-  if (L->optional_held == 0) return false;
-  (void)hipStreamSynchronize(L->stream);
-  dev_free(L->f2);
-  dev_free(L->rcopy2);
-  dev_free(L->phi2);
-  L->f2 = L->rcopy2 = L->phi2 = nullptr;
-  L->optional_held = 0;
-  return true;
-}
 hlbm_status lat_alloc(hlbm_lattice_s* L, void** p, size_t bytes) {
   if (*p) return HLBM_OK;
   hlbm_status s = dev_alloc(p, bytes);
-  if (s == HLBM_E_OOM && give_back_second_arrays(L)) s = dev_alloc(p, bytes);
   if (s == HLBM_OK) L->allocs[*p] = bytes ? bytes : 256;
   return s;
 }
-// A second array (and, with extra_bytes, what the passes need beside it) is
-// taken only within the handle's limit and where a quarter of the device's
-// memory stays free: without it the lattice runs single steps in place.
-void lat_alloc_second(hlbm_lattice_s* L, void** p, size_t bytes, void** extra = nullptr, size_t extra_bytes = 0) {
+// An optional array (and, with extra_bytes, what the passes need beside it) is
+// taken only within the handle's limit and where half of the device's memory
+// stays free: without it the lattice runs single steps in place.
+void lat_alloc_optional(hlbm_lattice_s* L, void** p, size_t bytes, void** extra = nullptr, size_t extra_bytes = 0) {
   const size_t all = bytes + extra_bytes;
   size_t avail = 0, total = 0;
   if (*p || L->optional_limit - L->optional_held < all || hipMemGetInfo(&avail, &total) != hipSuccess ||
-      avail < all || avail - all < total / 4)
+      !optional_fits(avail, total, all))
     return;
   void *a = nullptr, *b = nullptr;
-  if (dev_alloc(&a, bytes) != HLBM_OK) return;
-  if (extra_bytes && dev_alloc(&b, extra_bytes) != HLBM_OK) return dev_free(a);
+  if (hipMalloc(&a, bytes) != hipSuccess || (extra_bytes && hipMalloc(&b, extra_bytes) != hipSuccess)) {
+    (void)hipGetLastError();
+    dev_free(a);
+    return;
+  }
   *p = a;
   if (extra_bytes) *extra = b;
   L->optional_held += all;
@@ -395,14 +459,19 @@ hlbm_status hlbm_optional_bytes(const hlbm_desc* desc, int with_adjoint, uint64_
 hlbm_status hlbm_optional_held(hlbm_lattice L, uint64_t* bytes) {
   CHECK_LAT(L);
   if (!bytes) return fail(HLBM_E_INVALID, "null output");
+  std::lock_guard<std::mutex> lock(g_opt_mu);
   *bytes = L->optional_held;
   return HLBM_OK;
 }
 
 hlbm_status hlbm_optional_release(hlbm_lattice L) {
   CHECK_LAT(L);
-  give_back_second_arrays(L);
+  std::unique_lock<std::mutex> lock(g_opt_mu);
+  while (L->opt_busy > 0) g_opt_cv.wait(lock);
   L->optional_limit = 0;
+  if (L->optional_held == 0) return HLBM_OK;
+  HIP_TRY(hipDeviceSynchronize());  // groups run passes on streams of their own
+  opt_drop(L);
   return HLBM_OK;
 }
 
@@ -462,7 +531,7 @@ hlbm_status hlbm_create_bounded(const hlbm_desc* desc, uint64_t optional_limit, 
   if ((s = lat_alloc(L, &L->dpor, L->dsize * L->plane)) != HLBM_OK) return bail(s);
   if (primal_passes_of(&L->desc)) {
     const size_t f2 = L->ssize * L->q * L->plane;
-    lat_alloc_second(L, &L->f2, f2, &L->rcopy2, pass_bytes_primal(&L->desc) - f2);
+    lat_alloc_optional(L, &L->f2, f2, &L->rcopy2, pass_bytes_primal(&L->desc) - f2);
   }
   if ((s = lat_alloc(L, &L->ghost, L->ssize * L->q * L->gplane)) != HLBM_OK) return bail(s);
   if ((s = ensure_partials(L, 2 * n_blocks(L) + 8)) != HLBM_OK) return bail(s);
@@ -480,12 +549,14 @@ hlbm_status hlbm_create_bounded(const hlbm_desc* desc, uint64_t optional_limit, 
     return bail(fail(HLBM_E_DEVICE, "porosity fill failed"));
   if (launch_init(L, 1.0, nullptr) != hipSuccess) return bail(fail(HLBM_E_DEVICE, "init failed"));
   if (hipStreamSynchronize(L->stream) != hipSuccess) return bail(fail(HLBM_E_DEVICE, "sync failed"));
+  opt_register(L);
   *out = L;
   return HLBM_OK;
 }
 
 void hlbm_destroy(hlbm_lattice L) {
   if (!L) return;
+  opt_unregister(L);
   (void)hipStreamSynchronize(L->stream);
   void* bufs[] = {L->f,   L->f2,    L->dpor,  L->ghost, L->acc_rho, L->acc_j, L->acc_f, L->acc_tau, L->acc_obj, L->acc_pend,
                   L->phi, L->phi2, L->prep,  L->src,   L->gdat,    L->oprep, L->pv[0], L->pv[1],   L->snap,
@@ -793,6 +864,7 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
   const int64_t nb = n_blocks(L);
   // Multi-step passes swap the two population arrays: a captured run, whose
   // replays start from the same array every time, takes single steps.
+  PassScope scope(&L, 1);
   const bool multi = L->f2 != nullptr && !stream_capturing(L->stream);
   void* const start = L->f;
   const size_t state_bytes = L->ssize * L->q * L->plane;
@@ -970,7 +1042,11 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
   }
   const bool passes = adjoint_passes_of(&L->desc);
   const bool capturing = stream_capturing(L->stream);
-  if (passes && !capturing) lat_alloc_second(L, &L->phi2, as * L->q * plane);
+  PassScope scope(&L, 1);
+  if (passes && !capturing && !L->phi2_asked) {
+    L->phi2_asked = 1;
+    lat_alloc_optional(L, &L->phi2, as * L->q * plane);
+  }
   const bool multi =
       L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !capturing;
   void* const start = L->phi;
@@ -1238,6 +1314,24 @@ namespace {
 hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int32_t* modes, int32_t count) {
   hlbm_status s;
   const size_t ps = packed_primal_size(), as = packed_adjoint_size();
+  size_t count_a = 0;
+  for (int i = 0; i < count; ++i) count_a += modes[i] == HLBM_GROUP_ADJOINT;
+  auto room = [&](size_t m, size_t esz, void** tab, int** first, size_t* cap) -> hlbm_status {
+    if (m <= *cap) return HLBM_OK;
+    dev_free(*tab);
+    dev_free(*first);
+    *tab = nullptr;
+    *first = nullptr;
+    *cap = 0;
+    hlbm_status st;
+    if ((st = dev_alloc(tab, esz * m)) != HLBM_OK) return st;
+    if ((st = dev_alloc((void**)first, sizeof(int) * 2 * m)) != HLBM_OK) return st;
+    *cap = m;
+    return HLBM_OK;
+  };
+  if ((s = room(count - count_a, ps, &g->tab_primal, &g->first_primal, &g->cap_primal)) != HLBM_OK) return s;
+  if ((s = room(count_a, as, &g->tab_adjoint, &g->first_adjoint, &g->cap_adjoint)) != HLBM_OK) return s;
+  PassScope scope(lats, count);
   std::vector<unsigned char> tp, ta;
   std::vector<int> fp, fa;
   std::vector<hlbm_lattice_s*> lp, la;
@@ -1282,27 +1376,15 @@ hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int
   const int n_primal = (int)fp.size(), n_adjoint = (int)fa.size();
   fp.insert(fp.end(), gp.begin(), gp.end());  // the second half: first blocks of a pass
   fa.insert(fa.end(), ga.begin(), ga.end());
-  auto upload = [&](std::vector<unsigned char>& t, std::vector<int>& f, size_t esz, void** tab, int** first,
-                    size_t* cap) -> hlbm_status {
+  auto upload = [&](std::vector<unsigned char>& t, std::vector<int>& f, size_t esz, void* tab, int* first) -> hlbm_status {
     const size_t m = f.size() / 2;
     if (m == 0) return HLBM_OK;
-    if (m > *cap) {
-      dev_free(*tab);
-      dev_free(*first);
-      *tab = nullptr;
-      *first = nullptr;
-      *cap = 0;
-      hlbm_status st;
-      if ((st = dev_alloc(tab, esz * m)) != HLBM_OK) return st;
-      if ((st = dev_alloc((void**)first, sizeof(int) * 2 * m)) != HLBM_OK) return st;
-      *cap = m;
-    }
-    HIP_TRY(hipMemcpyAsync(*tab, t.data(), esz * m, hipMemcpyHostToDevice, g->stream));
-    HIP_TRY(hipMemcpyAsync(*first, f.data(), sizeof(int) * 2 * m, hipMemcpyHostToDevice, g->stream));
+    HIP_TRY(hipMemcpyAsync(tab, t.data(), esz * m, hipMemcpyHostToDevice, g->stream));
+    HIP_TRY(hipMemcpyAsync(first, f.data(), sizeof(int) * 2 * m, hipMemcpyHostToDevice, g->stream));
     return HLBM_OK;
   };
-  if ((s = upload(tp, fp, ps, &g->tab_primal, &g->first_primal, &g->cap_primal)) != HLBM_OK) return s;
-  if ((s = upload(ta, fa, as, &g->tab_adjoint, &g->first_adjoint, &g->cap_adjoint)) != HLBM_OK) return s;
+  if ((s = upload(tp, fp, ps, g->tab_primal, g->first_primal)) != HLBM_OK) return s;
+  if ((s = upload(ta, fa, as, g->tab_adjoint, g->first_adjoint)) != HLBM_OK) return s;
   HIP_TRY(hipStreamSynchronize(g->stream));  // host tables go out of scope
   void** second = count ? new void*[count] : nullptr;
   for (int i = 0; i < count; ++i) second[i] = modes[i] == HLBM_GROUP_ADJOINT ? lats[i]->phi2 : lats[i]->f2;
@@ -1462,6 +1544,7 @@ extern "C" hlbm_status hlbm_group_step(hlbm_group g, int64_t n) {
   }
   // Two-step passes need the second arrays that the tables name (they may have
   // been given back for memory); a caller's capture takes single steps.
+  PassScope scope(g->members, g->count);
   bool passes = !stream_capturing(g->stream);
   for (int i = 0; i < g->count; ++i) {
     const hlbm_lattice_s* L = g->members[i];

@@ -167,4 +167,11 @@ inline uint64_t pass_bytes_adjoint(const hlbm_desc* d) {
          (uint64_t)q_of(d->stencil);
 }
 
+// Whether `bytes` of such arrays may be taken: half of the device stays free
+// for what is needed, by this library or by others, which cannot ask for them
+// back.
+inline bool optional_fits(uint64_t avail, uint64_t total, uint64_t bytes) {
+  return avail >= bytes && avail - bytes >= total / 2;
+}
+
 }  // namespace hlbm

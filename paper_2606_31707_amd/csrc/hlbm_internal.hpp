@@ -114,6 +114,11 @@ struct hlbm_lattice_s {
   // Arrays of the multi-step passes (f2, rcopy2, phi2), which the handle does
   // without where they do not fit: bytes held, and the most it may hold.
   uint64_t optional_held = 0, optional_limit = UINT64_MAX;
+  int phi2_asked = 0;  // phi2 is asked for once, by the first adjoint solve outside a capture
+  // list of all handles, and the calls that are using this one's optional
+  // arrays (both under the list's mutex)
+  hlbm_lattice_s *opt_next = nullptr, *opt_prev = nullptr;
+  int opt_busy = 0;
 
   // device the handle was created on, and the device address of that GPU's
   // copy of the library's scratch array (the allocation-free entry point)

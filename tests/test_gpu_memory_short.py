@@ -1,0 +1,139 @@
+"""On a device with little free memory the optional arrays make room: a host copy's staging, a
+new lattice, a bandwidth probe and another thread's creation succeed where they fit without
+them, and the lattices that lose theirs go on with the same results."""
+import threading
+
+import numpy as np
+import pytest
+
+from tests.pairs import say
+
+pytestmark = pytest.mark.gpu
+GB = 1 << 30
+
+
+def lat(H, nx, ny, prec, **kw):
+    L = H.Lattice(precision=prec, nx=nx, ny=ny, tau=0.6, u_in=0.04, **kw)
+    L.build_cylinder(nx / 4, (ny - 1) / 2, ny / 8)
+    L.init_equilibrium()
+    return L
+
+
+class Filled:
+    """Holds device memory (untouched) until `left` bytes are free."""
+
+    def __init__(self, left):
+        import torch
+        self.torch, self.blocks = torch, []
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        size = 64 * GB
+        while size >= 1 << 25:
+            free = torch.cuda.mem_get_info()[0]
+            if free - left >= size:
+                self.blocks.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+            else:
+                size >>= 1
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *_):
+        self.blocks.clear()
+        self.torch.cuda.empty_cache()
+
+
+def state(H, L):
+    import torch
+    out = torch.empty(3 * L.n, dtype=torch.float64, device="cuda")
+    L.field(H.FIELD_U, out)
+    return out.cpu().numpy()
+
+
+def reference(H, nx, ny, prec, steps):
+    L = lat(H, nx, ny, prec)
+    for n in steps:
+        L.run_primal(n)
+    out = state(H, L)
+    L.close()
+    return out
+
+
+def test_staging_and_probe_make_room():
+    """8192 x 4096 FP64: populations 2.4 GB, host staging of them the same, 1.6 GB free."""
+    from paper_2606_31707_amd import hlbm as H
+    say("memory short: staging, probe")
+    ref = reference(H, 8192, 4096, 0, (8, 5))
+    for what in ("populations", "probe"):
+        A = lat(H, 8192, 4096, 0)
+        assert A.optional_held() > 2 * GB
+        A.run_primal(8)
+        with Filled(int(1.6 * GB)):
+            if what == "populations":
+                f = A.populations()
+                assert f.shape == (9, A.n)
+            else:
+                assert A.copy_probe(2, n_launches=2) > 0.0
+            assert A.optional_held() == 0
+        A.run_primal(5)  # single steps
+        assert np.array_equal(state(H, A), ref)
+        A.close()
+
+
+def test_another_lattice_makes_room_and_takes_no_optional_arrays():
+    """A FP64 lattice of 2.7 GB beside one whose second array holds 2.4 of the 4 GB it could have."""
+    from paper_2606_31707_amd import hlbm as H
+    say("memory short: another lattice, a group")
+    ref = reference(H, 8192, 4096, 0, (8, 5))
+    A = lat(H, 8192, 4096, 0)
+    C = lat(H, 256, 128, 0)
+    D = lat(H, 256, 128, 0)
+    g = H.Group()
+    g.set([C, D], [H.GROUP_PRIMAL] * 2)
+    g.step(20)  # passes on the group's stream
+    A.run_primal(8)
+    with Filled(int(1.8 * GB)):
+        B = lat(H, 8192, 4096, 0)
+        assert A.optional_held() == 0 and C.optional_held() == 0 and D.optional_held() == 0
+        assert B.optional_held() == 0  # less than half of the device is free
+        B.run_primal(8)
+        g.step(21)
+        g.synchronize()
+        B.run_primal(5)
+        assert np.array_equal(state(H, B), ref)
+    A.run_primal(5)
+    assert np.array_equal(state(H, A), ref)
+    E = lat(H, 256, 128, 0)
+    E.run_primal(41)
+    assert np.array_equal(C.populations(), E.populations()) and np.array_equal(D.populations(), E.populations())
+    for L in (A, B, C, D, E):
+        L.close()
+
+
+def test_arrays_in_use_by_another_thread_are_waited_for():
+    from paper_2606_31707_amd import hlbm as H
+    say("memory short: threads")
+    steps = [8] * 40
+    ref = reference(H, 4096, 2048, 0, steps)
+    import torch
+    A = lat(H, 4096, 2048, 0, stream=torch.cuda.Stream().cuda_stream)
+    failed = []
+
+    def run():
+        try:
+            for n in steps:
+                A.run_primal(n)
+            A.synchronize()
+        except Exception as e:  # reported by the main thread
+            failed.append(e)
+
+    with Filled(int(1.4 * GB)):
+        t = threading.Thread(target=run)
+        t.start()
+        B = lat(H, 8192, 2560, 0)  # 1.7 GB: fits where A's second array was
+        t.join()
+        B.close()
+    assert not failed
+    assert A.optional_held() == 0
+    assert np.array_equal(state(H, A), ref)
+    A.close()
