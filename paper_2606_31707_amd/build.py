@@ -2,7 +2,8 @@
 libhlbm_canary.so, the same sources with 64 x 4 tiles and every sweep's
 workgroup order flipped (XCD-renumbered where the default keeps the dispatch
 order and the other way round): the race canary, under which every per-cell
-result must be bitwise the same."""
+result must be bitwise the same.  It also takes multi-step passes on every
+lattice that can, whether they pay there or not."""
 from __future__ import annotations
 
 import os
@@ -18,7 +19,7 @@ CANARY_PATH = os.path.join(HERE, "libhlbm_canary.so")
 SOURCES = ["hlbm_launch.hip", "hlbm_march2d.hip", "hlbm_march2d_adjoint.hip", "hlbm_march3d.hip", "hlbm_march3d_adjoint.hip",
            "hlbm_window2d.hip", "hlbm_packed2d.hip", "hlbm_api.hip"]
 ARCH = os.environ.get("HLBM_OFFLOAD_ARCH", "gfx950")
-CANARY_DEFINES = ["-DHLBM_TILE_BX=64", "-DHLBM_XCD_REMAP=0"]
+CANARY_DEFINES = ["-DHLBM_TILE_BX=64", "-DHLBM_XCD_REMAP=0", "-DHLBM_PASS_RULES=0"]
 
 
 FLAGS = [

@@ -10,7 +10,6 @@
 #include <string>
 #include <vector>
 
-#include "hlbm_host.hpp"
 #include "hlbm_internal.hpp"
 #include "hlbm_stop.hpp"
 
@@ -529,6 +528,8 @@ hlbm_status hlbm_create_bounded(const hlbm_desc* desc, uint64_t optional_limit, 
   };
   if ((s = lat_alloc(L, &L->f, L->ssize * L->q * L->plane)) != HLBM_OK) return bail(s);
   if ((s = lat_alloc(L, &L->dpor, L->dsize * L->plane)) != HLBM_OK) return bail(s);
+  if (desc->stencil == HLBM_D3Q19 && desc->precision != HLBM_FP16S)
+    L->march3 = march3d_plan(L->desc, march3d_rows_of(desc->precision == HLBM_FP64));
   if (primal_passes_of(&L->desc)) {
     const size_t f2 = L->ssize * L->q * L->plane;
     lat_alloc_optional(L, &L->f2, f2, &L->rcopy2, pass_bytes_primal(&L->desc) - f2);
@@ -866,6 +867,7 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
   // replays start from the same array every time, takes single steps.
   PassScope scope(&L, 1);
   const bool multi = L->f2 != nullptr && !stream_capturing(L->stream);
+  const int limit = multi ? primal_pass_limit(L, accumulate) : 1;
   void* const start = L->f;
   const size_t state_bytes = L->ssize * L->q * L->plane;
   // snapshot of u at the start of a steady run
@@ -883,9 +885,10 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
     int64_t chunk = n_steps - done;
     if (steady_tol > 0.0 && chunk > check_every) chunk = check_every;
     for (int64_t k = 0; k < chunk;) {
-      const int K = multi && L->parity == 0 ? paired_pass(primal_pass_steps(L, accumulate, chunk - k),
-                                                          n_steps - done - k, L->f != start)
-                                            : 1;
+      // (window steps after single ones that left pending values take single steps)
+      const int K = L->parity == 0 && L->pend_n == 0
+                        ? paired_pass(pass_steps(limit, chunk - k), n_steps - done - k, L->f != start)
+                        : 1;
       s = timed_launch(L, accumulate ? 1 : 0, chunk - k, K, [&]() {
         return K > 1 ? launch_primal_pass(L, accumulate, K) : launch_primal_step(L, accumulate);
       });
@@ -1049,6 +1052,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
   }
   const bool multi =
       L->phi2 != nullptr && passes && L->obj_kind != HLBM_OBJ_MEA && !turb_diff && !capturing;
+  const int limit = multi ? adjoint_pass_limit(L) : 1;
   void* const start = L->phi;
   const int pv_start = L->pvcur;
   // Where a call leaves phi and the outlet values: the arrays it found them in
@@ -1078,8 +1082,8 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
     int64_t chunk = iters - done;
     if (o->tol > 0.0 && chunk > M) chunk = M;
     for (int64_t k = 0; k < chunk;) {
-      const int K = multi && (L->adj_iters & 1) == 0
-                        ? paired_pass(adjoint_pass_steps(L, chunk - k), iters - done - k, L->phi != start)
+      const int K = (L->adj_iters & 1) == 0
+                        ? paired_pass(pass_steps(limit, chunk - k), iters - done - k, L->phi != start)
                         : 1;
       s = timed_launch(L, 2, chunk - k, K, [&]() { return K > 1 ? launch_adjoint_pass(L, K) : launch_adjoint_step(L); });
       if (s != HLBM_OK) return s;

@@ -52,35 +52,6 @@ inline int nsym_of(int stencil) { return stencil == HLBM_D2Q9 ? 3 : 6; }
 inline int ncoef_of(int stencil) { return 3 + dim_of(stencil) + nsym_of(stencil); }
 inline int nb_of(int stencil) { return 1 + dim_of(stencil) + nsym_of(stencil); }
 
-// Whether lattices of a descriptor take multi-step passes, and so hold a second
-// population array (primal) and a second phi array (adjoint).  Single steps
-// remain for a body force (tests), walls on the x axis (a value that bounces
-// there stays on its row, which a strip does not provide for), one-row
-// channels (their row is beside both walls), and rows whose byte offsets
-// exceed 32 bits; in 3D fewer than two planes, and FP16S, whose conversions cost
-// what the saved bytes give (192x96x64 21.5 us a step, 32.5 with passes;
-// 756x168x84 with walls 158 and 198; 768x384x128 565 and 478); for the adjoint
-// also the HRR collision (its frozen data would have to wait for the later
-// levels as well).  J_MEA takes single steps too, but holds the second phi
-// array: a window can be given another objective.  The 3D adjoint passes are
-// bound by their instructions and pay only in FP64 beyond the caches (us an
-// iteration, single / pass: FP64 756x168x84 798 / 533, 300x128x64 175 / 137,
-// 240x110x66 (279 MB) 109 / 100, 192x96x64 (189 MB) 57 / 73; FP32 768x384x128
-// 1195 / 1439, 192x96x64 34 / 44).
-inline bool primal_passes_of(const hlbm_desc* d) {
-  if (d->stencil == HLBM_D3Q19 && (d->nz < 2 || d->precision == HLBM_FP16S)) return false;
-  return d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
-         (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->force[0] == 0.0 && d->force[1] == 0.0 &&
-         d->force[2] == 0.0;
-}
-inline bool adjoint_passes_of(const hlbm_desc* d) {
-  if (d->stencil == HLBM_D3Q19 &&
-      (d->nz < 2 || d->precision != HLBM_FP64 || (int64_t)d->nx * d->ny * d->nz * 160 <= ((int64_t)256 << 20)))
-    return false;
-  return d->bc_x != HLBM_BC_WALLS && d->ny >= 2 &&
-         (3 * (int64_t)d->nx + 256) * 8 < ((int64_t)1 << 32) && d->collision == HLBM_COLL_BGK;
-}
-
 // What is wrong with a descriptor, or nullptr if it is valid.
 inline const char* desc_problem(const hlbm_desc* d) {
   if (!d) return "null descriptor";
@@ -148,30 +119,6 @@ inline const char* footprint_of(const hlbm_desc* desc, int with_window, int with
   }
   *bytes = b;
   return nullptr;
-}
-
-// Device bytes of the arrays that only the multi-step passes use, which a
-// lattice does without where they do not fit: the second population array
-// and, in FP64, a window step's region records; the second phi array.
-inline uint64_t pass_bytes_primal(const hlbm_desc* d) {
-  if (!primal_passes_of(d)) return 0;
-  const uint64_t q = q_of(d->stencil), as = asize_of(d->precision);
-  uint64_t b = (uint64_t)plane_stride((int64_t)d->nx * d->ny * d->nz, ssize_of(d->precision)) * q * ssize_of(d->precision);
-  if (d->precision == HLBM_FP64)
-    b += (uint64_t)round_up((int64_t)d->ny * d->nz, 128) * (uint64_t)region_copy_stride((int)q, (int)as) * as;
-  return b;
-}
-inline uint64_t pass_bytes_adjoint(const hlbm_desc* d) {
-  if (!adjoint_passes_of(d)) return 0;
-  return (uint64_t)plane_stride((int64_t)d->nx * d->ny * d->nz, ssize_of(d->precision)) * asize_of(d->precision) *
-         (uint64_t)q_of(d->stencil);
-}
-
-// Whether `bytes` of such arrays may be taken: half of the device stays free
-// for what is needed, by this library or by others, which cannot ask for them
-// back.
-inline bool optional_fits(uint64_t avail, uint64_t total, uint64_t bytes) {
-  return avail >= bytes && avail - bytes >= total / 2;
 }
 
 }  // namespace hlbm

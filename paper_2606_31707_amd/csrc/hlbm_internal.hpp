@@ -9,7 +9,7 @@
 
 #include "../../include/hlbm.h"
 #include "hlbm_device.hpp"
-#include "hlbm_host.hpp"
+#include "hlbm_pass_rules.hpp"
 
 struct hlbm_lattice_s {
   hlbm_desc desc;
@@ -28,6 +28,7 @@ struct hlbm_lattice_s {
   void* ghost = nullptr;  // q * gplane outlet virtual values (even -> odd step)
   bool stream_nt = false;  // streaming load/store hints in the sweeps
   bool large = false;      // populations and porosity exceed the Infinity Cache
+  hlbm::March3 march3{};   // tiles of the D3Q19 passes
   int parity = 0;         // 0: canonical layout; 1: after an even (local) step
   int64_t steps = 0;
 
@@ -193,13 +194,14 @@ hipError_t launch_mea_flags(hlbm_lattice_s* L);
 hipError_t launch_tangent_step(hlbm_lattice_s* L);
 hipError_t launch_tangent_objective(hlbm_lattice_s* L, double* partials, int* nblocks);
 hipError_t launch_primal_step(hlbm_lattice_s* L, int accumulate);
-// Multi-step passes (L->f2 present, parity 0): how many of `left` steps the
-// next launch takes (1: a single step), and a pass of K steps, which reads
-// L->f, writes L->f2 and swaps the two.
-int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left);
+// Multi-step passes (L->f2 present, parity 0): the steps a pass of the lattice
+// takes at most (1: single steps), how many of `left` steps the next launch
+// takes, and a pass of K steps, which reads L->f, writes L->f2 and swaps the two.
+int primal_pass_limit(const hlbm_lattice_s* L, int accumulate);
+inline int pass_steps(int limit, int64_t left) { return limit == 4 && left >= 4 ? 4 : (limit > 1 && left >= 2 ? 2 : 1); }
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K);
 hipError_t launch_window_pass(hlbm_lattice_s* L, int K);  // K window steps
-int window_pass_steps(const hlbm_lattice_s* L, int64_t left);
+int window_pass_limit(const hlbm_lattice_s* L);
 // Objective terms of a small region: from records (one of region_copy_stride
 // values per cell and step, in step order), from the canonical state (parity 0)
 struct Records {
@@ -220,7 +222,7 @@ hipError_t launch_adjoint_prep(hlbm_lattice_s* L, int source, double tau_adj, in
 hipError_t launch_adjoint_step(hlbm_lattice_s* L);
 // The same for the adjoint (L->phi2 present, an even count so far, closure
 // frozen).
-int adjoint_pass_steps(const hlbm_lattice_s* L, int64_t left);
+int adjoint_pass_limit(const hlbm_lattice_s* L);
 hipError_t launch_adjoint_pass(hlbm_lattice_s* L, int K);
 hipError_t launch_adjoint_residual(hlbm_lattice_s* L, int first, double* partials, int* nblocks);
 hipError_t launch_gradient(hlbm_lattice_s* L, double* g_dev);

@@ -76,11 +76,10 @@ void march2d(hlbm_lattice_s* L) {
 // Four steps a pass; two for FP16 lattices that stay in the caches, whose
 // loads and conversions rather than bytes bound a pass (1100 x 410: 4.6 us a
 // step with two, 5.0 with four; 8192 x 4096: 172 and 110).
-int primal_pass_steps(const hlbm_lattice_s* L, int accumulate, int64_t left) {
-  if (accumulate) return window_pass_steps(L, left);
-  if (L->desc.stencil == HLBM_D3Q19) return left >= 2 ? 2 : 1;
-  const bool two = L->desc.precision == HLBM_FP16S && !L->large;
-  return left >= 4 && !two ? 4 : (left >= 2 ? 2 : 1);
+int primal_pass_limit(const hlbm_lattice_s* L, int accumulate) {
+  if (accumulate) return window_pass_limit(L);
+  if (L->desc.stencil == HLBM_D3Q19) return passes_pay_3d(L->desc, PASS_PLAIN, L->march3) ? 2 : 1;
+  return HLBM_PASS_RULES && L->desc.precision == HLBM_FP16S && !L->large ? 2 : 4;
 }
 
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K) {

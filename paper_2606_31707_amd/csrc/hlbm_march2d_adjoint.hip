@@ -23,9 +23,9 @@ void march2d_adjoint_pass(hlbm_lattice_s* L) {
 // ones, where the halo of four levels costs more than the launch it saves
 // (400 x 160 FP32: 3.8 us an iteration with two, 4.5 with four; 1024 x 512 with
 // the dissipation box 8.1 and 7.3, FP64 with the drag plane 12.5 and 11.6).
-int adjoint_pass_steps(const hlbm_lattice_s* L, int64_t left) {
-  if (L->desc.stencil == HLBM_D3Q19) return left >= 2 ? 2 : 1;
-  return left >= 4 && L->n >= 400000 ? 4 : (left >= 2 ? 2 : 1);
+int adjoint_pass_limit(const hlbm_lattice_s* L) {
+  if (L->desc.stencil == HLBM_D3Q19) return 2;  // the lattices that hold phi2 (adjoint_passes_of)
+  return !HLBM_PASS_RULES || L->n >= 400000 ? 4 : 2;
 }
 
 hipError_t launch_adjoint_pass(hlbm_lattice_s* L, int K) {

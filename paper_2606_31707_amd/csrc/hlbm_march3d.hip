@@ -5,32 +5,13 @@
 
 namespace hlbm {
 
-March3 march3d_plan(const hlbm_lattice_s* L, int R) {
-  March3 m;
-  m.tx = (L->desc.nx + 61) / 62;
-  m.ty = (L->desc.ny + R - 3) / (R - 2);
-  const int tiles = m.tx * m.ty, nz = L->desc.nz;
-  double best = 0.0;
-  for (int chunks = 1; chunks <= nz; ++chunks) {
-    const int planes = (nz + chunks - 1) / chunks;
-    const int64_t rounds = ((int64_t)tiles * ((nz + planes - 1) / planes) + 255) / 256;
-    const double cost = (double)rounds * (planes + 3.0);
-    if (chunks == 1 || cost < best) {
-      best = cost;
-      m.planes = planes;
-    }
-  }
-  m.chunks = (nz + m.planes - 1) / m.planes;
-  return m;
-}
-
 namespace {
 template <typename S>
 void march3d_pass(hlbm_lattice_s* L, bool window) {
   constexpr int R = march3d_rows<typename Prec<S>::T>();
   const double cs = L->desc.smagorinsky_cs;
   const MarchColl c{L->desc.tau, 1.0 / L->desc.tau, 18.0 * sqrt(2.0) * cs * cs};
-  const March3 m = march3d_plan(L, R);
+  const March3 m = L->march3;
   const Probe pr = make_probe(L, 2);
   const Geo g = make_geo(L);
   const dim3 grid((unsigned)(m.tx * m.ty * m.chunks)), block(64 * R);

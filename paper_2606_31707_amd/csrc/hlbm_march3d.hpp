@@ -27,20 +27,9 @@
 
 namespace hlbm {
 
-// Tiles and plane chunks of a pass (host: march3d_plan).
-struct March3 {
-  int tx, ty, chunks, planes;  // tiles along x and y, chunks along z, planes per chunk
-};
-
-March3 march3d_plan(const hlbm_lattice_s* L, int R);
-
-// Rows of a workgroup: three wavefronts a SIMD in FP32 (16 rows and four
-// wavefronts, which share fewer recomputed rows but have 128 registers each:
-// 870 instead of 845 us at 768x384x128, 227 instead of 203 at 756x168x84); two
-// in FP64, whose state takes twice the registers.
 template <typename T>
 constexpr int march3d_rows() {
-  return sizeof(T) == 8 ? 8 : 12;
+  return march3d_rows_of(sizeof(T) == 8);
 }
 
 // LDS slot of a direction with cy != 0.

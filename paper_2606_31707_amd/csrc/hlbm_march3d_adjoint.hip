@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * march3d_rows<T>()) void k_march3d_adjoint(
 
 hipError_t launch_march3d_adjoint(hlbm_lattice_s* L) {
   constexpr int R = march3d_rows<double>();
-  const March3 m = march3d_plan(L, R);
+  const March3 m = L->march3;
   const MarchAdj ac{L->adj_les, L->adj_omega};
   k_march3d_adjoint<double><<<dim3((unsigned)(m.tx * m.ty * m.chunks)), dim3(64 * R), 0, L->stream>>>(
       make_geo(L), make_obj(L), ac, m, (const double*)L->phi, (double*)L->phi2, (const double*)L->prep, L->src,

@@ -9,9 +9,8 @@ namespace hlbm {
 
 // Window steps of a pass.  Single steps remain for the HRR collision and tracked
 // mean populations (q more sums per cell, more than the pass saves), J_MEA
-// (terms of its own), steps after single ones that left pending values, and
-// large regions in 3D, whose FP64
-// terms do not fit beside two levels' state.  Four steps a pass; two in FP64,
+// (terms of its own), 3D lattices where no pass pays, and large regions in 3D,
+// whose FP64 terms do not fit beside two levels' state.  Four steps a pass; two in FP64,
 // whose registers hold no more, and with a large region's terms in lattices
 // that stay in the caches, where four levels spill more than they save (1024 x
 // 512 with closure 15.7 us a step, two levels 13.0; 8192 x 4096 403 and 682).
@@ -19,15 +18,18 @@ namespace hlbm {
 // 13.0 / 7.0, with a dissipation box 12.2 / 9.1, FP64 15.1 / 9.6; 8192 x 4096
 // FP32 608 / 248, FP16S 413 / 199; 768x384x128 FP32 with closure 1445 / 1337;
 // 756x168x84 FP64 881 / 523.
-int window_pass_steps(const hlbm_lattice_s* L, int64_t left) {
+int window_pass_limit(const hlbm_lattice_s* L) {
   const hlbm_desc& d = L->desc;
-  if (d.collision != HLBM_COLL_BGK || d.track_mean_populations || L->pend_n != 0 || left < 2) return 1;
-  int K = d.stencil == HLBM_D3Q19 || d.precision == HLBM_FP64 || left < 4 ? 2 : 4;
+  if (d.collision != HLBM_COLL_BGK || d.track_mean_populations) return 1;
+  int K = d.stencil == HLBM_D3Q19 || d.precision == HLBM_FP64 ? 2 : 4;
+  if (d.stencil == HLBM_D3Q19 &&
+      !passes_pay_3d(d, L->obj_set && L->rcopy ? PASS_WINDOW_REGION : PASS_WINDOW, L->march3))
+    return 1;
   if (L->obj_set) {
     if (L->obj_kind == HLBM_OBJ_MEA) return 1;
     if (!L->rcopy) {
       if (d.stencil == HLBM_D3Q19) return 1;
-      if (!L->large) K = 2;
+      if (HLBM_PASS_RULES && !L->large) K = 2;
     } else if (d.precision != HLBM_FP64 &&
                L->rplane * region_copy_stride(L->q, (int)L->asize) > pend_slot_elems(L)) {
       return 1;  // the pending slots hold the records of the later levels

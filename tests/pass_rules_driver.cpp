@@ -1,0 +1,26 @@
+// Answers for lattices on standard input, one a line, whether they take multi-step passes
+// (csrc/hlbm_pass_rules.hpp): stencil precision nx ny nz bc_x bc_y bc_z collision closure kind
+// -> bytes of optional arrays, whether passes of that kind (PassKind) pay.
+#include <cstdio>
+#include <cstring>
+
+#include "hlbm_pass_rules.hpp"
+
+int main() {
+  using namespace hlbm;
+  hlbm_desc d;
+  int kind;
+  std::memset(&d, 0, sizeof d);
+  d.struct_size = sizeof d;
+  d.tau = 0.56;
+  d.inlet_profile = HLBM_INLET_PARABOLIC;
+  d.u_in = 0.04;
+  while (std::scanf("%d %d %d %d %d %d %d %d %d %lf %d", &d.stencil, &d.precision, &d.nx, &d.ny, &d.nz, &d.bc_x, &d.bc_y,
+                    &d.bc_z, &d.collision, &d.smagorinsky_cs, &kind) == 11) {
+    if (desc_problem(&d)) return std::printf("bad descriptor: %s\n", desc_problem(&d)), 1;
+    const March3 m = march3d_plan(d, march3d_rows_of(d.precision == HLBM_FP64));
+    std::printf("%llu %d\n", (unsigned long long)(kind == PASS_ADJOINT ? pass_bytes_adjoint(&d) : pass_bytes_primal(&d)),
+                (int)passes_pay_3d(d, (PassKind)kind, m));
+  }
+  return 0;
+}

@@ -1,0 +1,90 @@
+"""Which lattices take multi-step passes: the rules of csrc/hlbm_pass_rules.hpp, compiled for the
+host, against lattices measured with and without them on an MI355X (ratio pass / single steps):
+none that a pass slows down may take it, and those that gain much must."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PLAIN, WINDOW, WINDOW_REGION, ADJOINT = range(4)
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-I",
+                    os.path.join(ROOT, "paper_2606_31707_amd", "csrc"), os.path.join(ROOT, "tests", "pass_rules_driver.cpp"),
+                    "-o", exe], check=True)
+
+    def run(rows):
+        text = "\n".join(" ".join(map(str, r)) for r in rows)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return run
+
+
+# stencil, precision, nx, ny, nz, bc_x, bc_y, bc_z, collision, closure, kind: ratio
+MEASURED_3D = {
+    (1, 0, 20, 200, 50, 2, 1, 0, 1, 0.1, PLAIN): 1.74,
+    (1, 1, 20, 200, 50, 2, 1, 0, 0, 0.0, PLAIN): 1.42,
+    (1, 1, 10, 10, 1000, 2, 1, 0, 1, 0.1, PLAIN): 1.71,
+    (1, 1, 64, 64, 64, 2, 1, 0, 0, 0.0, PLAIN): 1.30,
+    (1, 1, 128, 64, 32, 2, 1, 0, 1, 0.0, PLAIN): 1.33,
+    (1, 0, 64, 64, 64, 2, 1, 0, 1, 0.1, PLAIN): 1.38,
+    (1, 0, 64, 20, 400, 2, 1, 0, 1, 0.0, PLAIN): 1.23,
+    (1, 1, 32, 32, 32, 2, 1, 0, 1, 0.1, PLAIN): 1.17,
+    (1, 1, 186, 70, 3, 0, 1, 1, 0, 0.1, PLAIN): 1.21,
+    (1, 0, 9, 225, 337, 2, 0, 0, 0, 0.0, PLAIN): 2.65,
+    (1, 0, 63, 75, 363, 2, 0, 0, 0, 0.1, PLAIN): 1.22,
+    (1, 1, 63, 375, 145, 2, 1, 0, 0, 0.0, PLAIN): 1.22,
+    (1, 1, 81, 91, 368, 2, 1, 1, 0, 0.0, PLAIN): 1.15,
+    (1, 1, 64, 64, 64, 2, 1, 0, 0, 0.1, WINDOW): 1.37,
+    (1, 1, 10, 10, 1000, 2, 1, 0, 0, 0.0, WINDOW): 1.35,
+    (1, 0, 64, 20, 400, 2, 1, 0, 0, 0.1, WINDOW): 1.20,
+    (1, 0, 34, 308, 93, 2, 0, 0, 0, 0.0, WINDOW): 1.10,
+    (1, 0, 64, 20, 400, 2, 1, 0, 0, 0.1, WINDOW_REGION): 1.25,
+    (1, 1, 20, 200, 50, 2, 1, 0, 0, 0.1, WINDOW_REGION): 1.37,
+    (1, 1, 76, 402, 159, 2, 0, 0, 0, 0.0, WINDOW_REGION): 1.35,
+    (1, 0, 63, 75, 363, 2, 0, 0, 0, 0.0, ADJOINT): 1.45,
+    (1, 0, 76, 402, 159, 2, 0, 0, 0, 0.0, ADJOINT): 1.24,
+    (1, 0, 63, 375, 145, 2, 1, 0, 0, 0.0, ADJOINT): 1.22,
+    (1, 0, 192, 96, 64, 2, 1, 0, 0, 0.0, ADJOINT): 1.28,
+    # and gains
+    (1, 0, 756, 168, 84, 2, 0, 0, 0, 0.0, PLAIN): 0.70,
+    (1, 0, 96, 48, 16, 2, 1, 0, 0, 0.0, PLAIN): 0.64,
+    (1, 0, 16, 16, 16, 2, 1, 0, 0, 0.0, PLAIN): 0.87,
+    (1, 0, 300, 128, 64, 2, 1, 0, 1, 0.1, PLAIN): 0.77,
+    (1, 1, 768, 384, 128, 2, 0, 0, 0, 0.0, PLAIN): 0.77,
+    (1, 1, 130, 29, 64, 0, 0, 0, 0, 0.0, PLAIN): 0.74,
+    (1, 1, 696, 97, 69, 2, 1, 0, 1, 0.1, PLAIN): 0.87,
+    (1, 0, 756, 168, 84, 2, 1, 0, 0, 0.0, WINDOW): 0.59,
+    (1, 0, 300, 128, 64, 2, 1, 0, 0, 0.1, WINDOW): 0.60,
+    (1, 1, 192, 96, 64, 2, 1, 0, 0, 0.0, WINDOW): 0.81,
+    (1, 0, 16, 16, 16, 2, 1, 0, 0, 0.1, WINDOW_REGION): 0.87,
+    (1, 1, 32, 32, 32, 2, 1, 0, 0, 0.0, WINDOW_REGION): 0.82,
+    (1, 1, 768, 384, 128, 2, 0, 0, 0, 0.1, WINDOW_REGION): 0.97,
+    (1, 0, 756, 168, 84, 2, 1, 0, 0, 0.0, ADJOINT): 0.67,
+    (1, 0, 300, 128, 64, 2, 1, 0, 0, 0.1, ADJOINT): 0.79,
+}
+
+
+def test_3d_lattices_take_passes_where_they_pay(ask):
+    for row, (_, pays) in zip(MEASURED_3D, ask(MEASURED_3D)):
+        if row[10] != ADJOINT:
+            assert pays == (MEASURED_3D[row] < 1.0), row
+
+
+def test_3d_lattices_without_a_pass_that_pays_hold_no_arrays_for_it(ask):
+    narrow = (1, 1, 9, 225, 337, 2, 0, 0, 0, 0.1, PLAIN)
+    assert ask([narrow])[0] == (0, 0)
+    for row, (held, _) in zip(MEASURED_3D, ask(MEASURED_3D)):
+        if row[10] == ADJOINT:
+            assert (held > 0) == (MEASURED_3D[row] < 1.0), row
+
+
+def test_plans_of_extreme_shapes_are_quick(ask):
+    """A plan looks at a bounded number of chunkings however many planes there are."""
+    rows = [(1, 1, 2, 1, 1 << 30, 0, 0, 0, 0, 0.0, PLAIN), (1, 0, 2, 1 << 15, 1 << 15, 0, 0, 0, 0, 0.0, PLAIN),
+            (1, 1, (1 << 31) - 1, 1, 1, 0, 0, 0, 0, 0.0, PLAIN), (1, 1, 2, 1 << 30, 1, 0, 0, 0, 0, 0.0, PLAIN)]
+    assert ask(rows) == [(0, 0)] * 4  # two columns fill no tile, one plane no pass
