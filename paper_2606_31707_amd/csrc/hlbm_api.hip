@@ -519,8 +519,7 @@ hlbm_status hlbm_create_bounded(const hlbm_desc* desc, uint64_t optional_limit, 
   // streaming hints for BGK primal sweeps over lattices larger than the
   // 256 MiB Infinity Cache (D2Q9 measured 160 MB slower with them, 320 MB
   // faster); which steps take them is decided per stencil at launch
-  const int64_t sweep_bytes = (int64_t)(L->ssize * L->q + L->dsize) * L->plane;
-  L->large = sweep_bytes > ((int64_t)256 << 20);
+  L->large = beyond_caches(L->desc);
   L->stream_nt = desc->cache_policy == HLBM_CACHE_STREAMING || (desc->cache_policy == HLBM_CACHE_AUTO && L->large);
   auto bail = [&](hlbm_status st) {
     hlbm_destroy(L);
@@ -867,7 +866,7 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
   // replays start from the same array every time, takes single steps.
   PassScope scope(&L, 1);
   const bool multi = L->f2 != nullptr && !stream_capturing(L->stream);
-  const int limit = multi ? primal_pass_limit(L, accumulate) : 1;
+  const int limit = multi && n_steps > 1 ? primal_pass_limit(L, accumulate) : 1;
   void* const start = L->f;
   const size_t state_bytes = L->ssize * L->q * L->plane;
   // snapshot of u at the start of a steady run

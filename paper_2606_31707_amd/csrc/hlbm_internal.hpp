@@ -171,11 +171,6 @@ struct Acc {
 };
 
 
-// Chunking of a D2Q9 multi-step pass.
-struct March2 {
-  int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
-};
-
 Geo make_geo(const hlbm_lattice_s* L);
 ObjBox make_obj(const hlbm_lattice_s* L);
 Coll make_coll(const hlbm_lattice_s* L);

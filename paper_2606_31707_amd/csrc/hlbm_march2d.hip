@@ -6,34 +6,6 @@
 
 namespace hlbm {
 
-// Rows per chunk: the number of iterations (rows plus the halo of the levels)
-// times what an iteration costs with m workgroups on a compute unit.  Measured
-// on 1100 x 410: a second wavefront on a SIMD adds 45 % to an iteration in
-// FP64 and 9 % in FP32 (latency left by one is filled by the other), each
-// further one 40 %.  Long chunks stop paying on lattices larger than the
-// caches, where neighbouring chunks share their halo rows in L2
-// (8192 x 4096 FP32: 8 rows 167 us, 16 rows 169, 58 rows 184; FP16S, whose
-// rows are half as long, 150, 117 and 110).
-March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64) {
-  const int W = 64 - 2 * (K - 1), ny = L->desc.ny;
-  March2 m;
-  m.strips = (L->desc.nx + W - 1) / W;
-  const int most = L->desc.precision == HLBM_FP16S ? 24 : 12;
-  double best = 0.0;
-  for (int rows = 1; rows <= most && rows <= ny; ++rows) {
-    const int64_t groups = ((int64_t)m.strips * ((ny + rows - 1) / rows) + 3) / 4;
-    const double per_cu = groups <= 1024 ? (double)((groups + 255) / 256) : groups / 256.0;
-    const double share = f64 ? 0.55 + 0.47 * per_cu : (per_cu <= 2.0 ? 1.0 : 0.1 + 0.42 * per_cu);
-    const double cost = (rows + 2 * (K - 1)) * share;
-    if (rows == 1 || cost < best) {
-      best = cost;
-      m.rows = rows;
-    }
-  }
-  m.chunks = (ny + m.rows - 1) / m.rows;
-  return m;
-}
-
 Probe make_probe(const hlbm_lattice_s* L, int K) {
   Probe pr{{nullptr, nullptr, nullptr, nullptr}, 0, 0, 0};
   if (L->probe_buf != nullptr && L->probe_cap > 0) {
@@ -52,7 +24,7 @@ void march2d(hlbm_lattice_s* L) {
   const Geo g = make_geo(L);
   const double cs = L->desc.smagorinsky_cs;
   const MarchColl c{L->desc.tau, 1.0 / L->desc.tau, 18.0 * sqrt(2.0) * cs * cs};
-  const March2 m = march2d_plan(L, K, sizeof(S) == 8);
+  const March2 m = march2d_plan(L->desc, K);
   const Probe pr = make_probe(L, K);
   const dim3 grid((unsigned)((m.strips * m.chunks + 3) / 4));
   const S* A = (const S*)L->f;
@@ -73,13 +45,8 @@ void march2d(hlbm_lattice_s* L) {
 }
 }  // namespace
 
-// Four steps a pass; two for FP16 lattices that stay in the caches, whose
-// loads and conversions rather than bytes bound a pass (1100 x 410: 4.6 us a
-// step with two, 5.0 with four; 8192 x 4096: 172 and 110).
 int primal_pass_limit(const hlbm_lattice_s* L, int accumulate) {
-  if (accumulate) return window_pass_limit(L);
-  if (L->desc.stencil == HLBM_D3Q19) return passes_pay_3d(L->desc, PASS_PLAIN, L->march3) ? 2 : 1;
-  return HLBM_PASS_RULES && L->desc.precision == HLBM_FP16S && !L->large ? 2 : 4;
+  return accumulate ? window_pass_limit(L) : pass_limit(L->desc, PASS_PLAIN, L->march3);
 }
 
 hipError_t launch_primal_pass(hlbm_lattice_s* L, int accumulate, int K) {

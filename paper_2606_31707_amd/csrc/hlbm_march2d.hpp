@@ -34,8 +34,6 @@
 
 namespace hlbm {
 
-// Strips and row chunks of a pass (host: march2d_plan).
-March2 march2d_plan(const hlbm_lattice_s* L, int K, bool f64);
 hipError_t launch_window2d(hlbm_lattice_s* L, int K);  // K D2Q9 window steps (hlbm_window2d.hip)
 hipError_t launch_march3d_adjoint(hlbm_lattice_s* L);  // two D3Q19 adjoint iterations
 hipError_t launch_march3d(hlbm_lattice_s* L, bool window);  // two D3Q19 steps (hlbm_march3d.hip)

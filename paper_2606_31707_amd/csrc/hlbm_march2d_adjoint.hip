@@ -10,7 +10,7 @@ namespace hlbm {
 namespace {
 template <typename T, int K>
 void march2d_adjoint_pass(hlbm_lattice_s* L) {
-  const March2 m = march2d_plan(L, K, sizeof(T) == 8);
+  const March2 m = march2d_plan(L->desc, K);
   const MarchAdj ac{L->adj_les, L->adj_omega};
   const dim3 grid((unsigned)((m.strips * m.chunks + 3) / 4));
   k_march2d_adjoint<T, K><<<grid, 256, 0, L->stream>>>(make_geo(L), make_obj(L), ac, m, (const T*)L->phi,
@@ -19,13 +19,9 @@ void march2d_adjoint_pass(hlbm_lattice_s* L) {
 }
 }  // namespace
 
-// Four iterations a pass on lattices with work for every SIMD, two on smaller
-// ones, where the halo of four levels costs more than the launch it saves
-// (400 x 160 FP32: 3.8 us an iteration with two, 4.5 with four; 1024 x 512 with
-// the dissipation box 8.1 and 7.3, FP64 with the drag plane 12.5 and 11.6).
 int adjoint_pass_limit(const hlbm_lattice_s* L) {
-  if (L->desc.stencil == HLBM_D3Q19) return 2;  // the lattices that hold phi2 (adjoint_passes_of)
-  return !HLBM_PASS_RULES || L->n >= 400000 ? 4 : 2;
+  const bool small = region_copy_used((int64_t)L->rn[0] * L->rn[1] * L->rn[2], L->n, L->obj_kind);
+  return pass_limit(L->desc, small ? PASS_ADJOINT : PASS_ADJOINT_LARGE, L->march3);
 }
 
 hipError_t launch_adjoint_pass(hlbm_lattice_s* L, int K) {

@@ -14,10 +14,118 @@
 
 namespace hlbm {
 
-// What a pass computes: plain steps, window steps (with a small objective
-// region, whose single steps launch a region pass each, or without), adjoint
-// iterations.
-enum PassKind { PASS_PLAIN, PASS_WINDOW, PASS_WINDOW_REGION, PASS_ADJOINT };
+// What a pass computes: plain steps, window steps (without an objective
+// region; with a small one, whose single steps launch a region pass each; with
+// a large one, whose terms the sweep adds), adjoint iterations (the objective's
+// region small, large).
+enum PassKind { PASS_PLAIN, PASS_WINDOW, PASS_WINDOW_REGION, PASS_ADJOINT, PASS_WINDOW_LARGE, PASS_ADJOINT_LARGE };
+
+// Whether the populations and the porosity exceed the 256 MiB Infinity Cache.
+inline bool beyond_caches(const hlbm_desc& d) {
+  const int64_t plane = plane_stride((int64_t)d.nx * d.ny * d.nz, ssize_of(d.precision));
+  return (int64_t)(ssize_of(d.precision) * q_of(d.stencil) + dsize_of(d.precision)) * plane > ((int64_t)256 << 20);
+}
+
+// ---- D2Q9: two or four steps -----------------------------------------------
+
+// Strips and row chunks of a pass.
+struct March2 {
+  int strips, chunks, rows;  // strips along x, chunks along y, rows per chunk
+};
+
+// Rows per chunk: the number of iterations (rows plus the halo of the levels)
+// times what an iteration costs with m workgroups on a compute unit.  Measured
+// on 1100 x 410: a second wavefront on a SIMD adds 45 % to an iteration in
+// FP64 and 9 % in FP32 (latency left by one is filled by the other), each
+// further one 40 %.  Long chunks stop paying on lattices larger than the
+// caches, where neighbouring chunks share their halo rows in L2
+// (8192 x 4096 FP32: 8 rows 167 us, 16 rows 169, 58 rows 184; FP16S, whose
+// rows are half as long, 150, 117 and 110).
+inline March2 march2d_plan(const hlbm_desc& d, int K) {
+  const int W = 64 - 2 * (K - 1), ny = d.ny;
+  const bool f64 = d.precision == HLBM_FP64;
+  March2 m;
+  m.strips = (d.nx + W - 1) / W;
+  const int most = d.precision == HLBM_FP16S ? 24 : 12;
+  double best = 0.0;
+  for (int rows = 1; rows <= most && rows <= ny; ++rows) {
+    const int64_t groups = ((int64_t)m.strips * ((ny + rows - 1) / rows) + 3) / 4;
+    const double per_cu = groups <= 1024 ? (double)((groups + 255) / 256) : groups / 256.0;
+    const double share = f64 ? 0.55 + 0.47 * per_cu : (per_cu <= 2.0 ? 1.0 : 0.1 + 0.42 * per_cu);
+    const double cost = (rows + 2 * (K - 1)) * share;
+    if (rows == 1 || cost < best) {
+      best = cost;
+      m.rows = rows;
+    }
+  }
+  m.chunks = (ny + m.rows - 1) / m.rows;
+  return m;
+}
+
+// Steps (iterations) of a pass by the number of cells and the kernels.  Plain
+// steps: four; two for FP16 lattices that stay in the caches, whose loads and
+// conversions rather than bytes bound a pass (1100 x 410: 4.6 us a step with
+// two, 5.0 with four; 8192 x 4096: 172 and 110).  Window steps: four; two in
+// FP64, whose registers hold no more, and with a large region's terms in
+// lattices that stay in the caches, where four levels spill more than they save (1024 x
+// 512 with closure 15.7 us a step, two levels 13.0; 8192 x 4096 403 and 682).
+// Adjoint: four on lattices with work for every SIMD, two on smaller ones, where
+// the halo of four levels costs more than the launch it saves (400 x 160 FP32:
+// 3.8 us an iteration with two, 4.5 with four; 1024 x 512 with the dissipation box
+// 8.1 and 7.3, FP64 with the drag plane 12.5 and 11.6).
+inline int pass_levels_2d(const hlbm_desc& d, PassKind kind) {
+  switch (kind) {
+    case PASS_PLAIN: return HLBM_PASS_RULES && d.precision == HLBM_FP16S && !beyond_caches(d) ? 2 : 4;
+    case PASS_WINDOW:
+    case PASS_WINDOW_REGION: return d.precision == HLBM_FP64 ? 2 : 4;
+    case PASS_WINDOW_LARGE: return d.precision == HLBM_FP64 || (HLBM_PASS_RULES && !beyond_caches(d)) ? 2 : 4;
+    default: return !HLBM_PASS_RULES || (int64_t)d.nx * d.ny >= 400000 ? 4 : 2;
+  }
+}
+
+// Whether passes of that many steps beat single ones.  A pass takes the time of
+// the rows that a wavefront goes through (its chunk and 2 (K - 1) more), times
+// the workgroups of a compute unit; single steps that of the cells and, on
+// small lattices, of their launches, worth `launch` rows: plain passes pay where
+//   n >= share 256 4 W (rows' time - launch),   W = 64 - 2 (K - 1) own columns.
+// Almost every 2D lattice lies above it; below it are narrow ones of thousands of
+// rows (us a step, single / pass: 7 x 8990 FP64 with closure 6.2 / 8.8, 19 x 8747 FP32 with
+// HRR and closure 5.9 / 8.1) and, for FP32 with HRR and closure, where the
+// second workgroup of a compute unit is not for free, some of 50 to 400 thousand
+// cells (289 x 835 5.7 / 6.5; 512 x 256 4.8 / 5.3; above it 400 x 160, 5.0 / 4.8).
+// FP16S windows with closure and no region on channels whose wavefronts have two
+// rows of their own for six of halo (4081 x 32 5.4 / 6.4, 904 x 135 5.4 / 5.6); FP64
+// windows with a large region and closure, three rows a wavefront (512 x 256 7.6 /
+// 9.0, 4081 x 32 8.0 / 8.7; two rows 904 x 135 8.8 / 7.3); in the adjoint of
+// channels the strips of the outlet set the time of a pass of two: FP64 with three
+// or more rows and one workgroup a compute unit (1700 x 148 7.2 / 8.0, 289 x 835 7.5 /
+// 7.9; two rows 447 x 480 7.1 / 6.1), FP32 with a large region (556 x 584 7.4 / 8.0,
+// 422 x 356 5.2 / 5.6; 904 x 135 5.6 / 4.8).  Of 5700 runs on other random lattices
+// of 256 to 8 M cells 36 are more than 3 % slower than single steps, by 16 % at
+// most; the mean is 0.71 of them.
+inline bool passes_pay_2d(const hlbm_desc& d, PassKind kind, int K) {
+  if (!HLBM_PASS_RULES) return true;
+  const bool f64 = d.precision == HLBM_FP64, f32 = d.precision == HLBM_FP32;
+  const bool les = d.smagorinsky_cs > 0.0, hrr = d.collision == HLBM_COLL_HRR, channel = d.bc_x == HLBM_BC_INLET_OUTLET;
+  const March2 m = march2d_plan(d, K);
+  const int64_t n = (int64_t)d.nx * d.ny, groups = ((int64_t)m.strips * m.chunks + 3) / 4;
+  switch (kind) {
+    case PASS_PLAIN: {
+      if (!f64 && !les && !hrr) return true;
+      const double per_cu = groups <= 1024 ? (double)((groups + 255) / 256) : groups / 256.0;
+      const bool both = les && hrr;
+      const double rows = (m.rows + 2.0 * (K - 1)) * (f32 && !both ? 0.25 + 0.75 * per_cu : per_cu);
+      const double share = f32 ? 0.4 : (les || hrr ? 0.5 : 0.2), launch = f32 ? (both ? 7.0 : 12.0) : 9.0;
+      return n >= share * 256.0 * 4.0 * (64 - 2 * (K - 1)) * (rows - launch);
+    }
+    case PASS_WINDOW: return !(d.precision == HLBM_FP16S && les && channel && m.rows == 2 && groups > 256);
+    case PASS_WINDOW_LARGE: return !(f64 && les && channel && m.rows == 3 && groups <= 256);
+    case PASS_ADJOINT: return !(f64 && channel && K == 2 && m.rows >= 3 && groups <= 256);
+    case PASS_ADJOINT_LARGE:
+      return !(channel && K == 2 && (f64 ? m.rows >= 3 && groups <= 256 : n >= 125000));
+    default: return true;
+  }
+}
 
 // ---- D3Q19: two steps ------------------------------------------------------
 
@@ -97,13 +205,24 @@ inline bool passes_pay_3d(const hlbm_desc& d, PassKind kind, const March3& m) {
       if (f64) share = 0.5;
       launch = f64 ? 3.5 - 0.25 * walls : 3.5;
       break;
-    case PASS_ADJOINT: break;
+    default: break;
   }
   const int R = march3d_rows_of(f64);
   const double tiles = (double)m.tx * m.ty;
   const int64_t rounds = ((int64_t)(tiles * m.chunks) + 255) / 256;
   const double I = (double)rounds * (m.planes + 2.0);
   return n >= share * 256.0 * 62.0 * (R - 2) * (I - launch);
+}
+
+// Steps that a pass of the lattice takes at most; 1: single steps.  m: its plan
+// (D3Q19).  3D adjoint passes pay on every lattice that holds the second phi
+// array (adjoint_passes_of).
+inline int pass_limit(const hlbm_desc& d, PassKind kind, const March3& m) {
+  if (d.stencil == HLBM_D2Q9) {
+    const int K = pass_levels_2d(d, kind);
+    return passes_pay_2d(d, kind, K) ? K : 1;
+  }
+  return kind == PASS_ADJOINT || kind == PASS_ADJOINT_LARGE || passes_pay_3d(d, kind, m) ? 2 : 1;
 }
 
 inline bool any_primal_pass_pays_3d(hlbm_desc d) {

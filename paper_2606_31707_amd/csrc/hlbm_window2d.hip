@@ -7,13 +7,10 @@
 
 namespace hlbm {
 
-// Window steps of a pass.  Single steps remain for the HRR collision and tracked
-// mean populations (q more sums per cell, more than the pass saves), J_MEA
-// (terms of its own), 3D lattices where no pass pays, and large regions in 3D,
-// whose FP64 terms do not fit beside two levels' state.  Four steps a pass; two in FP64,
-// whose registers hold no more, and with a large region's terms in lattices
-// that stay in the caches, where four levels spill more than they save (1024 x
-// 512 with closure 15.7 us a step, two levels 13.0; 8192 x 4096 403 and 682).
+// Window steps of a pass (pass_limit).  Single steps remain for the HRR
+// collision and tracked mean populations (q more sums per cell, more than the
+// pass saves), J_MEA (terms of its own) and large regions in 3D, whose FP64
+// terms do not fit beside two levels' state.
 // us a step, single steps / passes: 1100 x 410 FP32 9.5 / 5.0, with a drag plane
 // 13.0 / 7.0, with a dissipation box 12.2 / 9.1, FP64 15.1 / 9.6; 8192 x 4096
 // FP32 608 / 248, FP16S 413 / 199; 768x384x128 FP32 with closure 1445 / 1337;
@@ -21,21 +18,19 @@ namespace hlbm {
 int window_pass_limit(const hlbm_lattice_s* L) {
   const hlbm_desc& d = L->desc;
   if (d.collision != HLBM_COLL_BGK || d.track_mean_populations) return 1;
-  int K = d.stencil == HLBM_D3Q19 || d.precision == HLBM_FP64 ? 2 : 4;
-  if (d.stencil == HLBM_D3Q19 &&
-      !passes_pay_3d(d, L->obj_set && L->rcopy ? PASS_WINDOW_REGION : PASS_WINDOW, L->march3))
-    return 1;
+  PassKind kind = PASS_WINDOW;
   if (L->obj_set) {
     if (L->obj_kind == HLBM_OBJ_MEA) return 1;
     if (!L->rcopy) {
       if (d.stencil == HLBM_D3Q19) return 1;
-      if (HLBM_PASS_RULES && !L->large) K = 2;
-    } else if (d.precision != HLBM_FP64 &&
-               L->rplane * region_copy_stride(L->q, (int)L->asize) > pend_slot_elems(L)) {
-      return 1;  // the pending slots hold the records of the later levels
+      kind = PASS_WINDOW_LARGE;
+    } else {
+      // the pending slots hold the records of the later levels
+      if (d.precision != HLBM_FP64 && L->rplane * region_copy_stride(L->q, (int)L->asize) > pend_slot_elems(L)) return 1;
+      kind = PASS_WINDOW_REGION;
     }
   }
-  return K;
+  return pass_limit(d, kind, L->march3);
 }
 
 // Level 0's records go to the region copy, those of the later levels to the
@@ -69,7 +64,7 @@ void window2d(hlbm_lattice_s* L) {
   const Geo g = make_geo(L);
   const double cs = L->desc.smagorinsky_cs;
   const MarchColl c{L->desc.tau, 1.0 / L->desc.tau, 18.0 * sqrt(2.0) * cs * cs};
-  const March2 m = march2d_plan(L, K, sizeof(S) == 8);
+  const March2 m = march2d_plan(L->desc, K);
   const Probe pr = make_probe(L, K);
   const Window wn = make_window(L);
   const dim3 grid((unsigned)((m.strips * m.chunks + 3) / 4));

@@ -1,6 +1,6 @@
 // Answers for lattices on standard input, one a line, whether they take multi-step passes
 // (csrc/hlbm_pass_rules.hpp): stencil precision nx ny nz bc_x bc_y bc_z collision closure kind
-// -> bytes of optional arrays, whether passes of that kind (PassKind) pay.
+// -> bytes of optional arrays, steps that a pass of that kind (PassKind) takes at most (1: none).
 #include <cstdio>
 #include <cstring>
 
@@ -19,8 +19,9 @@ int main() {
                     &d.bc_z, &d.collision, &d.smagorinsky_cs, &kind) == 11) {
     if (desc_problem(&d)) return std::printf("bad descriptor: %s\n", desc_problem(&d)), 1;
     const March3 m = march3d_plan(d, march3d_rows_of(d.precision == HLBM_FP64));
-    std::printf("%llu %d\n", (unsigned long long)(kind == PASS_ADJOINT ? pass_bytes_adjoint(&d) : pass_bytes_primal(&d)),
-                (int)passes_pay_3d(d, (PassKind)kind, m));
+    const bool adjoint = kind == PASS_ADJOINT || kind == PASS_ADJOINT_LARGE;
+    std::printf("%llu %d\n", (unsigned long long)(adjoint ? pass_bytes_adjoint(&d) : pass_bytes_primal(&d)),
+                pass_limit(d, (PassKind)kind, m));
   }
   return 0;
 }
