@@ -1397,8 +1397,12 @@ hlbm_status group_tables(hlbm_group_s* g, hlbm_lattice_s* const* lats, const int
   g->n_adjoint = n_adjoint;
   g->blocks_primal = bp;
   g->blocks_adjoint = ba;
-  g->pass_primal = pass_p ? qp : 0;
-  g->pass_adjoint = pass_a ? qa : 0;
+  bool windows = false;
+  for (int i = 0; i < count; ++i) windows |= modes[i] == HLBM_GROUP_PRIMAL_WINDOW;
+  const bool with_other = pass_p && pass_a && n_primal > 0 && n_adjoint > 0;
+  const int prec = count ? lats[0]->desc.precision : 0;
+  g->pass_primal = pass_p && packed_passes_pay(prec, windows ? PASS_WINDOW : PASS_PLAIN, with_other, qp) ? qp : 0;
+  g->pass_adjoint = pass_a && packed_passes_pay(prec, PASS_ADJOINT, with_other, qa) ? qa : 0;
   g->pv_adjoint = 0;
   g->steps_since_set = 0;
   return HLBM_OK;

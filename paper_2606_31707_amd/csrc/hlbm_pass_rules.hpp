@@ -127,6 +127,27 @@ inline bool passes_pay_2d(const hlbm_desc& d, PassKind kind, int K) {
   }
 }
 
+// Whether a packed list takes passes of two steps.  kind: PASS_PLAIN, PASS_WINDOW
+// (a list with window members) or PASS_ADJOINT; with_other: the group's other
+// list takes passes too, in the same launches; blocks: workgroups of its pass.
+// Two lists in one launch for two steps instead of four launches pay at any size
+// (us a step: FP64 4 x 26x13 ... 54x27 10.5 / 6.9, FP32 10.2 / 6.1; 14 x 636x318 ... 198
+// / 140).  For one list a pass saves a launch of two and its longer chain costs
+// more: on few workgroups, with FP64 window members (one body of 256 registers
+// serves all members: 6 x 68x17 ... 5.9 / 9.4, 5 x 316x158 ... 24.6 / 28.5) and for FP32
+// adjoints (4 x 113x56 ... 5.5 / 6.8, 9 x 301x1204 58 / 72), while FP64 adjoints gain
+// from 400 workgroups on (276 blocks 7.8 / 8.7, 430 11.1 / 10.2), FP32 and FP16S
+// windows from 150 (92 blocks 6.8 / 7.2, 173 9.6 / 7.7), plain lists from 200
+// (74 blocks 4.6 / 4.8, 204 6.7 / 6.2).
+inline bool packed_passes_pay(int precision, PassKind kind, bool with_other, int blocks) {
+  if (!HLBM_PASS_RULES || with_other) return true;
+  switch (kind) {
+    case PASS_PLAIN: return blocks >= 200;
+    case PASS_WINDOW: return precision != HLBM_FP64 && blocks >= 150;
+    default: return precision == HLBM_FP64 && blocks >= 400;
+  }
+}
+
 // ---- D3Q19: two steps ------------------------------------------------------
 
 // Tiles and plane chunks of a pass.

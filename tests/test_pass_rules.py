@@ -130,6 +130,23 @@ def test_2d_lattices_take_passes_where_they_pay(ask):
         assert held > 0  # (whether windows have a region, and the closure, may change later)
 
 
+# precision, kind, whether the group's other list takes passes, workgroups: ratio
+MEASURED_PACKED = {
+    (0, WINDOW, 0, 25): 1.59, (0, WINDOW, 0, 647): 1.16, (0, WINDOW, 0, 1917): 1.06, (1, WINDOW, 0, 15): 1.10,
+    (2, WINDOW, 0, 13): 1.14, (1, PLAIN, 0, 74): 1.04, (2, PLAIN, 0, 63): 1.08, (0, PLAIN, 0, 54): 1.09,
+    (0, ADJOINT, 0, 27): 1.31, (0, ADJOINT, 0, 276): 1.10, (1, ADJOINT, 0, 106): 1.31, (2, ADJOINT, 0, 3898): 1.24,
+    (1, WINDOW, 0, 173): 0.81, (2, WINDOW, 0, 264): 0.76, (1, WINDOW, 0, 4539): 0.54, (0, PLAIN, 0, 204): 0.92,
+    (0, PLAIN, 0, 776): 0.81, (1, PLAIN, 0, 1516): 0.87, (0, ADJOINT, 0, 430): 0.92, (0, ADJOINT, 0, 1934): 0.85,
+    (0, WINDOW, 1, 9): 0.66, (1, ADJOINT, 1, 9): 0.60, (0, ADJOINT, 1, 5029): 0.71, (1, WINDOW, 1, 4773): 0.53,
+}
+
+
+def test_packed_lists_take_passes_where_they_pay(ask):
+    rows = [(0, p, other, blocks, 0, 0, 0, 0, 0, 0.0, kind) for p, kind, other, blocks in MEASURED_PACKED]
+    for key, (_, pays) in zip(MEASURED_PACKED, ask(rows)):
+        assert pays == (MEASURED_PACKED[key] < 1.0), key
+
+
 def test_plans_of_extreme_shapes_are_quick(ask):
     """A plan looks at a bounded number of chunkings however many planes there are."""
     rows = [(1, 1, 2, 1, 1 << 30, 0, 0, 0, 0, 0.0, PLAIN), (1, 0, 2, 1 << 15, 1 << 15, 0, 0, 0, 0, 0.0, PLAIN),
