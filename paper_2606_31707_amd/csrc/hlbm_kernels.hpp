@@ -1474,7 +1474,10 @@ __global__ __launch_bounds__(256) void k_window_region(const Geo g, const ObjBox
 // state and porosity that the window sweep wrote, one per step (moment-form
 // objectives): one lane per region cell reading its own records, instead of
 // one cache line per population and cell of the lattice.
-template <int Q, typename T>
+// NR: the records of a launch, known to the compiler so that the loads of all
+// are on their way at once (a loop over a number of them: a step of 192x96x64
+// FP16S with closure and a drag plane 34.1 instead of 33.8 us).
+template <int Q, typename T, int NR>
 __global__ __launch_bounds__(256) void k_window_region_copy(const ObjBox ob, const Records rc,
                                                             double* __restrict__ acc_obj) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1483,7 +1486,8 @@ __global__ __launch_bounds__(256) void k_window_region_copy(const ObjBox ob, con
   double sum[N];
 #pragma unroll
   for (int m = 0; m < N; ++m) sum[m] = acc_obj[m * ob.rplane + r];
-  for (int i = 0; i < rc.n; ++i) {
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
     const T* rec = (const T*)rc.rec[i] + r * region_copy_stride(Q, (int)sizeof(T));
     double sd[Q];
 #pragma unroll

@@ -145,7 +145,7 @@ static void primal_mode(hlbm_lattice_s* L, int accumulate) {
     const dim3 rg((unsigned)((rcells + 255) / 256));  // one lane per region cell
     if (!mea && L->rcopy) {  // the sweep copies the region cells' state, the pass follows it
       primal_variant<Q, S, 3, HRR>(L);
-      k_window_region_copy<Q, T><<<rg, 256, 0, L->stream>>>(make_obj(L), Records{{L->rcopy}, 1}, L->acc_obj);
+      k_window_region_copy<Q, T, 1><<<rg, 256, 0, L->stream>>>(make_obj(L), Records{{L->rcopy}, 1}, L->acc_obj);
       return;
     }
     if (mea)
@@ -196,7 +196,14 @@ static dim3 region_grid(const hlbm_lattice_s* L) {  // one lane per region cell
 }
 template <int Q, typename S>
 static hipError_t region_records_impl(hlbm_lattice_s* L, const Records& rc) {
-  k_window_region_copy<Q, typename Prec<S>::T><<<region_grid(L), 256, 0, L->stream>>>(make_obj(L), rc, L->acc_obj);
+  using T = typename Prec<S>::T;
+  const dim3 grid = region_grid(L);
+  switch (rc.n) {
+    case 1: k_window_region_copy<Q, T, 1><<<grid, 256, 0, L->stream>>>(make_obj(L), rc, L->acc_obj); break;
+    case 2: k_window_region_copy<Q, T, 2><<<grid, 256, 0, L->stream>>>(make_obj(L), rc, L->acc_obj); break;
+    case 4: k_window_region_copy<Q, T, 4><<<grid, 256, 0, L->stream>>>(make_obj(L), rc, L->acc_obj); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 hipError_t launch_region_records(hlbm_lattice_s* L, const Records& rc) {
