@@ -804,6 +804,14 @@ hlbm_status hlbm_profile_get(hlbm_lattice L, int32_t kind, double* mean_us, int6
   return HLBM_OK;
 }
 
+hlbm_status hlbm_pass_steps(hlbm_lattice L, int32_t kind, int64_t* steps) {
+  CHECK_LAT(L);
+  if (kind < 0 || kind > 2) return fail(HLBM_E_INVALID, "kind must be 0, 1 or 2");
+  if (!steps) return fail(HLBM_E_INVALID, "null output");
+  *steps = L->pass_steps[kind];
+  return HLBM_OK;
+}
+
 hlbm_status hlbm_set_probe(hlbm_lattice L, int32_t x, int32_t y, int32_t z, int64_t capacity) {
   CHECK_LAT(L);
   if (capacity < 0) return fail(HLBM_E_INVALID, "capacity must be >= 0");
@@ -896,6 +904,7 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
       L->steps += K;
       if (accumulate) L->nsamp += K;
       if (L->probe_buf) L->probe_n += K;
+      if (K > 1) L->pass_steps[accumulate ? 1 : 0] += K;
       k += K;
     }
     done += chunk;
@@ -1088,6 +1097,7 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
       if (s != HLBM_OK) return s;
       L->pvcur ^= 1;  // a pass reads and writes the outlet buffers once
       L->adj_iters += K;
+      if (K > 1) L->pass_steps[2] += K;
       k += K;
     }
     done += chunk;
@@ -1454,9 +1464,14 @@ extern "C" hlbm_status hlbm_group_set(hlbm_group g, const hlbm_lattice* lats, co
 namespace {
 // The packed launches of an n-step run: passes of two steps, in pairs, where a
 // list takes them (members at parity 0), single steps otherwise (AA parity
-// from the step count since the last set).  dry: only counts the outlet buffer
-// toggles (*pv; each adjoint launch makes one).
-hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, int* pv, bool dry) {
+// from the step count since the last set).  dry: only counts (*out) the outlet
+// buffer toggles, one an adjoint launch, and the steps of passes.
+struct GroupRun {
+  int pv = 0;
+  int64_t pass_primal = 0, pass_adjoint = 0;
+};
+hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, bool dry, GroupRun* out) {
+  GroupRun run;
   int flip_p = 0, flip_a = 0, at = g->pv_adjoint;
   hipError_t e = hipSuccess;
   int64_t kp = g->n_primal > 0 ? 0 : n, ka = g->n_adjoint > 0 ? 0 : n;
@@ -1486,8 +1501,11 @@ hipError_t enqueue_group_steps(hlbm_group_s* g, int64_t n, bool passes, int* pv,
     at ^= do_a;
     kp += do_p ? (two_p ? 2 : 1) : 0;
     ka += do_a ? (two_a ? 2 : 1) : 0;
+    run.pass_primal += two_p ? 2 : 0;
+    run.pass_adjoint += two_a ? 2 : 0;
   }
-  *pv = at;
+  run.pv = at;
+  *out = run;
   return e;
 }
 
@@ -1518,8 +1536,8 @@ bool launch_group_graph(hlbm_group_s* g, int64_t n, bool passes) {
       (void)hipGetLastError();
       return false;
     }
-    int pv = 0;
-    const hipError_t e = enqueue_group_steps(g, n, passes, &pv, false);
+    GroupRun run;
+    const hipError_t e = enqueue_group_steps(g, n, passes, false, &run);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(g->stream, &graph);
     hipGraphExec_t exec = nullptr;
@@ -1557,27 +1575,29 @@ extern "C" hlbm_status hlbm_group_step(hlbm_group g, int64_t n) {
     const hlbm_lattice_s* L = g->members[i];
     passes = passes && (g->modes[i] == HLBM_GROUP_ADJOINT ? L->phi2 : L->f2) == g->second[i];
   }
-  int pv = 0;
-  HIP_TRY(enqueue_group_steps(g, n, passes, &pv, true));
+  GroupRun run;
+  HIP_TRY(enqueue_group_steps(g, n, passes, true, &run));
   bool done = false;
   if (n >= kGraphMinSteps && g->stream != nullptr && g->graph_ok) {
     done = launch_group_graph(g, n, passes);
     if (!done) g->graph_ok = false;  // from now on the plain launches below
   }
-  if (!done) HIP_TRY(enqueue_group_steps(g, n, passes, &pv, false));
+  if (!done) HIP_TRY(enqueue_group_steps(g, n, passes, false, &run));
   for (int i = 0; i < g->count; ++i) {
     hlbm_lattice_s* L = g->members[i];
     if (g->modes[i] == HLBM_GROUP_ADJOINT) {
       L->adj_iters += n;
-      L->pvcur ^= pv ^ g->pv_adjoint;
+      L->pvcur ^= run.pv ^ g->pv_adjoint;
+      L->pass_steps[2] += run.pass_adjoint;
     } else {
       L->parity ^= (int)(n & 1);
       L->steps += n;
       if (g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW) L->nsamp += n;
+      L->pass_steps[g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW ? 1 : 0] += run.pass_primal;
       L->adj_ready = 0;
     }
   }
-  g->pv_adjoint = pv;
+  g->pv_adjoint = run.pv;
   g->steps_since_set += n;
   return HLBM_OK;
 }

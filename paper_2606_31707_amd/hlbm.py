@@ -44,6 +44,7 @@ EXPORTS = [
     "hlbm_group_set", "hlbm_group_step", "hlbm_group_synchronize", "hlbm_run_tangent",
     "hlbm_copy_probe", "hlbm_device_bytes", "hlbm_set_porosity_noalloc",
     "hlbm_create_bounded", "hlbm_optional_bytes", "hlbm_optional_held", "hlbm_optional_release",
+    "hlbm_pass_steps",
 ]
 
 GROUP_PRIMAL, GROUP_PRIMAL_WINDOW, GROUP_ADJOINT = 0, 1, 2
@@ -155,6 +156,7 @@ def open_library(path: str):
         "hlbm_synchronize": (i32, [vp]),
         "hlbm_profile_enable": (i32, [vp, i32]),
         "hlbm_profile_get": (i32, [vp, i32, P(dbl), P(i64)]),
+        "hlbm_pass_steps": (i32, [vp, i32, P(i64)]),
         "hlbm_set_probe": (i32, [vp, i32, i32, i32, i64]),
         "hlbm_reconfigure": (i32, [vp, dbl, dbl, dbl]),
         "hlbm_group_create": (i32, [vp, P(vp)]),
@@ -416,6 +418,16 @@ class Lattice:
             us, n = C.c_double(), C.c_int64()
             _check(self._lib.hlbm_profile_get(self._h, kind, C.byref(us), C.byref(n)))
             out[name] = {"mean_us": us.value, "sampled": n.value}
+        return out
+
+    def pass_steps(self) -> dict:
+        """Steps taken in multi-step passes so far, by kind."""
+        out = {}
+        for kind, name in ((PROFILE_PRIMAL, "primal"), (PROFILE_PRIMAL_WINDOW, "primal_window"),
+                           (PROFILE_ADJOINT, "adjoint")):
+            n = C.c_int64()
+            _check(self._lib.hlbm_pass_steps(self._h, kind, C.byref(n)))
+            out[name] = n.value
         return out
 
     def set_probe(self, x, y, z=0, capacity=1 << 18):
