@@ -36,8 +36,9 @@ from paper_2606_31707_amd import hlbm as H  # noqa: E402
 from paper_2606_31707_amd import inputs as I  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2606_31707_amd", f)
-                  for f in ("csrc/hlbm_device.hpp", "csrc/hlbm_kernels.hpp", "build.py")]
+CSRC = os.path.join(ROOT, "paper_2606_31707_amd", "csrc")
+KERNEL_SOURCES = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC))] + \
+                 [os.path.join(ROOT, "paper_2606_31707_amd", "build.py")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic.json")
 
 
@@ -313,7 +314,7 @@ def kernel_source_hash() -> str:
 
 
 def traffic_for(kernel_hash: str, kind: str, case: str = "les_fp32"):
-    """HBM bytes per launch of a sweep kind from the committed rocprofv3
+    """HBM bytes per step of a sweep kind from the committed rocprofv3
     counter summary, if it was taken on the current kernel source."""
     try:
         rec = json.load(open(TRAFFIC_FILE))
@@ -322,9 +323,44 @@ def traffic_for(kernel_hash: str, kind: str, case: str = "les_fp32"):
     if rec.get("kernel_source_sha256") != kernel_hash:
         return None
     try:
-        return rec["cases"][case][kind]["bytes_per_launch"]
+        return rec["cases"][case][kind]["bytes_per_step"]
     except KeyError:
         return None
+
+
+def pass_bytes_per_update(G, region_cells: int = 0):
+    """kind -> bytes per lattice update of a pass of K steps, as a function of K: what a pass
+    cannot do without (two population or phi arrays, the porosity or the frozen data, the window sums and
+    the region's terms once a pass, a small region's records once a step), without the rows, columns and
+    planes that neighbouring tiles read twice."""
+    d = G.desc
+    dim, nsym = (2, 3) if d.stencil == H.D2Q9 else (3, 6)
+    ss, ds, as_ = {H.FP64: (8, 8, 8), H.FP32: (4, 4, 4), H.FP16S: (2, 4, 4)}[d.precision]
+    les = d.smagorinsky_cs > 0.0
+    rfrac, ncoef = region_cells / G.n, 3 + dim + nsym
+    record = 128 * -(-(G.q + 1) * as_ // 128) if 0 < region_cells * 8 <= G.n else 0
+    plain = 2 * G.q * ss + ds
+    return {"primal": lambda K: plain / K,
+            "primal_window": lambda K: (plain + 16 * (1 + dim + les) + 16 * ncoef * rfrac) / K + 2 * record * rfrac,
+            "adjoint": lambda K: (2 * G.q * as_ + as_ * (dim + 1 + les) + 8 * (ncoef - 2) * rfrac) / K}
+
+
+def taken_bytes_per_update(G, steps: dict, before: dict | None = None, region_cells: int = 0):
+    """kind -> (bytes per lattice update of the launches that were taken, share of the steps in
+    passes, steps per pass) for `steps` steps of each kind since `before` (G.passes())."""
+    single, passes, out = G.bytes_per_update(), G.passes(), {}
+    per_pass = pass_bytes_per_update(G, region_cells)
+    for k, (n, m) in passes.items():
+        n0, m0 = before[k] if before else (0, 0)
+        n, m = n - n0, m - m0
+        share = min(1.0, n / steps[k]) if steps.get(k) else 0.0
+        K = n / m if m else 1.0
+        out[k] = ((1.0 - share) * single[k] + share * per_pass[k](K), share, K)
+    return out
+
+
+def region_cells_of(w) -> int:
+    return int(np.prod([h - l + 1 for l, h in zip(w.lo, w.hi)]))
 
 
 # Sweep measurements on lattices that do not fit in any cache: each case runs
@@ -348,8 +384,9 @@ PROBES = [("copy_own", 0, False), ("copy_own_nt", 0, True), ("copy_odd", 1, Fals
 
 
 def report_sweeps(case: str, launches: int):
-    """One sweep case: time per launch of every sweep kind (HIP events around
-    back-to-back launches), algorithmic bytes and bandwidth, and the probe."""
+    """One sweep case: time per step of every sweep kind (HIP events around
+    back-to-back launches), the bytes of the launches taken and the bandwidth,
+    and the probe."""
     wf, prec, coll, track, turb = SWEEP_CASES[case]
     w = wf()
     G = H.Lattice(stencil=w.stencil, precision=prec, nx=w.nx, ny=w.ny, nz=w.nz, tau=w.tau, cs=w.cs,
@@ -358,7 +395,8 @@ def report_sweeps(case: str, launches: int):
     G.build_cylinder(w.xc, w.yc, w.D, noise=I.porosity_noise(w), noise_mode=w.noise_mode, box_half=w.box_half)
     G.init_equilibrium(1.0, I.initial_velocity(w))
     G.set_objective(w.objective, w.lo, w.hi, u0=w.u0)
-    G.run_primal(2)
+    G.run_primal(8)
+    before = G.passes()
     G.profile_enable(launches)
     G.run_primal(launches)
     G.run_primal(launches, accumulate=True)
@@ -367,16 +405,19 @@ def report_sweeps(case: str, launches: int):
     prof = G.profile()
     G.profile_enable(0)
     bpu = G.bytes_per_update()
+    taken = taken_bytes_per_update(G, dict.fromkeys(bpu, launches), before, region_cells_of(w))
     rows = {}
     for k in ("primal", "primal_window", "adjoint"):
         us = prof[k]["mean_us"]
-        gbs = bpu[k] * w.n / us / 1e3
-        rows[k] = {"us_per_launch": us, "bytes_per_update": bpu[k], "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS,
-                   "GLUPS": w.n / us / 1e3}
+        bytes_, share, K = taken[k]
+        gbs = bytes_ * w.n / us / 1e3
+        rows[k] = {"us_per_step": us, "bytes_per_update": bytes_, "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS,
+                   "GLUPS": w.n / us / 1e3, "share_in_passes": share, "steps_per_pass": K,
+                   "single_step_bytes_per_update": bpu[k]}
     for name, pattern, nt in PROBES:
         us = G.copy_probe(pattern, nt, launches)
         gbs = bpu["primal"] * w.n / us / 1e3
-        rows[name] = {"us_per_launch": us, "bytes_per_update": bpu["primal"], "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS}
+        rows[name] = {"us_per_step": us, "bytes_per_update": bpu["primal"], "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS}
     G.close()
     out = {"report": "sweeps", "case": case, "workload": w.name, "cells": w.n,
            "precision": PRECISION_NAMES[prec], "collision": "hrr" if coll == H.COLL_HRR else "bgk",
@@ -397,10 +438,10 @@ def profile_commands(out: str):
     for c in SWEEP_CASES:
         run = f"python3 bench.py --report sweeps --sweep-case {c}"
         cmds[f"{c}/trace"] = (f"rocprofv3 --kernel-trace --stats -d {out}/{c}/trace -o sweep --output-format csv "
-                              f"-- {run} --sweep-launches 20")
+                              f"-- {run} --sweep-launches 24")
         for ctr in ("FETCH_SIZE", "WRITE_SIZE"):
             cmds[f"{c}/{ctr}"] = (f"rocprofv3 --pmc {ctr} -d {out}/{c}/{ctr} -o sweep --output-format csv "
-                                  f"-- {run} --sweep-launches 6")
+                                  f"-- {run} --sweep-launches 8")
     for ctr in ("FETCH_SIZE", "WRITE_SIZE"):
         cmds[f"copy_{ctr}"] = (f"rocprofv3 --pmc {ctr} -d {out}/copy_{ctr} -o copy --output-format csv "
                                f"-- python3 bench.py --copy-calibration-mib 512")
@@ -444,6 +485,12 @@ def kernel_kind(name: str):
         base, targs = it
     if base in ("k_primal", "k_primal_stream", "k_primal_wstream"):
         return ("primal" if targs[3] == "0" else "primal_window"), targs[2]
+    if base in ("k_march2d", "k_march3d"):
+        return "primal", None
+    if base in ("k_window2d", "k_window3d"):
+        return "primal_window", None
+    if base in ("k_march2d_adjoint", "k_march3d_adjoint"):
+        return "adjoint", None
     if base in ("k_window_region", "k_window_region_copy"):
         return "region", None
     if base == "k_adjoint":
@@ -460,11 +507,22 @@ def kernel_kind(name: str):
     return None, None
 
 
+def kernel_steps(name: str) -> int:
+    """Steps (iterations) that a launch of a sweep kernel takes: 2 or 4 of a multi-step pass."""
+    import re
+    m = re.match(r"(?:void )?hlbm::(k_\w+)<([^>]*)>", name)
+    base, targs = (m.group(1), [a.strip() for a in m.group(2).split(",")]) if m else (_itanium_kernel(name) or ("", []))
+    if base in ("k_march2d", "k_window2d", "k_march2d_adjoint"):
+        return int(targs[1])
+    return 2 if base in ("k_march3d", "k_window3d", "k_march3d_adjoint") else 1
+
+
 def les_dispatches(trace_dir: str, w, short):
-    """Total duration, launch count and kernels per sweep kind of the
-    dispatches on lattice `w` in a rocprofv3 kernel trace: sweeps with a grid
-    of at least half the lattice's cells, region passes with the grid of w's
-    objective region (rounded up to whole workgroups).  The reduced record is
+    """Total duration, step count and kernels per sweep kind of the
+    dispatches on lattice `w` in a rocprofv3 kernel trace: single sweeps with a
+    grid of at least half the lattice's cells, multi-step passes with the
+    largest grid of their kernel, region passes with the grid of w's objective
+    region (rounded up to whole workgroups).  The reduced record is
     kept beside the trace (les_dispatches.json) so that the summary can be
     redone without the full trace file."""
     import csv
@@ -472,10 +530,10 @@ def les_dispatches(trace_dir: str, w, short):
     path = os.path.join(trace_dir, "bench_kernel_trace.csv")
     if not os.path.exists(path):
         return json.load(open(cache))
-    region = int(np.prod([h - l + 1 for l, h in zip(w.lo, w.hi)]))
-    region_grid = -(-region // 256) * 256
+    region_grid = -(-region_cells_of(w) // 256) * 256
     acc = {}
     per_kernel = {}
+    found = []  # (kind, name, grid, ns)
     with open(path, newline="") as fh:
         for r in csv.DictReader(fh):
             name = short(r["Kernel_Name"])
@@ -486,17 +544,26 @@ def les_dispatches(trace_dir: str, w, short):
                 grid = int(r["Grid_Size"])
             else:
                 grid = int(r["Grid_Size_X"]) * int(r.get("Grid_Size_Y") or 1) * int(r.get("Grid_Size_Z") or 1)
-            if kind == "region" and grid != region_grid:
+            found.append((kind, name, grid, float(r["End_Timestamp"]) - float(r["Start_Timestamp"])))
+    largest = {}
+    for _, name, grid, _ in found:
+        largest[name] = max(grid, largest.get(name, 0))
+    for kind, name, grid, ns in found:
+        if kind == "region":
+            if grid != region_grid:
                 continue
-            if kind != "region" and grid < w.n // 2:
+        elif kernel_steps(name) > 1:
+            # of the lattice's stencil (the 3D kernels' names say so), on the largest lattice
+            if (w.stencil == I.D3Q19) != ("3d" in name) or grid != largest[name]:
                 continue
-            ns = float(r["End_Timestamp"]) - float(r["Start_Timestamp"])
-            a = acc.setdefault(kind, {"ns": 0.0, "calls": 0, "kernels": []})
-            a["ns"] += ns
-            a["calls"] += 1
-            k = per_kernel.setdefault((kind, name), [0.0, 0])
-            k[0] += ns
-            k[1] += 1
+        elif grid < w.n // 2:
+            continue
+        a = acc.setdefault(kind, {"ns": 0.0, "calls": 0, "kernels": []})
+        a["ns"] += ns
+        a["calls"] += kernel_steps(name)
+        k = per_kernel.setdefault((kind, name), [0.0, 0])
+        k[0] += ns
+        k[1] += 1
     for (kind, name), (ns, calls) in sorted(per_kernel.items()):
         acc[kind]["kernels"].append(f"`{name}` {calls} x {ns / calls / 1e3:.1f} us")
     with open(cache, "w") as fh:
@@ -545,7 +612,7 @@ def summarize_profiles(d: str):
                "cases": {}}
 
     def per_kind(stats_rows):
-        """total ns and launch counts per kind from a kernel-trace stats file."""
+        """total ns and step counts per kind from a kernel-trace stats file."""
         acc = {}
         for r in stats_rows:
             k, _ = kernel_kind(short(r["Name"]))
@@ -553,11 +620,11 @@ def summarize_profiles(d: str):
                 continue
             a = acc.setdefault(k, {"ns": 0.0, "calls": 0, "kernels": []})
             a["ns"] += float(r["TotalDurationNs"])
-            a["calls"] += int(r["Calls"])
+            a["calls"] += int(r["Calls"]) * kernel_steps(short(r["Name"]))
             a["kernels"].append(f"`{short(r['Name'])}` {int(r['Calls'])} x {float(r['AverageNs']) / 1e3:.1f} us")
         return acc
 
-    def launch_us(acc, kind):
+    def step_us(acc, kind):
         if kind not in acc or acc[kind]["calls"] == 0:
             return None
         t = acc[kind]["ns"]
@@ -575,7 +642,7 @@ def summarize_profiles(d: str):
                 continue
             a = acc.setdefault(k, [0.0, 0])
             a[0] += float(r["Counter_Value"])
-            a[1] += 1
+            a[1] += kernel_steps(short(r["Kernel_Name"]))
         return acc
 
     for case in SWEEP_CASES if np.isfinite(cf) else ():
@@ -600,18 +667,22 @@ def summarize_profiles(d: str):
                  + (", Smagorinsky C_S 0.1" if w.cs > 0 else "")
                  + (", full mean populations tracked" if track else "")
                  + (", differentiated closure in the adjoint" if turb == H.TURB_DIFFERENTIATED else ""), "",
-                 f"{w.n} cells; every sweep kind launched back to back (even and odd AA steps alternating). "
+                 f"{w.n} cells; every sweep kind launched back to back, as the library takes it: multi-step passes, "
+                 "or single steps (even and odd AA steps alternating) where there are none. "
                  "Commands (run from the repository root on the MI355X box, `export TMPDIR=/tmp`):", "", "```",
                  cmds[f"{case}/trace"], cmds[f"{case}/FETCH_SIZE"], cmds[f"{case}/WRITE_SIZE"], "```", "",
                  f"Counter values are scaled by what the same counter reads for a plain 512 MiB device copy "
                  f"(FETCH_SIZE x{ff:.3f}, WRITE_SIZE x{wf:.3f}).", "",
-                 "| sweep | B/LU (algorithmic) | trace us / launch | GB/s (algorithmic / trace) | % of 8 TB/s "
-                 "| counter read MB | counter write MB | traffic / algorithmic | library event us |",
+                 "B/LU: bytes per cell and step that the launches taken cannot do without (a pass moves the "
+                 "populations once for its steps; what neighbouring tiles read twice is not counted). All figures "
+                 "per step.", "",
+                 "| sweep | B/LU | trace us | GB/s (B/LU / trace) | % of 8 TB/s "
+                 "| counter read MB | counter write MB | traffic / B/LU | library event us |",
                  "|---|---|---|---|---|---|---|---|---|"]
         bpu = {k: v["bytes_per_update"] for k, v in rep["sweeps"].items()} if rep else {}
         for kind in ("primal", "primal_window", "adjoint", "copy_own", "copy_own_nt", "copy_odd", "copy_odd_nt",
                      "copy_pull"):
-            us = launch_us(acc, kind)
+            us = step_us(acc, kind)
             if us is None or kind not in bpu:
                 continue
             alg = bpu[kind] * w.n
@@ -624,10 +695,10 @@ def summarize_profiles(d: str):
                     rd += fe["region"][0] / nl * ff * 1024
                     wt += wr["region"][0] / nl * wf * 1024
             gbs = alg / us / 1e3
-            ev = rep["sweeps"][kind]["us_per_launch"] if rep else float("nan")
-            rec[kind] = {"us_per_launch": us, "algorithmic_bytes_per_launch": alg, "GB_s": gbs,
-                         "frac": gbs / HBM_PEAK_GBS, "read_bytes_per_launch": rd, "write_bytes_per_launch": wt,
-                         "bytes_per_launch": (rd + wt) if rd is not None else None,
+            ev = rep["sweeps"][kind]["us_per_step"] if rep else float("nan")
+            rec[kind] = {"us_per_step": us, "algorithmic_bytes_per_step": alg, "GB_s": gbs,
+                         "frac": gbs / HBM_PEAK_GBS, "read_bytes_per_step": rd, "write_bytes_per_step": wt,
+                         "bytes_per_step": (rd + wt) if rd is not None else None,
                          "traffic_over_algorithmic": (rd + wt) / alg if rd is not None else None,
                          "library_event_us": ev, "kernels": acc[kind]["kernels"]
                          + (acc["region"]["kernels"] if kind == "primal_window" and "region" in acc else [])}
@@ -670,15 +741,16 @@ def summarize_profiles(d: str):
             lines.append(f"| `{short(r['Name'])}` | {r['Calls']} | {float(r['AverageNs']) / 1e3:.2f} | "
                          f"{float(r['MinNs']) / 1e3:.2f} | {float(r['MaxNs']) / 1e3:.2f} | "
                          f"{float(r['Percentage']):.2f} |")
-        lines += ["", "Per launch of each LES sweep kind (trace durations of the dispatches on the LES lattice, "
-                      "selected by grid size; a window step = its sweep + the region pass):", ""]
+        lines += ["", "Per step of each LES sweep kind (trace durations of the dispatches on the LES lattice, "
+                      "selected by grid size; a pass counts as its steps; a window step = its sweep + the region "
+                      "pass):", ""]
         w = I.les_re3900()
         for kind in ("primal", "primal_window", "adjoint"):
-            us = launch_us(acc, kind)
+            us = step_us(acc, kind)
             if us is None:
                 continue
-            ev = live["sweeps"][kind]["us_per_launch"] if live else None
-            lines.append(f"- {kind}: {us:.1f} us per launch (trace)" +
+            ev = live["sweeps"][kind]["us_per_step"] if live else None
+            lines.append(f"- {kind}: {us:.1f} us per step (trace)" +
                          (f"; the benchmark's own HIP-event figure in an unprofiled run of the same command: "
                           f"{ev:.1f} us" if ev else ""))
         for kind in ("primal", "primal_window", "adjoint", "region"):
@@ -686,7 +758,8 @@ def summarize_profiles(d: str):
                 lines.append(f"  - {kind}: " + "; ".join(acc[kind]["kernels"]))
         if live:
             lines += ["", f"Dominant sweep of the benchmark line: {live['roofline']['kind']} "
-                          f"({live['roofline']['achieved']:.0f} GB/s algorithmic, frac {live['roofline']['frac']:.3f})."]
+                          f"({live['roofline']['achieved']:.0f} GB/s of the bytes its launches cannot do without, "
+                          f"frac {live['roofline']['frac']:.3f})."]
         with open(os.path.join(ROOT, "profiles", "bench_trace_les_re3900_768x384x128.md"), "w") as fh:
             fh.write("\n".join(lines) + "\n")
     except OSError as e:
@@ -845,9 +918,8 @@ def report_les(spinup: int, window: int, adj_iters: int, forms, collision: int =
             variants += [(vname("diff", ta), H.TURB_DIFFERENTIATED, ta) for ta in tau_adjs]
         r["adjoint"] = {}
         p = G.profile()
-        bpu = G.bytes_per_update()
-        r["sweeps"] = {k: {"us_per_launch": p[k]["mean_us"], "GLUPS": w.n / p[k]["mean_us"] / 1e3,
-                           "GB_s": bpu[k] * w.n / p[k]["mean_us"] / 1e3} for k in p if p[k]["sampled"]}
+        r["sweeps"] = {k: {"us_per_step": p[k]["mean_us"], "GLUPS": w.n / p[k]["mean_us"] / 1e3}
+                       for k in p if p[k]["sampled"]}
         for vn, turb, tau_adj in variants:
             ta = time.perf_counter()
             G.profile_enable(97)
@@ -860,11 +932,10 @@ def report_les(spinup: int, window: int, adj_iters: int, forms, collision: int =
                 log(f"les {name} adjoint {vn}: {it} it, residual {rr:.2e}")
             g = G.gradient()
             grads[(name, vn)] = g
-            pa, ba = G.profile()["adjoint"]["mean_us"], G.bytes_per_update()["adjoint"]
+            pa = G.profile()["adjoint"]["mean_us"]
             r["adjoint"][vn] = {"iters": it, "residual": rr, "tol": adj_tol, "converged": st == H.OK,
                                    "seconds": time.perf_counter() - ta,
-                                   "max_abs_grad": float(np.abs(g).max()), "us_per_launch": pa,
-                                   "GB_s": ba * w.n / pa / 1e3 if pa > 0 else None}
+                                   "max_abs_grad": float(np.abs(g).max()), "us_per_step": pa}
             log(f"les {name} adjoint {vn}: {it} it, residual {rr:.2e}")
         r["seconds"] = time.perf_counter() - t0
         res[name] = r
@@ -1092,7 +1163,7 @@ def main():
                     default=None,
                     help="print a secondary measurement report instead of the benchmark line")
     ap.add_argument("--sweep-case", choices=list(SWEEP_CASES), default="les_fp32")
-    ap.add_argument("--sweep-launches", type=int, default=20)
+    ap.add_argument("--sweep-launches", type=int, default=24)
     ap.add_argument("--fields", type=int, default=32)
     ap.add_argument("--fd-fields", type=int, default=2)
     ap.add_argument("--fd-directions", type=int, default=8)
@@ -1216,25 +1287,34 @@ def bench_les(args):
         return f"J {qq.J:.6e}, adjoint {qq.it} it, residual {qq.res:.3e}"
 
     lu, dt, each, prof = timed_queries(q, args.steps, args.warmup, args.profile_every, describe)
-    bpu = q.G.bytes_per_update()
     n = w.n
-    launches = {"primal": q.spinup, "primal_window": q.window, "adjoint": q.it}
+    sweep_steps = {"primal": q.spinup, "primal_window": q.window, "adjoint": q.it}
+    taken = taken_bytes_per_update(q.G, {k: v * (args.steps + args.warmup) for k, v in sweep_steps.items()},
+                                   None, region_cells_of(w))
     sweeps = {}
     for k in ("primal", "primal_window", "adjoint"):
         us = prof[k]["mean_us"]
-        gbs = bpu[k] * n / (us * 1e-6) / 1e9 if us > 0 else 0.0
-        sweeps[k] = {"us_per_launch": us, "launches_per_step": launches[k],
-                     "ms_per_step": us * launches[k] / 1e3, "bytes_per_update": bpu[k],
-                     "GB_s": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS, "launches_timed": prof[k]["sampled"]}
-    dom = max(sweeps, key=lambda k: sweeps[k]["ms_per_step"])
-    names = {"primal": "k_primal<19, float, *, 0, false> (AA step, Smagorinsky, no window)",
-             "primal_window": "k_primal(_stream|_wstream)<19, float, *, 3, false> + k_window_region_copy<19, float> "
-                              "(AA step with the FP64 window: rho, j, tau_eff sums updated once per group of four "
-                              "steps; drag-plane terms by the region pass from the sweep's record of the plane)",
-             "adjoint": "k_adjoint<19, float, *, false, false> (mean-flow adjoint sweep, frozen turbulence)"}
+        bytes_, share, K = taken[k]
+        gbs = bytes_ * n / (us * 1e-6) / 1e9 if us > 0 else 0.0
+        sweeps[k] = {"us_per_step": us, "steps_per_query": sweep_steps[k],
+                     "ms_per_query": us * sweep_steps[k] / 1e3, "bytes_per_update": bytes_,
+                     "share_in_passes": share, "steps_per_pass": K,
+                     "GB_s": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS, "steps_timed": prof[k]["sampled"]}
+    dom = max(sweeps, key=lambda k: sweeps[k]["ms_per_query"])
+    singles = {"primal": "k_primal<19, float, *, 0, false> (AA step, Smagorinsky, no window)",
+               "primal_window": "k_primal(_stream|_wstream)<19, float, *, 3, false> + k_window_region_copy<19, float, 1> "
+                                "(AA step with the FP64 window: rho, j, tau_eff sums updated once per group of four "
+                                "steps; drag-plane terms by the region pass from the sweep's record of the plane)",
+               "adjoint": "k_adjoint<19, float, *, false, false> (mean-flow adjoint sweep, frozen turbulence)"}
+    names = {"primal": "k_march3d<float, false, true> (two steps in one pass, Smagorinsky, no window)",
+             "primal_window": "k_window3d<float, true> + k_window_region_copy<19, float, 2> (two steps in one pass with "
+                              "the FP64 window: rho, j, tau_eff sums read and written once a pass; drag-plane terms by "
+                              "the region pass from the steps' records of the plane)",
+             "adjoint": "k_march3d_adjoint"}
+    names = {k: names[k] if taken[k][1] > 0.5 else singles[k] for k in names}
     d = sweeps[dom]
     khash = kernel_source_hash()
-    log(f"sweeps: " + ", ".join(f"{k} {v['us_per_launch']:.1f} us ({v['GB_s']:.0f} GB/s)" for k, v in sweeps.items())
+    log(f"sweeps: " + ", ".join(f"{k} {v['us_per_step']:.1f} us ({v['GB_s']:.0f} GB/s)" for k, v in sweeps.items())
         + f"; dominant {dom}")
     out = {
         "metric": "primal+adjoint MLUPS (whole mean-flow gradient query)",
@@ -1267,11 +1347,13 @@ def bench_les(args):
         "roofline": {"bound": "hbm", "achieved": d["GB_s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": d["GB_s"] / HBM_PEAK_GBS, "traffic": traffic_for(khash, dom),
                      "kernel": names[dom], "kind": dom,
-                     "bytes_per_update": d["bytes_per_update"], "updates_per_launch": n,
-                     "us_per_launch": d["us_per_launch"],
+                     "bytes_per_update": d["bytes_per_update"], "updates_per_step": n,
+                     "us_per_step": d["us_per_step"], "steps_per_pass": d["steps_per_pass"],
                      "timing": "HIP events on the sweep stream around blocks of back-to-back launches",
-                     "note": "2.9 GB of FP32 populations, 1.5 GB of FP64 window sums and 2.3 GB of FP32 pending "
-                             "window values: HBM-resident"},
+                     "note": "bytes that the launches taken cannot do without (a pass reads and writes the "
+                             "populations and the window sums once for its steps; the rows, columns and planes "
+                             "that neighbouring tiles read twice are not counted); two arrays of 2.9 GB of FP32 "
+                             "populations and 1.5 GB of FP64 window sums: HBM-resident"},
         "sweeps": sweeps,
     }
     if not args.no_vortex:
@@ -1340,10 +1422,12 @@ def bench_vortex(args):
                 f"residual {qq.adj_res:.2e}")
 
     lu, dt, each, prof = timed_queries(q, args.steps, args.warmup, args.profile_every, describe)
-    bpu = q.G.bytes_per_update()
     n = w.n
     kus = prof["primal"]["mean_us"]
-    achieved = bpu["primal"] * n / (kus * 1e-6) / 1e9 if kus > 0 else 0.0
+    steps, passes = q.G.passes()["primal"]
+    K = steps / passes if passes else 1.0
+    bytes_ = pass_bytes_per_update(q.G)["primal"](K) if passes else q.G.bytes_per_update()["primal"]
+    achieved = bytes_ * n / (kus * 1e-6) / 1e9 if kus > 0 else 0.0
     out = {
         "metric": "primal+adjoint MLUPS (whole mean-flow gradient query)",
         "value": lu / dt / 1e6,
@@ -1366,11 +1450,12 @@ def bench_vortex(args):
                    "adjoint_converged": q.converged, "J_mean": q.J},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_primal<9, double> (AA step, no window)",
-                     "bytes_per_update": bpu["primal"], "updates_per_launch": n, "us_per_launch": kus,
+                     "kernel": "k_march2d<double, 4, false, false> (four steps in one pass, no window)" if passes else
+                               "k_primal<9, double> (AA step, no window)",
+                     "bytes_per_update": bytes_, "updates_per_step": n, "us_per_step": kus, "steps_per_pass": K,
                      "timing": "HIP events on the sweep stream around blocks of back-to-back launches",
-                     "note": "effective bandwidth: the 36 MB of FP64 populations stay resident in the 256 MB "
-                             "Infinity Cache, so this is not an HBM fraction"},
+                     "note": "the two arrays of 32 MB of FP64 populations stay resident in the 256 MB Infinity Cache, "
+                             "and a pass is bound by the vector units: not an HBM fraction"},
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, args.cpu_primal, args.cpu_adjoint)

@@ -351,8 +351,9 @@ hlbm_status hlbm_synchronize(hlbm_lattice lat);
 hlbm_status hlbm_profile_enable(hlbm_lattice lat, int32_t every);
 hlbm_status hlbm_profile_get(hlbm_lattice lat, int32_t kind, double* mean_us, int64_t* sampled);
 /* Steps of a kind (as above) that the handle has taken in multi-step passes,
- * its own or a group's, since its creation. */
-hlbm_status hlbm_pass_steps(hlbm_lattice lat, int32_t kind, int64_t* steps);
+ * its own or a group's, since its creation, and the number of those passes
+ * (either output may be NULL). */
+hlbm_status hlbm_pass_steps(hlbm_lattice lat, int32_t kind, int64_t* steps, int64_t* passes);
 /* Velocity probe: every primal step records u_y of cell (x, y, z) (the
  * pre-collision state of that step) into a device ring of `capacity` values
  * (capacity 0 removes the probe).  hlbm_get_probe copies the last

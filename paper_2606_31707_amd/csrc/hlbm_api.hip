@@ -804,11 +804,11 @@ hlbm_status hlbm_profile_get(hlbm_lattice L, int32_t kind, double* mean_us, int6
   return HLBM_OK;
 }
 
-hlbm_status hlbm_pass_steps(hlbm_lattice L, int32_t kind, int64_t* steps) {
+hlbm_status hlbm_pass_steps(hlbm_lattice L, int32_t kind, int64_t* steps, int64_t* passes) {
   CHECK_LAT(L);
   if (kind < 0 || kind > 2) return fail(HLBM_E_INVALID, "kind must be 0, 1 or 2");
-  if (!steps) return fail(HLBM_E_INVALID, "null output");
-  *steps = L->pass_steps[kind];
+  if (steps) *steps = L->pass_steps[kind];
+  if (passes) *passes = L->pass_count[kind];
   return HLBM_OK;
 }
 
@@ -904,7 +904,10 @@ hlbm_status hlbm_run_primal(hlbm_lattice L, int64_t n_steps, int32_t accumulate,
       L->steps += K;
       if (accumulate) L->nsamp += K;
       if (L->probe_buf) L->probe_n += K;
-      if (K > 1) L->pass_steps[accumulate ? 1 : 0] += K;
+      if (K > 1) {
+        L->pass_steps[accumulate ? 1 : 0] += K;
+        L->pass_count[accumulate ? 1 : 0] += 1;
+      }
       k += K;
     }
     done += chunk;
@@ -1097,7 +1100,10 @@ hlbm_status hlbm_solve_adjoint(hlbm_lattice L, const hlbm_adjoint_opts* o, hlbm_
       if (s != HLBM_OK) return s;
       L->pvcur ^= 1;  // a pass reads and writes the outlet buffers once
       L->adj_iters += K;
-      if (K > 1) L->pass_steps[2] += K;
+      if (K > 1) {
+        L->pass_steps[2] += K;
+        L->pass_count[2] += 1;
+      }
       k += K;
     }
     done += chunk;
@@ -1589,11 +1595,14 @@ extern "C" hlbm_status hlbm_group_step(hlbm_group g, int64_t n) {
       L->adj_iters += n;
       L->pvcur ^= run.pv ^ g->pv_adjoint;
       L->pass_steps[2] += run.pass_adjoint;
+      L->pass_count[2] += run.pass_adjoint / 2;
     } else {
       L->parity ^= (int)(n & 1);
       L->steps += n;
       if (g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW) L->nsamp += n;
-      L->pass_steps[g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW ? 1 : 0] += run.pass_primal;
+      const int kind = g->modes[i] == HLBM_GROUP_PRIMAL_WINDOW ? 1 : 0;
+      L->pass_steps[kind] += run.pass_primal;
+      L->pass_count[kind] += run.pass_primal / 2;
       L->adj_ready = 0;
     }
   }

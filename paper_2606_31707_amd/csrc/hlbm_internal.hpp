@@ -115,7 +115,7 @@ struct hlbm_lattice_s {
   // Arrays of the multi-step passes (f2, rcopy2, phi2), which the handle does
   // without where they do not fit: bytes held, and the most it may hold.
   uint64_t optional_held = 0, optional_limit = UINT64_MAX;
-  int64_t pass_steps[3] = {0, 0, 0};  // steps taken in passes so far (hlbm_pass_steps)
+  int64_t pass_steps[3] = {0, 0, 0}, pass_count[3] = {0, 0, 0};  // steps taken in passes so far, those passes
   int phi2_asked = 0;  // phi2 is asked for once, by the first adjoint solve outside a capture
   // list of all handles, and the calls that are using this one's optional
   // arrays (both under the list's mutex)

@@ -156,7 +156,7 @@ def open_library(path: str):
         "hlbm_synchronize": (i32, [vp]),
         "hlbm_profile_enable": (i32, [vp, i32]),
         "hlbm_profile_get": (i32, [vp, i32, P(dbl), P(i64)]),
-        "hlbm_pass_steps": (i32, [vp, i32, P(i64)]),
+        "hlbm_pass_steps": (i32, [vp, i32, P(i64), P(i64)]),
         "hlbm_set_probe": (i32, [vp, i32, i32, i32, i64]),
         "hlbm_reconfigure": (i32, [vp, dbl, dbl, dbl]),
         "hlbm_group_create": (i32, [vp, P(vp)]),
@@ -422,12 +422,16 @@ class Lattice:
 
     def pass_steps(self) -> dict:
         """Steps taken in multi-step passes so far, by kind."""
+        return {k: v[0] for k, v in self.passes().items()}
+
+    def passes(self) -> dict:
+        """(steps taken in multi-step passes so far, number of those passes) by kind."""
         out = {}
         for kind, name in ((PROFILE_PRIMAL, "primal"), (PROFILE_PRIMAL_WINDOW, "primal_window"),
                            (PROFILE_ADJOINT, "adjoint")):
-            n = C.c_int64()
-            _check(self._lib.hlbm_pass_steps(self._h, kind, C.byref(n)))
-            out[name] = n.value
+            n, m = C.c_int64(), C.c_int64()
+            _check(self._lib.hlbm_pass_steps(self._h, kind, C.byref(n), C.byref(m)))
+            out[name] = (n.value, m.value)
         return out
 
     def set_probe(self, x, y, z=0, capacity=1 << 18):
