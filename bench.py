@@ -385,35 +385,41 @@ PROBES = [("copy_own", 0, False), ("copy_own_nt", 0, True), ("copy_odd", 1, Fals
 
 def report_sweeps(case: str, launches: int):
     """One sweep case: time per step of every sweep kind (HIP events around
-    back-to-back launches), the bytes of the launches taken and the bandwidth,
-    and the probe."""
+    back-to-back launches) in multi-step passes, where the library takes them,
+    and in single steps, the bytes that these cannot do without and the
+    bandwidth, and the probe."""
     wf, prec, coll, track, turb = SWEEP_CASES[case]
     w = wf()
-    G = H.Lattice(stencil=w.stencil, precision=prec, nx=w.nx, ny=w.ny, nz=w.nz, tau=w.tau, cs=w.cs,
-                  bc_x=H.BC_INLET_OUTLET, bc_y=w.bc_y, bc_z=w.bc_z, inlet_profile=w.inlet_profile, u_in=w.u_max,
-                  track_mean_populations=track, collision=coll)
-    G.build_cylinder(w.xc, w.yc, w.D, noise=I.porosity_noise(w), noise_mode=w.noise_mode, box_half=w.box_half)
-    G.init_equilibrium(1.0, I.initial_velocity(w))
-    G.set_objective(w.objective, w.lo, w.hi, u0=w.u0)
-    G.run_primal(8)
-    before = G.passes()
-    G.profile_enable(launches)
-    G.run_primal(launches)
-    G.run_primal(launches, accumulate=True)
-    tau_adj = LES_TAU_ADJ if w.cs > 0 else 0.0
-    G.solve_adjoint(H.SOURCE_MEAN, tau_adj=tau_adj, turb=turb, max_iters=launches)
-    prof = G.profile()
-    G.profile_enable(0)
-    bpu = G.bytes_per_update()
-    taken = taken_bytes_per_update(G, dict.fromkeys(bpu, launches), before, region_cells_of(w))
     rows = {}
-    for k in ("primal", "primal_window", "adjoint"):
-        us = prof[k]["mean_us"]
-        bytes_, share, K = taken[k]
-        gbs = bytes_ * w.n / us / 1e3
-        rows[k] = {"us_per_step": us, "bytes_per_update": bytes_, "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS,
-                   "GLUPS": w.n / us / 1e3, "share_in_passes": share, "steps_per_pass": K,
-                   "single_step_bytes_per_update": bpu[k]}
+    for limit in (None, 0):  # as the library takes them, and in single steps
+        G = H.Lattice(stencil=w.stencil, precision=prec, nx=w.nx, ny=w.ny, nz=w.nz, tau=w.tau, cs=w.cs,
+                      bc_x=H.BC_INLET_OUTLET, bc_y=w.bc_y, bc_z=w.bc_z, inlet_profile=w.inlet_profile, u_in=w.u_max,
+                      track_mean_populations=track, collision=coll, optional_limit=limit)
+        G.build_cylinder(w.xc, w.yc, w.D, noise=I.porosity_noise(w), noise_mode=w.noise_mode, box_half=w.box_half)
+        G.init_equilibrium(1.0, I.initial_velocity(w))
+        G.set_objective(w.objective, w.lo, w.hi, u0=w.u0)
+        G.run_primal(8)
+        before = G.passes()
+        G.profile_enable(launches)
+        G.run_primal(launches)
+        G.run_primal(launches, accumulate=True)
+        tau_adj = LES_TAU_ADJ if w.cs > 0 else 0.0
+        G.solve_adjoint(H.SOURCE_MEAN, tau_adj=tau_adj, turb=turb, max_iters=launches)
+        prof = G.profile()
+        G.profile_enable(0)
+        bpu = G.bytes_per_update()
+        taken = taken_bytes_per_update(G, dict.fromkeys(bpu, launches), before, region_cells_of(w))
+        for k in ("primal", "primal_window", "adjoint"):
+            us = prof[k]["mean_us"]
+            bytes_, share, K = taken[k]
+            if limit is None and share == 0.0:
+                continue  # no passes: the single steps below
+            gbs = bytes_ * w.n / us / 1e3
+            rows[k if limit == 0 else k + "_pass"] = {
+                "us_per_step": us, "bytes_per_update": bytes_, "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS,
+                "GLUPS": w.n / us / 1e3, "share_in_passes": share, "steps_per_pass": K}
+        if limit is None:
+            G.close()
     for name, pattern, nt in PROBES:
         us = G.copy_probe(pattern, nt, launches)
         gbs = bpu["primal"] * w.n / us / 1e3
@@ -486,11 +492,13 @@ def kernel_kind(name: str):
     if base in ("k_primal", "k_primal_stream", "k_primal_wstream"):
         return ("primal" if targs[3] == "0" else "primal_window"), targs[2]
     if base in ("k_march2d", "k_march3d"):
-        return "primal", None
+        return "primal_pass", None
     if base in ("k_window2d", "k_window3d"):
-        return "primal_window", None
+        return "primal_window_pass", None
     if base in ("k_march2d_adjoint", "k_march3d_adjoint"):
-        return "adjoint", None
+        return "adjoint_pass", None
+    if base == "k_window_region_copy" and len(targs) > 2 and targs[2] != "1":
+        return "region_pass", None  # the records of several steps
     if base in ("k_window_region", "k_window_region_copy"):
         return "region", None
     if base == "k_adjoint":
@@ -549,7 +557,7 @@ def les_dispatches(trace_dir: str, w, short):
     for _, name, grid, _ in found:
         largest[name] = max(grid, largest.get(name, 0))
     for kind, name, grid, ns in found:
-        if kind == "region":
+        if kind in ("region", "region_pass"):
             if grid != region_grid:
                 continue
         elif kernel_steps(name) > 1:
@@ -628,8 +636,9 @@ def summarize_profiles(d: str):
         if kind not in acc or acc[kind]["calls"] == 0:
             return None
         t = acc[kind]["ns"]
-        if kind == "primal_window" and "region" in acc:
-            t += acc["region"]["ns"]  # the region pass belongs to the window step
+        for window, region in (("primal_window", "region"), ("primal_window_pass", "region_pass")):
+            if kind == window and region in acc:
+                t += acc[region]["ns"]  # the region pass belongs to the window step
         return t / acc[kind]["calls"] / 1e3
 
     def counters(sub, counter):
@@ -667,8 +676,9 @@ def summarize_profiles(d: str):
                  + (", Smagorinsky C_S 0.1" if w.cs > 0 else "")
                  + (", full mean populations tracked" if track else "")
                  + (", differentiated closure in the adjoint" if turb == H.TURB_DIFFERENTIATED else ""), "",
-                 f"{w.n} cells; every sweep kind launched back to back, as the library takes it: multi-step passes, "
-                 "or single steps (even and odd AA steps alternating) where there are none. "
+                 f"{w.n} cells; every sweep kind launched back to back, in multi-step passes (`_pass`) where the library "
+                 "takes them and, on a lattice without the arrays for them, in single steps (even and odd AA steps "
+                 "alternating). "
                  "Commands (run from the repository root on the MI355X box, `export TMPDIR=/tmp`):", "", "```",
                  cmds[f"{case}/trace"], cmds[f"{case}/FETCH_SIZE"], cmds[f"{case}/WRITE_SIZE"], "```", "",
                  f"Counter values are scaled by what the same counter reads for a plain 512 MiB device copy "
@@ -680,8 +690,8 @@ def summarize_profiles(d: str):
                  "| counter read MB | counter write MB | traffic / B/LU | library event us |",
                  "|---|---|---|---|---|---|---|---|---|"]
         bpu = {k: v["bytes_per_update"] for k, v in rep["sweeps"].items()} if rep else {}
-        for kind in ("primal", "primal_window", "adjoint", "copy_own", "copy_own_nt", "copy_odd", "copy_odd_nt",
-                     "copy_pull"):
+        for kind in ("primal_pass", "primal_window_pass", "adjoint_pass", "primal", "primal_window", "adjoint",
+                     "copy_own", "copy_own_nt", "copy_odd", "copy_odd_nt", "copy_pull"):
             us = step_us(acc, kind)
             if us is None or kind not in bpu:
                 continue
@@ -691,9 +701,10 @@ def summarize_profiles(d: str):
             if nl:
                 rd = fe[kind][0] / nl * ff * 1024
                 wt = wr[kind][0] / wr[kind][1] * wf * 1024
-                if kind == "primal_window" and "region" in fe:
-                    rd += fe["region"][0] / nl * ff * 1024
-                    wt += wr["region"][0] / nl * wf * 1024
+                for window, region in (("primal_window", "region"), ("primal_window_pass", "region_pass")):
+                    if kind == window and region in fe:
+                        rd += fe[region][0] / nl * ff * 1024
+                        wt += wr[region][0] / nl * wf * 1024
             gbs = alg / us / 1e3
             ev = rep["sweeps"][kind]["us_per_step"] if rep else float("nan")
             rec[kind] = {"us_per_step": us, "algorithmic_bytes_per_step": alg, "GB_s": gbs,
@@ -701,7 +712,9 @@ def summarize_profiles(d: str):
                          "bytes_per_step": (rd + wt) if rd is not None else None,
                          "traffic_over_algorithmic": (rd + wt) / alg if rd is not None else None,
                          "library_event_us": ev, "kernels": acc[kind]["kernels"]
-                         + (acc["region"]["kernels"] if kind == "primal_window" and "region" in acc else [])}
+                         + (acc["region"]["kernels"] if kind == "primal_window" and "region" in acc else [])
+                         + (acc["region_pass"]["kernels"] if kind == "primal_window_pass" and "region_pass" in acc
+                            else [])}
             tr = f"{(rd + wt) / alg:.3f}" if rd is not None else "—"
             lines.append(f"| {kind} | {bpu[kind]:.1f} | {us:.1f} | {gbs:.0f} | {gbs / HBM_PEAK_GBS * 100:.1f} | "
                          + (f"{rd / 1e6:.0f} | {wt / 1e6:.0f} | " if rd is not None else "— | — | ")
@@ -745,15 +758,16 @@ def summarize_profiles(d: str):
                       "selected by grid size; a pass counts as its steps; a window step = its sweep + the region "
                       "pass):", ""]
         w = I.les_re3900()
-        for kind in ("primal", "primal_window", "adjoint"):
+        for kind in ("primal_pass", "primal_window_pass", "adjoint_pass", "primal", "primal_window", "adjoint"):
             us = step_us(acc, kind)
             if us is None:
                 continue
-            ev = live["sweeps"][kind]["us_per_step"] if live else None
+            ev = live["sweeps"][kind.replace("_pass", "")]["us_per_step"] if live else None
             lines.append(f"- {kind}: {us:.1f} us per step (trace)" +
                          (f"; the benchmark's own HIP-event figure in an unprofiled run of the same command: "
                           f"{ev:.1f} us" if ev else ""))
-        for kind in ("primal", "primal_window", "adjoint", "region"):
+        for kind in ("primal_pass", "primal_window_pass", "adjoint_pass", "region_pass", "primal", "primal_window",
+                     "adjoint", "region"):
             if kind in acc:
                 lines.append(f"  - {kind}: " + "; ".join(acc[kind]["kernels"]))
         if live:
@@ -1345,7 +1359,8 @@ def bench_les(args):
                                    f"the last {LES_CHECK} sweeps, reported, not a convergence claim",
                    "J_mean": q.J},
         "roofline": {"bound": "hbm", "achieved": d["GB_s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": d["GB_s"] / HBM_PEAK_GBS, "traffic": traffic_for(khash, dom),
+                     "frac": d["GB_s"] / HBM_PEAK_GBS,
+                     "traffic": traffic_for(khash, dom + ("_pass" if d["share_in_passes"] > 0.5 else "")),
                      "kernel": names[dom], "kind": dom,
                      "bytes_per_update": d["bytes_per_update"], "updates_per_step": n,
                      "us_per_step": d["us_per_step"], "steps_per_pass": d["steps_per_pass"],

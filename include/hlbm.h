@@ -139,8 +139,10 @@ typedef enum { HLBM_COLL_BGK = 0, HLBM_COLL_HRR = 1 } hlbm_collision;
  * otherwise (a lattice that stays in that cache from one step to the next
  * is 5-20 % slower with the hints, a larger D2Q9 one 5-20 % faster (adjoint
  * 4-5 %), D3Q19 1-2 %).  PLAIN and STREAMING force either.  Results are
- * bitwise identical under every policy, for either collision.  Every other
- * kernel uses plain accesses. */
+ * bitwise identical under every policy, for either collision.  These are the
+ * sweeps of single steps; multi-step passes, which most lattices take (see
+ * hlbm_run_primal), and every other kernel use plain accesses whatever the
+ * policy. */
 typedef enum { HLBM_CACHE_AUTO = 0, HLBM_CACHE_PLAIN = 1, HLBM_CACHE_STREAMING = 2 } hlbm_cache_policy;
 
 typedef struct {
@@ -273,8 +275,8 @@ hlbm_status hlbm_set_objective(hlbm_lattice lat, int32_t kind, const int32_t lo[
 
 /* Advance n_steps collide-and-stream steps (in-place AA pattern, or two or
  * four steps in one pass between two population arrays where the lattice has
- * a second one: the same results bit for bit; a captured run takes single
- * steps).  If
+ * a second one and its shape makes passes pay: the same results bit for bit; a
+ * captured run takes single steps).  If
  * accumulate != 0 every step adds its pre-collision state to the FP64 window
  * (rho, j, optional f, tau_eff, objective terms and dJ/df, dJ/dd
  * coefficients).  If steady_tol > 0, every check_every steps the call stops

@@ -500,12 +500,16 @@ __device__ __forceinline__ void march2d(const Geo& g, const Coll& c, const Strip
 }
 
 // Wavefronts per SIMD the register allocation aims at: at 3 the FP64 passes of
-// four steps spill (1100 x 410: 11.2 us a step instead of 6.1), the others fit.
+// four steps spill (1100 x 410: 11.2 us a step instead of 6.1).  As given, no
+// FP64 or FP16 pass uses scratch; of the FP32 ones BGK with closure does, 10
+// registers (44 bytes a lane) with four steps and 9 with two, without 1 and 3.
 template <typename S, int K>
 constexpr int march2d_waves() {
   return sizeof(S) == 8 ? (K > 2 ? 2 : 3) : (K > 2 ? 4 : 6);
 }
-// With window sums, which wait in registers as well.
+// With window sums, which wait in registers as well.  Without a large region's
+// terms nothing spills; with them the passes of four do (56 to 167 registers; they
+// pay beyond the caches only), and FP64 with closure (31, 96 bytes a lane).
 template <typename S, int K, bool LARGE>
 constexpr int window2d_waves() {
   return LARGE || sizeof(S) == 8 || K > 2 ? 2 : 4;

@@ -17,7 +17,10 @@
 // and columns that neighbours recompute.  Its stores of whole rows shifted by
 // one cell do not fill 128-byte lines; with stores aligned to lines the FP32
 // pass takes 684 instead of 840 us, but no layout of 64 own columns was found
-// whose halo loads did not cost that again (816 us at best).  us a step, single
+// whose halo loads did not cost that again (816 us at best).  The plane bases of
+// loads and stores do not all fit the scalar registers: 90 of them spill to
+// vector lanes in FP32 with closure, 201 with the window's, 109 to 225 in FP64
+// (there a window with closure also spills 4 vector registers).  us a step, single
 // steps / passes: 768x384x128 FP32 1104 / 845, FP64 2262 / 1558; 756x168x84
 // with walls FP32 301 / 204, FP64 612 / 431; 192x96x64 with walls FP32 31.4 /
 // 31.4 (periodic 26.0), FP64 56.4 / 54.4.

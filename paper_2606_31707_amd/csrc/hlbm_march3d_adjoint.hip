@@ -2,8 +2,8 @@
 // (BGK, frozen relaxation time, moment-form objectives).
 //
 // What bounds it: instructions (a level of the adjoint and its share of the
-// scalar registers' spills take 600 in FP32, twice the primal's), so that it pays only where
-// single iterations are bound by FP64 traffic from HBM.
+// scalar registers' spills, 362 in FP64, take 600 in FP32, twice the primal's), so
+// that it pays only where single iterations are bound by FP64 traffic from HBM.
 // The tiles of the primal passes (hlbm_march3d.hpp): phihat streams as the
 // populations do.  The frozen data of a plane waits one plane in registers for
 // level 1; the source of the objective's region is read at each level.  Nothing

@@ -7,7 +7,8 @@
 // adjoint members.  One body serves all window members (closure, sums and
 // objective terms by runtime flags), one the plain ones: bodies for strips
 // without ends or walls as well outgrow the instruction cache and the registers
-// (19.7 us a step instead of 16.5).  12 members of 128 x 64 to 512 x 256, FP32: single
+// (19.7 us a step instead of 16.5).  The three bodies fill 256 registers and spill
+// (FP64 57, 216 bytes a lane; FP32 and FP16S 10, 44 bytes).  12 members of 128 x 64 to 512 x 256, FP32: single
 // steps 27.1 us a step, passes 15.8.
 
 #include "hlbm_march2d.hpp"

@@ -13,7 +13,7 @@ namespace hlbm {
 // terms do not fit beside two levels' state.
 // us a step, single steps / passes: 1100 x 410 FP32 9.5 / 5.0, with a drag plane
 // 13.0 / 7.0, with a dissipation box 12.2 / 9.1, FP64 15.1 / 9.6; 8192 x 4096
-// FP32 608 / 248, FP16S 413 / 199; 768x384x128 FP32 with closure 1445 / 1337;
+// FP32 608 / 248, FP16S 413 / 199; 768x384x128 FP32 with closure 1462 / 1390;
 // 756x168x84 FP64 881 / 523.
 int window_pass_limit(const hlbm_lattice_s* L) {
   const hlbm_desc& d = L->desc;

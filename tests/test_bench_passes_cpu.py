@@ -13,14 +13,15 @@ sys.path.insert(0, ROOT)
 def test_pass_kernels_map_to_sweep_kinds_and_steps():
     import bench
     cases = {
-        "void hlbm::k_march2d<double, 4, false, false>(hlbm::Geo, hlbm::MarchColl)": ("primal", 4),
-        "_ZN4hlbm9k_march2dIDF16_Li2ELb0ELb1EEEvNS_3GeoE": ("primal", 2),
-        "void hlbm::k_window2d<float, 2, false, true>(hlbm::Geo)": ("primal_window", 2),
-        "void hlbm::k_march2d_adjoint<float, 4>(hlbm::Geo)": ("adjoint", 4),
-        "void hlbm::k_march3d<float, false, true>(hlbm::Geo)": ("primal", 2),
-        "void hlbm::k_window3d<float, true>(hlbm::Geo)": ("primal_window", 2),
-        "void hlbm::k_march3d_adjoint<double>(hlbm::Geo)": ("adjoint", 2),
-        "void hlbm::k_window_region_copy<19, float, 2>(hlbm::ObjBox)": ("region", 1),
+        "void hlbm::k_march2d<double, 4, false, false>(hlbm::Geo, hlbm::MarchColl)": ("primal_pass", 4),
+        "_ZN4hlbm9k_march2dIDF16_Li2ELb0ELb1EEEvNS_3GeoE": ("primal_pass", 2),
+        "void hlbm::k_window2d<float, 2, false, true>(hlbm::Geo)": ("primal_window_pass", 2),
+        "void hlbm::k_march2d_adjoint<float, 4>(hlbm::Geo)": ("adjoint_pass", 4),
+        "void hlbm::k_march3d<float, false, true>(hlbm::Geo)": ("primal_pass", 2),
+        "void hlbm::k_window3d<float, true>(hlbm::Geo)": ("primal_window_pass", 2),
+        "void hlbm::k_march3d_adjoint<double>(hlbm::Geo)": ("adjoint_pass", 2),
+        "void hlbm::k_window_region_copy<19, float, 2>(hlbm::ObjBox)": ("region_pass", 1),
+        "void hlbm::k_window_region_copy<19, float, 1>(hlbm::ObjBox)": ("region", 1),
         "void hlbm::k_primal<19, float, true, 3, false>(hlbm::Geo)": ("primal_window", 1),
         "__amd_rocclr_copyBuffer": (None, 1),
     }
