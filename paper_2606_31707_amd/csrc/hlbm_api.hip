@@ -48,10 +48,12 @@ void dev_free(void* p) {
 // calls, are no part of a handle's footprint, and are given back, whichever
 // handle holds them, when an allocation of the library does not fit beside
 // them.  Calls that launch passes mark their handles (PassScope), allocate
-// nothing in the meantime but their own optional arrays, and are waited for.
+// nothing in the meantime but their own optional arrays, and are waited for;
+// others wait until that is done.
 std::mutex g_opt_mu;
 std::condition_variable g_opt_cv;
 hlbm_lattice_s* g_opt_head = nullptr;
+int g_opt_wanted = 0;  // threads that want arrays back
 
 void opt_register(hlbm_lattice_s* L) {
   std::lock_guard<std::mutex> lock(g_opt_mu);
@@ -70,7 +72,8 @@ struct PassScope {
   hlbm_lattice_s* const* lats;
   int n;
   PassScope(hlbm_lattice_s* const* l, int count) : lats(l), n(count) {
-    std::lock_guard<std::mutex> lock(g_opt_mu);
+    std::unique_lock<std::mutex> lock(g_opt_mu);
+    while (g_opt_wanted > 0) g_opt_cv.wait(lock);
     for (int i = 0; i < n; ++i) lats[i]->opt_busy += 1;
   }
   ~PassScope() {
@@ -96,6 +99,7 @@ bool opt_reclaim() {
   if (hipGetDevice(&dev) != hipSuccess) return false;
   std::unique_lock<std::mutex> lock(g_opt_mu);
   bool any = false;
+  g_opt_wanted += 1;
   for (hlbm_lattice_s* L = g_opt_head; L;) {
     if (L->device != dev || L->optional_held == 0) {
       L = L->opt_next;
@@ -105,12 +109,14 @@ bool opt_reclaim() {
     } else {
       if (hipDeviceSynchronize() != hipSuccess) {
         (void)hipGetLastError();
-        return any;
+        break;
       }
       opt_drop(L);
       any = true;
     }
   }
+  g_opt_wanted -= 1;
+  g_opt_cv.notify_all();
   return any;
 }
 
@@ -157,6 +163,7 @@ void lat_alloc_optional(hlbm_lattice_s* L, void** p, size_t bytes, void** extra 
     dev_free(a);
     return;
   }
+  std::lock_guard<std::mutex> lock(g_opt_mu);
   *p = a;
   if (extra_bytes) *extra = b;
   L->optional_held += all;
@@ -466,7 +473,10 @@ hlbm_status hlbm_optional_held(hlbm_lattice L, uint64_t* bytes) {
 hlbm_status hlbm_optional_release(hlbm_lattice L) {
   CHECK_LAT(L);
   std::unique_lock<std::mutex> lock(g_opt_mu);
+  g_opt_wanted += 1;
   while (L->opt_busy > 0) g_opt_cv.wait(lock);
+  g_opt_wanted -= 1;
+  g_opt_cv.notify_all();
   L->optional_limit = 0;
   if (L->optional_held == 0) return HLBM_OK;
   HIP_TRY(hipDeviceSynchronize());  // groups run passes on streams of their own

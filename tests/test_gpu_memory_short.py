@@ -111,19 +111,22 @@ def test_another_lattice_makes_room_and_takes_no_optional_arrays():
 
 
 def test_arrays_in_use_by_another_thread_are_waited_for():
+    """A thread that steps a lattice without a pause, in passes, while another one creates a lattice
+    that needs the room of its second array."""
     from paper_2606_31707_amd import hlbm as H
     say("memory short: threads")
-    steps = [8] * 40
-    ref = reference(H, 4096, 2048, 0, steps)
     import torch
     A = lat(H, 4096, 2048, 0, stream=torch.cuda.Stream().cuda_stream)
-    failed = []
+    assert A.optional_held() > 0
+    failed, calls, created = [], [0], threading.Event()
 
     def run():
         try:
-            for n in steps:
-                A.run_primal(n)
-            A.synchronize()
+            while calls[0] < 20 or (not created.is_set() and calls[0] < 2000):
+                A.run_primal(8)
+                calls[0] += 1
+                if calls[0] % 20 == 0:
+                    A.synchronize()
         except Exception as e:  # reported by the main thread
             failed.append(e)
 
@@ -131,9 +134,11 @@ def test_arrays_in_use_by_another_thread_are_waited_for():
         t = threading.Thread(target=run)
         t.start()
         B = lat(H, 8192, 2560, 0)  # 1.7 GB: fits where A's second array was
+        created.set()
         t.join()
         B.close()
-    assert not failed
+    assert not failed and calls[0] < 2000
     assert A.optional_held() == 0
-    assert np.array_equal(state(H, A), ref)
+    A.synchronize()
+    assert np.array_equal(state(H, A), reference(H, 4096, 2048, 0, [8] * calls[0]))
     A.close()
