@@ -515,6 +515,17 @@ def kernel_kind(name: str):
     return None, None
 
 
+def short_kernel_name(name: str) -> str:
+    """A kernel's name in a trace without return type, arguments and unnamed namespaces."""
+    name = name.replace("void ", "", 1).replace("(anonymous namespace)::", "")
+    if name.startswith("hlbm::"):
+        return name.split("(")[0]
+    it = _itanium_kernel(name)
+    if it is not None:  # mangled (_Float16 arguments): written out the same way
+        return f"hlbm::{it[0]}<{', '.join(it[1])}>"
+    return name.split("(")[0][:60]
+
+
 def kernel_steps(name: str) -> int:
     """Steps (iterations) that a launch of a sweep kernel takes: 2 or 4 of a multi-step pass."""
     import re
@@ -591,15 +602,7 @@ def summarize_profiles(d: str):
         with open(path, newline="") as fh:
             return list(csv.DictReader(fh))
 
-    def short(name):
-        name = name.replace("void ", "", 1)
-        if name.startswith("hlbm::"):
-            return name.split("(")[0]
-        it = _itanium_kernel(name)
-        if it is not None:  # mangled (_Float16 arguments): written out the same way
-            return f"hlbm::{it[0]}<{', '.join(it[1])}>"
-        return name.split("(")[0][:60]
-
+    short = short_kernel_name
     cmds = profile_commands(d)
 
     def copy_kib(sub, counter):

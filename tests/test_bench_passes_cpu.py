@@ -54,3 +54,12 @@ def test_bytes_of_the_launches_taken():
     d2 = H.make_desc(precision=H.FP64, nx=1100, ny=410)
     G = SimpleNamespace(desc=d2, q=9, n=1100 * 410)
     assert bench.pass_bytes_per_update(G)["primal"](4) == (2 * 72 + 8) / 4
+
+
+def test_short_kernel_names():
+    import bench
+    for name, want in (
+            ("void hlbm::k_window3d<float, true>(hlbm::Geo, hlbm::Window)", "hlbm::k_window3d<float, true>"),
+            ("void hlbm::(anonymous namespace)::k_packed2d<float>(hlbm::PackedPasses)", "hlbm::k_packed2d<float>"),
+            ("__amd_rocclr_copyBuffer", "__amd_rocclr_copyBuffer")):
+        assert bench.short_kernel_name(name) == want
