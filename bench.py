@@ -481,7 +481,7 @@ def kernel_kind(name: str):
     """(kind, parity) of a sweep kernel's (demangled or mangled) name, or
     (None, None)."""
     import re
-    m = re.match(r"(?:void )?hlbm::(k_\w+)<([^>]*)>", name)
+    m = re.match(r"(?:void )?hlbm::(?:\(anonymous namespace\)::)?(k_\w+)<([^>]*)>", name)
     if m:
         base, targs = m.group(1), [a.strip() for a in m.group(2).split(",")]
     else:
@@ -529,7 +529,7 @@ def short_kernel_name(name: str) -> str:
 def kernel_steps(name: str) -> int:
     """Steps (iterations) that a launch of a sweep kernel takes: 2 or 4 of a multi-step pass."""
     import re
-    m = re.match(r"(?:void )?hlbm::(k_\w+)<([^>]*)>", name)
+    m = re.match(r"(?:void )?hlbm::(?:\(anonymous namespace\)::)?(k_\w+)<([^>]*)>", name)
     base, targs = (m.group(1), [a.strip() for a in m.group(2).split(",")]) if m else (_itanium_kernel(name) or ("", []))
     if base in ("k_march2d", "k_window2d", "k_march2d_adjoint"):
         return int(targs[1])

@@ -18,6 +18,7 @@ def test_pass_kernels_map_to_sweep_kinds_and_steps():
         "void hlbm::k_window2d<float, 2, false, true>(hlbm::Geo)": ("primal_window_pass", 2),
         "void hlbm::k_march2d_adjoint<float, 4>(hlbm::Geo)": ("adjoint_pass", 4),
         "void hlbm::k_march3d<float, false, true>(hlbm::Geo)": ("primal_pass", 2),
+        "void hlbm::(anonymous namespace)::k_march3d_adjoint<double>(hlbm::Geo)": ("adjoint_pass", 2),
         "void hlbm::k_window3d<float, true>(hlbm::Geo)": ("primal_window_pass", 2),
         "void hlbm::k_march3d_adjoint<double>(hlbm::Geo)": ("adjoint_pass", 2),
         "void hlbm::k_window_region_copy<19, float, 2>(hlbm::ObjBox)": ("region_pass", 1),
