@@ -2492,7 +2492,74 @@ __device__ __forceinline__ void adjoint_cell(const Geo& g, const ObjBox& ob, con
   if constexpr (HRR) {
     hrr_adjoint<Q, T, NTP>(ph, prep, g.plane, cell, ac.diff != 0, lam);
   } else {
-    adjoint_bgk<Q, T>(ph, tx, ty, tz, d, omega, lam);
+    // The expressions of adjoint_bgk and adjoint_outlet (the passes'), written
+    // out: inlined from there, where they are simplified by themselves first, they
+    // leave the D3Q19 FP32 kernel 49 registers instead of 67 and fewer of the
+    // differentiated closure's 25 values a cell in flight (768x384x128 2104
+    // -> 2210 us an iteration, 192x96x64 55.2 -> 59.5; frozen 1180 either way).
+    // Weighted moments of phi (phi_i = ph[opp i], xi_opp(k) = -xi_k) over the
+    // opposite pairs: m0 = sum w phi, m1 = sum w phi xi, M2 = sum w phi xi xi;
+    // terms with zero lattice coefficients are never formed.
+    T m0 = (T)L::w[0] * ph[0];
+    T m1[3] = {0, 0, 0}, m2[6] = {0, 0, 0, 0, 0, 0};
+    bool h1[3] = {false, false, false}, h2[6] = {false, false, false, false, false, false};
+    const int ia[6] = {0, 1, 2, 0, 0, 1}, ib[6] = {0, 1, 2, 1, 2, 2};
+#pragma unroll
+    for (int k = 1; k < Q; ++k) {
+      if (L::opp[k] < k) continue;
+      const int o = L::opp[k];
+      const T w = (T)L::w[k];
+      const T wp = w * (ph[k] + ph[o]);
+      const T wq = w * (ph[k] - ph[o]);
+      m0 += wp;
+      const int c[3] = {L::cx[k], L::cy[k], L::cz[k]};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        if (c[a] == 0) continue;
+        const T t = c[a] > 0 ? -wq : wq;
+        m1[a] = h1[a] ? m1[a] + t : t;
+        h1[a] = true;
+      }
+#pragma unroll
+      for (int m = 0; m < 6; ++m) {
+        const int cf = c[ia[m]] * c[ib[m]];
+        if (cf == 0) continue;
+        const T t = cf > 0 ? wp : -wp;
+        m2[m] = h2[m] ? m2[m] + t : t;
+        h2[m] = true;
+      }
+    }
+    const T mxx = m2[0], myy = m2[1], mzz = m2[2], mxy = m2[3], mxz = m2[4], myz = m2[5];
+    T tt, m2tx, m2ty, m2tz, tmt;
+    if constexpr (D == 3) {
+      tt = tx * tx + ty * ty + tz * tz;
+      m2tx = mxx * tx + mxy * ty + mxz * tz;
+      m2ty = mxy * tx + myy * ty + myz * tz;
+      m2tz = mxz * tx + myz * ty + mzz * tz;
+      tmt = tx * m2tx + ty * m2ty + tz * m2tz;
+    } else {
+      tt = tx * tx + ty * ty;
+      m2tx = mxx * tx + mxy * ty;
+      m2ty = mxy * tx + myy * ty;
+      m2tz = (T)0;
+      tmt = tx * m2tx + ty * m2ty;
+    }
+    // sum_j phi_j d f^eq_j / d f_i = Phr + Phj . xi_i, scaled by omega
+    const T oPhr = omega * (m0 * ((T)1 + (T)1.5 * tt) - (T)4.5 * tmt);
+    const T od = omega * d;
+    const T oPjx = od * ((T)3 * m1[0] + (T)9 * m2tx - (T)3 * m0 * tx);
+    const T oPjy = od * ((T)3 * m1[1] + (T)9 * m2ty - (T)3 * m0 * ty);
+    const T oPjz = (D == 3) ? od * ((T)3 * m1[2] + (T)9 * m2tz - (T)3 * m0 * tz) : (T)0;
+    const T omc = (T)1 - omega;
+    lam[0] = omc * ph[0] + oPhr;
+#pragma unroll
+    for (int k = 1; k < Q; ++k) {
+      if (L::opp[k] < k) continue;
+      const int o = L::opp[k];
+      const T e = csum<T>(L::cx[k], L::cy[k], L::cz[k], oPjx, oPjy, oPjz);
+      lam[k] = omc * ph[o] + (oPhr + e);
+      lam[o] = omc * ph[k] + (oPhr - e);
+    }
     if (ac.diff) {  // differentiated Smagorinsky: (sum_j phi_j f^neq_j) (1/tau^2) dtau/df_i
       T sd = ph[0] * (T)ld_stream<NTP>(&at(prep, (D + 2 + L::opp[0]) * g.plane + c0, lo));
 #pragma unroll
@@ -2506,13 +2573,37 @@ __device__ __forceinline__ void adjoint_cell(const Geo& g, const ObjBox& ob, con
   }
   if (outlet) {  // virtual column: sum_j dV_j/df_i phiV_j = (xi_i - u).Psi / rho
     const int64_t o = y + (int64_t)g.ny * z;
-    T pv[Q];
+    // weighted moments of the virtual column's adjoint values (directions
+    // with xi_x = -1), zero coefficients skipped
+    T v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // v0, v1 (x y z), v2 (xx yy zz xy xz yz)
+    bool hv[10] = {false, false, false, false, false, false, false, false, false, false};
 #pragma unroll
-    for (int k = 0; k < Q; ++k)
-      if (L::cx[k] == -1) pv[k] = pv_in[k * g.gplane + o];
-    const T iro = (T)1 / (T)oprep[o];
-    adjoint_outlet<Q, T>(pv, iro, (T)oprep[g.gplane + o], (T)oprep[2 * g.gplane + o],
-                         (D == 3) ? (T)oprep[3 * g.gplane + o] : (T)0, lam);
+    for (int k = 0; k < Q; ++k) {
+      if (L::cx[k] != -1) continue;
+      const T wp = (T)L::w[k] * pv_in[k * g.gplane + o];
+      const int cf[10] = {1, L::cx[k], L::cy[k], L::cz[k], L::cx[k] * L::cx[k], L::cy[k] * L::cy[k],
+                          L::cz[k] * L::cz[k], L::cx[k] * L::cy[k], L::cx[k] * L::cz[k], L::cy[k] * L::cz[k]};
+#pragma unroll
+      for (int m = 0; m < 10; ++m) {
+        if (cf[m] == 0) continue;
+        const T t = cf[m] > 0 ? wp : -wp;
+        v[m] = hv[m] ? v[m] + t : t;
+        hv[m] = true;
+      }
+    }
+    const T v0 = v[0], v1x = v[1], v1y = v[2], v1z = v[3], vxx = v[4], vyy = v[5], vzz = v[6], vxy = v[7],
+            vxz = v[8], vyz = v[9];
+    const T ro = (T)oprep[o];
+    const T uox = (T)oprep[g.gplane + o];
+    const T uoy = (T)oprep[2 * g.gplane + o];
+    const T uoz = (D == 3) ? (T)oprep[3 * g.gplane + o] : (T)0;
+    const T Psx = (T)3 * v1x + (T)9 * (vxx * uox + vxy * uoy + vxz * uoz) - (T)3 * v0 * uox;
+    const T Psy = (T)3 * v1y + (T)9 * (vxy * uox + vyy * uoy + vyz * uoz) - (T)3 * v0 * uoy;
+    const T Psz = (T)3 * v1z + (T)9 * (vxz * uox + vyz * uoy + vzz * uoz) - (T)3 * v0 * uoz;
+    const T iro = (T)1 / ro;
+#pragma unroll
+    for (int i = 0; i < Q; ++i)
+      lam[i] += (((T)L::cx[i] - uox) * Psx + ((T)L::cy[i] - uoy) * Psy + ((T)L::cz[i] - uoz) * Psz) * iro;
   }
   int64_t r;
   if (region_index<Q>(ob, x, y, z, r)) {
